@@ -3,8 +3,9 @@
 //
 // Per column p (a bin of the row transforms; column 0 carries the real bins
 // p = 0 and p = M packed as U = C_0 + i C_M):
-//   [k >= 3: the y-solve of the interpolation system (Eq. (z_system); its
-//    k = 4, 5 counterparts) on the complex row spectra, FP64],
+//   [k >= 3: the values past the column's ends that stand for the interpolation
+//    system (bnd.hpp; bord, bc), or, MODE >= 2, the system solved on the
+//    column, FP64, for tables that do not hold its symbol],
 //   forward transform of the column zero-padded to 2N as its even and odd
 //   output bins: fe = FFT_N(a), fo = FFT_N(a_j w_2N^j),
 //   products with the spectra of w^x and w^y (convolution theorem, Eq. (eqnF)),
@@ -21,6 +22,7 @@
 // area of two slots (FP64, or N = 8192 in FP32), whose exchanges take a
 // barrier before their writes as well.
 #pragma once
+#include "bnd.hpp"
 #include "fft4.hpp"
 #include "kcommon.hpp"
 #include "sg_internal.h"
@@ -90,7 +92,7 @@ struct colfs_cfg {
   static constexpr bool KEEP = sizeof(R) == 4 && E == 8;
 };
 
-// MODE: 0 = k 1, 1 = k 2, 2 = k 3, 3 = k 4, 4 = k 5 (as k_col).
+// MODE: 0 odd k, 1 even k; 2, 3, 4 = k 3, 4, 5 with the y-solve inside.
 // SLOTS: LDS slots of N padded elements.  4: two exchange areas of two slots
 // used in turn (no exchange waits before its writes); 2: one area of two
 // slots; 1: one slot, every transform exchanged alone.  With fewer than four
@@ -137,7 +139,8 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS, int COMP, 
 __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj,
                                            const TO* __restrict__ tox, const TO* __restrict__ toy,
                                            const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-                                           const sg_bgrid* __restrict__ bg, cx<R>* smem) {
+                                           const sg_bgrid* __restrict__ bg, cx<R>* smem, int bord,
+                                           const double* __restrict__ bc) {
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
   constexpr bool solve = MODE >= 2;
   constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);
@@ -211,6 +214,9 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
   const TO* rowx = tox + (int64_t)c * (N + 1);
   const TO* rowy = toy + (int64_t)c * (N + 1);
   const int itn = it + (int)gridDim.x;
+  // bord (the order, with bc: bnd.hpp): the values past the column's ends
+  cx<R> end[2], start[2];
+  if (!solve && bord) bnd_line<N, T>(X + (int64_t)c * N, bord, bc, t, end, start);
   // this column's table entries first, then (PF) the next column: loads
   // complete in order, so waiting for the entries leaves the prefetch in
   // flight
@@ -251,6 +257,20 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
   for (int e = 0; e < E; ++e) {
     f[0][e] = a[e];
     f[1][e] = cmul(a[e], w2n_at(t, e));
+  }
+  if (!solve && bord) {
+    // folded onto elements 0, 1 (threads 0, 1) and N - 1, N - 2 (the last two)
+    const cx<R> w0 = w2n_at(t, 0), w1 = w2n_at(t, E - 1);
+    if (t < 2) {
+      const cx<R> z = t ? end[1] : end[0];
+      f[0][0] = f[0][0] + z;
+      f[1][0] = f[1][0] - cmul(z, w0);
+    }
+    if (t >= T - 2) {
+      const cx<R> z = t == T - 1 ? start[0] : start[1];
+      f[0][E - 1] = f[0][E - 1] + z;
+      f[1][E - 1] = f[1][E - 1] - cmul(z, w1);
+    }
   }
   if constexpr (SLOTS == 1) {
 #pragma unroll
@@ -459,9 +479,9 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS, int COMP, 
 __global__ void __launch_bounds__(N / E) SG_WAVES_PER_EU(colfs_wpe<R, N>::value)
     k_colfs(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
             const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-            const sg_bgrid* __restrict__ bg) {
+            const sg_bgrid* __restrict__ bg, int bord = 0, const double* __restrict__ bc = nullptr) {
   __shared__ cx<R> smem[colfs_cfg<R, N, E, SLOTS>::LDS];
-  colfs_body<R, TO, N, MODE, E, SLOTS, COMP, PF>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem);
+  colfs_body<R, TO, N, MODE, E, SLOTS, COMP, PF>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, bord, bc);
 }
 
 // Both force components of a column in one launch: the x pass (Yx into
@@ -472,11 +492,11 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS>
 __global__ void __launch_bounds__(N / E) SG_WAVES_PER_EU(colfs_wpe<R, N>::value)
     k_colfs_xy(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
                const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-               const sg_bgrid* __restrict__ bg) {
+               const sg_bgrid* __restrict__ bg, int bord = 0, const double* __restrict__ bc = nullptr) {
   __shared__ cx<R> smem[colfs_cfg<R, N, E, SLOTS>::LDS];
-  colfs_body<R, TO, N, MODE, E, SLOTS, 1, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem);
+  colfs_body<R, TO, N, MODE, E, SLOTS, 1, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, bord, bc);
   __syncthreads();
-  colfs_body<R, TO, N, MODE, E, SLOTS, 2, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem);
+  colfs_body<R, TO, N, MODE, E, SLOTS, 2, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, bord, bc);
 }
 
 // Plan-time spectrum columns of the long columns (FP64): column c of the
@@ -489,7 +509,7 @@ __global__ void __launch_bounds__(N / E) SG_WAVES_PER_EU(colfs_wpe<R, N>::value)
 template <int N, int E>
 __global__ void __launch_bounds__(N / E)
     k_specfs(const cx<double>* __restrict__ Sg, int M, void* __restrict__ tab, int kind, int fp32, double scale,
-             const cx<double>* __restrict__ r2n, const cx<double>* __restrict__ twfs) {
+             const cx<double>* __restrict__ r2n, const cx<double>* __restrict__ twfs, int solve = 0) {
   using S = fs_shape<N, E>;
   __shared__ cx<double> smem[S::SLOT];
   const int t = threadIdx.x;
@@ -544,6 +564,7 @@ __global__ void __launch_bounds__(N / E)
           sincospi((double)rows[v] / (2.0 * M) + (double)(2 * qq + h) / (2.0 * N), &sn, &cs);
           a = w.y * cs + w.x * sn;
         }
+        if (solve) a *= bnd_symbol(solve, rows[v], M) * bnd_symbol(solve, 2 * qq + h, N);
         const int64_t idx = (int64_t)rows[v] * (N + 1) + (h == 0 ? qq : N / 2 + 1 + qq);
         if (fp32 == 1) {
           const float hv = (float)a;
@@ -561,8 +582,8 @@ __global__ void __launch_bounds__(N / E)
 // Adjoint column pass for the long columns: the transposed convolution of
 // the gradients (gx, gy) with the weights (products with the conjugate
 // spectra, conj(i A) = -i A, summed over both components), cropped to N,
-// then the y-solve of the interpolation system (symmetric, so its own
-// transpose).  Xx, Xy: row spectra of gx, gy (column-major like X); Y: the
+// then the padding values' share of the interpolation system (bord, bc:
+// bnd.hpp), or, MODE >= 2, the y-solve (symmetric, so its own transpose).  Xx, Xy: row spectra of gx, gy (column-major like X); Y: the
 // packed row spectra of gC in tiles of tj rows, bin p of row j at
 // ((j/tj*2 + p%2)*(M/2) + p/2)*tj + j%tj.  SLOTS (1 or 2) arrays go through
 // each exchange; every exchange waits for the area to be free.
@@ -576,7 +597,8 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS>
 __global__ void __launch_bounds__(N / E)
     k_colfs_adj(const cx<R>* __restrict__ Xx, const cx<R>* __restrict__ Xy, cx<R>* __restrict__ Y, int M, int tj,
                 const TO* __restrict__ tox, const TO* __restrict__ toy, const cx<R>* __restrict__ r2n,
-                const cx<R>* __restrict__ twfs, const sg_bgrid* __restrict__ bg) {
+                const cx<R>* __restrict__ twfs, const sg_bgrid* __restrict__ bg, int bord = 0,
+                const double* __restrict__ bc = nullptr) {
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
   constexpr bool solve = MODE >= 2;
   constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);
@@ -763,8 +785,27 @@ __global__ void __launch_bounds__(N / E)
   }
   cx<R> acc[E];
   const int to = fresh_t();
+  cx<R> past{(R)0, (R)0}, before{(R)0, (R)0};  // slots N, N + 1 (threads 0, 1), -1, -2 (the last two)
 #pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = hs[0][e] + cmulc(hs[1][e], r2n[(unsigned)opaque(S::d1_index(to, e))]);
+  for (int e = 0; e < E; ++e) {
+    const cx<R> o = cmulc(hs[1][e], r2n[(unsigned)opaque(S::d1_index(to, e))]);
+    if (e == 0) past = hs[0][e] - o;
+    if (e == E - 1) before = hs[0][e] - o;
+    acc[e] = hs[0][e] + o;
+  }
+  if (!solve && bord) {
+    // the gradients found in the padding slots, to the threads of the ends
+    __syncthreads();
+    if (t < 2) smem[t] = past;
+    if (t >= T - 2) smem[2 + T - 1 - t] = before;
+    __syncthreads();
+    const cx<R> p0 = smem[0], p1 = smem[1], b0 = smem[2], b1 = smem[3];
+    const int len = bnd_reach(bord);
+    static_assert(S::B1 * S::LB2 >= kBndLen, "the ends lie in the first and the last element of a thread");
+    const int j0 = S::d1_index(to, 0), j1 = N - 1 - S::d1_index(to, E - 1);
+    if (j0 < len) acc[0] = bnd_add(acc[0], b0, b1, bc, j0);
+    if (j1 < len) acc[E - 1] = bnd_add(acc[E - 1], p0, p1, bc, j1);
+  }
   cx<R>* out = Y + (int64_t)(c & 1) * (M / 2) * tj + (int64_t)(c >> 1) * tj;
   const int64_t jstride = (int64_t)M * tj;
   if constexpr (solve) {

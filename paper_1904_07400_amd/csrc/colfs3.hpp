@@ -210,7 +210,7 @@ template <typename R, typename TO, int MODE, int L = 512>
 __global__ void __launch_bounds__(kC3T) SG_WAVES_PER_EU(SG_COLFS3_WPE)
     k_colfs3(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
              const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-             const sg_bgrid* __restrict__ bg) {
+             const sg_bgrid* __restrict__ bg, int bord = 0, const double* __restrict__ bc = nullptr) {
   using S3 = c3_shape<L>;
   constexpr int N = S3::N, E = S3::E, T = S3::T, SL = S3::SL;
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
@@ -235,12 +235,22 @@ __global__ void __launch_bounds__(kC3T) SG_WAVES_PER_EU(SG_COLFS3_WPE)
   // bin of register r within each half: 3 (lane + 64 r) + q
   auto bin = [&](int r) { return 3 * (lane + 64 * r) + q; };
 
-  // ---- the column (chunk of E per thread) and this thread's table entries
+  // ---- the column (chunk of E per thread for the solve) and this thread's
+  // table entries
+  const cx<R>* col = X + (int64_t)c * N;
+  auto at = [&](int e) { return solve ? t * E + e : t + T * e; };
   cx<R> a[E];
-  {
-    const cx<R>* col = X + (int64_t)c * N;
 #pragma unroll
-    for (int e = 0; e < E; ++e) a[e] = col[(unsigned)(t * E + e)];
+  for (int e = 0; e < E; ++e) a[e] = col[(unsigned)at(e)];
+  // bord (the order, with bc: bnd.hpp): the values past the column's ends,
+  // folded onto elements 0, 1 (lanes 0, 1) and N - 2, N - 1 (lanes 62, 63); each
+  // wave of the radix-3 step meets all four
+  cx<R> end{(R)0, (R)0}, start{(R)0, (R)0};
+  if (!solve && bord) {
+    cx<R> ev[2], sv[2];
+    bnd_line<N, 64>(col, bord, bc, lane, ev, sv);
+    if (lane < 2) end = ev[lane & 1];
+    if (lane >= 62) start = sv[(63 - lane) & 1];
   }
   TO tv[pre ? 4 : 1][pre ? E : 1];
   if constexpr (pre) {
@@ -264,7 +274,7 @@ __global__ void __launch_bounds__(kC3T) SG_WAVES_PER_EU(SG_COLFS3_WPE)
     for (int e = 0; e < E; ++e) a[e] = cx<R>{(R)d[e].x, (R)d[e].y};
   }
 #pragma unroll
-  for (int e = 0; e < E; ++e) smem[fspad(t * E + e)] = a[e];
+  for (int e = 0; e < E; ++e) smem[fspad(at(e))] = a[e];
   __syncthreads();
 
   // ---- forward radix-3 step: f[0] for x, f[1] for x_j w_2N^j
@@ -275,8 +285,14 @@ __global__ void __launch_bounds__(kC3T) SG_WAVES_PER_EU(SG_COLFS3_WPE)
     for (int e = 0; e < E; ++e) {
       const int n = lane + 64 * e;
       const cx<R> x0 = smem[fspad(n)], x1 = smem[fspad(n + L)], x2 = smem[fspad(n + 2 * L)];
-      f[0][e] = c3_sum<2 * qc>(x0, x1, x2);
-      f[1][e] = c3_sum<2 * qc + 1>(x0, x1, x2);
+      if (!solve && (e == 0 || e == E - 1)) {
+        const cx<R> h0 = e == 0 ? end : cx<R>{(R)0, (R)0}, h2 = e == E - 1 ? start : cx<R>{(R)0, (R)0};
+        f[0][e] = c3_sum<2 * qc>(x0 + h0, x1, x2 + h2);
+        f[1][e] = c3_sum<2 * qc + 1>(x0 - h0, x1, x2 - h2);
+      } else {
+        f[0][e] = c3_sum<2 * qc>(x0, x1, x2);
+        f[1][e] = c3_sum<2 * qc + 1>(x0, x1, x2);
+      }
       if constexpr (qc != 0) f[0][e] = cmul(f[0][e], r2n[(unsigned)(2 * qc * n)]);  // w_N^(n q) = w_2N^(2 n q)
       f[1][e] = cmul(f[1][e], r2n[(unsigned)((2 * qc + 1) * n)]);
     }

@@ -176,6 +176,51 @@ void gl_rule(int q, double* x, double* w) {
   }
 }
 
+// Entries of a padding-value coefficient table (bnd.hpp): c0, then c1.
+constexpr int kBndTable = 48;
+
+// The coefficients of order k's interpolation system for lines of n values:
+// with g_i = (A^-1)_0i, h_i = (A^-1)_1i and A the integer stencil matrix, c0 = g
+// (k = 3, 4), c0 = 76 g + h and c1 = g (k = 5), as many as fall above 1e-18 of
+// the first.  The rows of A^-1 come from the banded elimination of A g = e_0
+// and A h = e_1, long double.
+std::vector<double> bnd_table(int k, int n) {
+  std::vector<double> out(2 * kBndTable, 0.0);
+  const int hb = k == 5 ? 2 : 1, reach = k == 3 ? 24 : (k == 4 ? 32 : 42);
+  const long double st[3] = {k == 3 ? 6.0L : (k == 4 ? 4.0L : 230.0L), k == 5 ? 76.0L : 1.0L, 1.0L};
+  // A = L D L^T (symmetric, diagonally dominant); the far end of a line of
+  // four times the reach moves the first rows by less than their rounding
+  const int m = std::min(n, 4 * kBndTable);
+  std::vector<std::array<long double, 3>> l(m);
+  std::vector<long double> d(m);
+  for (int i = 0; i < m; ++i) {
+    l[i] = {1.0L, 0.0L, 0.0L};
+    for (int b = std::min(hb, i); b >= 1; --b) {
+      long double v = st[b];
+      for (int c = b + 1; c <= std::min(hb, i); ++c) v -= l[i][c] * d[i - c] * l[i - b][c - b];
+      l[i][b] = v / d[i - b];
+    }
+    d[i] = st[0];
+    for (int c = 1; c <= std::min(hb, i); ++c) d[i] -= l[i][c] * l[i][c] * d[i - c];
+  }
+  auto row = [&](int r) {
+    std::vector<long double> x(m, 0.0L);
+    x[r] = 1.0L;
+    for (int i = 0; i < m; ++i)
+      for (int b = 1; b <= std::min(hb, i); ++b) x[i] -= l[i][b] * x[i - b];
+    for (int i = 0; i < m; ++i) x[i] /= d[i];
+    for (int i = m - 1; i >= 0; --i)
+      for (int b = 1; b <= std::min(hb, m - 1 - i); ++b) x[i] -= l[i + b][b] * x[i + b];
+    return x;
+  };
+  const std::vector<long double> g = row(0), h = k == 5 ? row(1) : g;
+  for (int i = 0; i < std::min(m, reach); ++i) {
+    out[i] = (double)(k == 5 ? 76.0L * g[i] + h[i] : g[i]);
+    if (k == 5) out[kBndTable + i] = (double)g[i];
+  }
+  return out;
+}
+
 struct GridPlan {
   sg_grid g;
   int M, N, k, kind;
@@ -194,6 +239,8 @@ struct GridPlan {
   bool fs = false;          // columns by the four-step pass (long columns, and 1536 in FP32)
   bool fs_adj = false;      // ... in the adjoint as well (the long columns)
   void* twfs = nullptr;     // its twiddle table
+  double* bcm = nullptr;    // k >= 3: coefficient tables of the padding values of rows and columns
+  double* bcn = nullptr;
   int tab_bytes = 8;        // bytes per spectrum entry: double, float hi + lo, or float
 };
 
@@ -430,13 +477,14 @@ sg_status build_spectra(sg_plan p, GridPlan& G, const void* r2m64, const void* r
     }
   }
   auto spec = [&](void* tab) {
-    return N == 8192 ? sg_launch_specfs(N, S, M, tab, G.kind, fp32, scale, r2n64, twfs64, p->st)
-                     : sg_launch_spec_col(N, S, M, tab, G.kind, fp32, scale, r2n64, twS64, p->st);
+    const int solve = G.k >= 3 ? G.k : 0;
+    return N == 8192 ? sg_launch_specfs(N, S, M, tab, G.kind, fp32, solve, scale, r2n64, twfs64, p->st)
+                     : sg_launch_spec_col(N, S, M, tab, G.kind, fp32, solve, scale, r2n64, twS64, p->st);
   };
   e = sg_launch_weights(G.k, G.hx, G.hy, M, N, wpx, wpy, 0, p->st);
-  if (e == hipSuccess) e = sg_launch_row_fwd(0, M, wpx, 2 * M, S, 2 * N, r2m64, 0, 1, twA64, nullptr, 1, 0, p->st);
+  if (e == hipSuccess) e = sg_launch_row_fwd(0, M, wpx, 2 * M, S, 2 * N, r2m64, 0, nullptr, 1, twA64, nullptr, 1, 0, p->st);
   if (e == hipSuccess) e = spec(G.tabx);
-  if (e == hipSuccess) e = sg_launch_row_fwd(0, M, wpy, 2 * M, S, 2 * N, r2m64, 0, 1, twA64, nullptr, 1, 0, p->st);
+  if (e == hipSuccess) e = sg_launch_row_fwd(0, M, wpy, 2 * M, S, 2 * N, r2m64, 0, nullptr, 1, twA64, nullptr, 1, 0, p->st);
   if (e == hipSuccess) e = spec(G.taby);
   if (e == hipSuccess) e = hipStreamSynchronize(p->st);
   if (e != hipSuccess) st = hip_check(p, e, "plan-time spectrum");
@@ -458,9 +506,9 @@ hipError_t launch_cols(sg_plan p, const GridClass& c, int tile, hipStream_t q, c
   const int tj = sg_row_tile(prec, c.M, c.N);
   const sg_bgrid* d = desc ? desc : c.desc;
   if (G.fs)
-    return sg_launch_colfs(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.tab_bytes, G.r2n, solve,
+    return sg_launch_colfs(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.tab_bytes, G.r2n, solve, G.bcn,
                            G.twfs, d, ng, q);
-  return sg_launch_col(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.r2n, solve, G.twB, d, ng,
+  return sg_launch_col(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.r2n, solve, G.bcn, G.twB, d, ng,
                        tile, c.var[1], q);
 }
 
@@ -482,7 +530,7 @@ hipError_t issue_class(sg_plan p, const GridClass& c, const void* sigma, void* f
   const GridPlan& G = p->grids[c.members[0]];
   const int solve = c.k >= 3 ? c.k : 0;
   const int ng = (int)c.members.size();
-  hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, 0, G.twA, c.desc, ng, tile[0], q);
+  hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, 0, G.twA, c.desc, ng, tile[0], q);
   if (e == hipSuccess) e = launch_cols(p, c, tile[1], q);
   if (e == hipSuccess) e = launch_rows_inv(p, c, fx, fy, tile[2], q, c.desc);
   return e;
@@ -544,7 +592,7 @@ sg_status time_tile(sg_plan p, GridClass& c, int pass, int tile, const void* sig
   hipError_t e = hipSuccess;
   auto launch = [&](int ps) -> hipError_t {
     if (ps == 0)
-      return sg_launch_row_fwd(prec, c.M, sig, c.M, nullptr, c.N, G.r2m, solve, 0, G.twA, c.desc, ng, t3[0], p->st);
+      return sg_launch_row_fwd(prec, c.M, sig, c.M, nullptr, c.N, G.r2m, solve, G.bcm, 0, G.twA, c.desc, ng, t3[0], p->st);
     if (ps == 1) return launch_cols(p, c, t3[1], p->st);
     return launch_rows_inv(p, c, fx, fy, t3[2], p->st, c.desc);
   };
@@ -862,6 +910,7 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
   std::map<std::pair<int, int>, void*> tw;  // (pass, length) -> stage twiddles
   std::map<std::tuple<int, int, int, double, double, int>, std::pair<void*, void*>> spectra;  // shared weight spectra
   std::map<int, void*> twfs;  // four-step twiddle tables by length
+  std::map<std::pair<int, int>, void*> bnd;  // (order, line length) -> padding-value coefficients
   sg_status s = SG_OK;
   int64_t off = 0;
   for (int i = 0; i < ngrids && s == SG_OK; ++i) {
@@ -949,6 +998,18 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
           twfs[G.N] = d;
         }
         G.twfs = twfs[G.N];
+      }
+      for (int ax = 0; ax < 2 && s == SG_OK && G.k >= 3; ++ax) {
+        const auto bk = std::make_pair(G.k, ax ? G.N : G.M);
+        if (!bnd.count(bk)) {
+          const std::vector<double> h = bnd_table(bk.first, bk.second);
+          void* d = nullptr;
+          s = dev_alloc(p, &d, h.size() * sizeof(double));
+          if (s == SG_OK)
+            s = hip_check(p, hipMemcpy(d, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy bnd");
+          if (s == SG_OK) bnd[bk] = d;
+        }
+        if (s == SG_OK) (ax ? G.bcn : G.bcm) = (double*)bnd[bk];
       }
       if (s == SG_OK && fresh) s = build_spectra(p, G, roots64[2 * G.M], roots64[2 * G.N]);
     }
@@ -1208,7 +1269,7 @@ sg_status sg_forces(sg_plan p, const void* sigma, void* fx, void* fy) {
     const int ng = (int)c.members.size();
     const int tj = sg_row_tile(prec, c.M, c.N);
     if (e == hipSuccess)
-      e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, 0, G.twA, c.desc, ng, c.tile[0], p->st);
+      e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, 0, G.twA, c.desc, ng, c.tile[0], p->st);
     if (e == hipSuccess) e = mark(p);
     if (e == hipSuccess) e = launch_cols(p, c, c.tile[1], p->st);
     if (e == hipSuccess) e = mark(p);
@@ -1238,7 +1299,7 @@ sg_status sg_forces_noalloc(sg_plan p, const void* sigma, void* fx, void* fy) {
     const int solve = c.k >= 3 ? c.k : 0;
     const int ng = (int)c.members.size();
     const int tj = sg_row_tile(prec, c.M, c.N);
-    hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, 0, G.twA, c.desc_s, ng,
+    hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, 0, G.twA, c.desc_s, ng,
                                      c.tile[0], p->st);
     if (e == hipSuccess) e = launch_cols(p, c, c.tile[1], p->st, c.desc_s);
     if (e == hipSuccess) e = launch_rows_inv(p, c, fx, fy, c.tile[2], p->st, c.desc_s);
@@ -1341,17 +1402,17 @@ sg_status sg_forces_adjoint(sg_plan p, const void* gfx, const void* gfy, void* g
     const int ng = (int)c.members.size();
     const int tj = sg_row_tile(prec, c.M, c.N);
     hipError_t e =
-        sg_launch_row_fwd(prec, c.M, gfx, c.M, nullptr, c.N, G.r2m, 0, 0, G.twA, c.desc, ng, c.tile[0], p->st);
+        sg_launch_row_fwd(prec, c.M, gfx, c.M, nullptr, c.N, G.r2m, 0, nullptr, 0, G.twA, c.desc, ng, c.tile[0], p->st);
     if (e == hipSuccess)
-      e = sg_launch_row_fwd(prec, c.M, gfy, c.M, nullptr, c.N, G.r2m, 0, 0, G.twA, c.desc_y, ng, c.tile[0], p->st);
+      e = sg_launch_row_fwd(prec, c.M, gfy, c.M, nullptr, c.N, G.r2m, 0, nullptr, 0, G.twA, c.desc_y, ng, c.tile[0], p->st);
     if (e == hipSuccess && G.fs_adj) {
       e = sg_launch_colfs_adj(prec, c.N, nullptr, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.tab_bytes, G.r2n,
-                              solve, G.twfs, c.desc, ng, p->st);
+                              solve, G.bcn, G.twfs, c.desc, ng, p->st);
       if (e == hipSuccess)
-        e = sg_launch_row_c2r(prec, c.M, c.N, nullptr, gsigma, tj, G.r2m, solve, G.twA, c.desc, ng, p->st);
+        e = sg_launch_row_c2r(prec, c.M, c.N, nullptr, gsigma, tj, G.r2m, solve, G.bcm, G.twA, c.desc, ng, p->st);
     } else if (e == hipSuccess) {
       e = sg_launch_adjoint_tail(prec, c.M, c.N, nullptr, nullptr, nullptr, gsigma, tj, nullptr, nullptr, G.kind, G.r2m,
-                                 G.r2n, solve, G.twB, G.twA, c.desc, ng, p->st);
+                                 G.r2n, solve, G.bcm, G.bcn, G.twB, G.twA, c.desc, ng, p->st);
     }
     if (e != hipSuccess) return hip_check(p, e, "adjoint launch");
   }

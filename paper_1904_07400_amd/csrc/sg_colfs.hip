@@ -107,49 +107,47 @@ struct colfs_pf {
 
 template <typename R, typename TO, int N, int MODE, int COMP>
 static void launch_colfs_k(const cx<R>* X, cx<R>* V, int M, int tj, const TO* tox, const TO* toy, const cx<R>* r2n,
-                           const cx<R>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
+                           const cx<R>* tw, const sg_bgrid* bg, int ngrids, int bord, const double* bc,
+                           hipStream_t st) {
   using Sel = colfs_sel<R, N>;
   if constexpr (colfs_pf<R, TO, N, MODE>::on && COMP == 0) {
     static const int cus = device_cus();
     const int slots = cus * colfs_pf<R, TO, N, MODE>::per_cu;
     const int nb = M < slots ? M : slots;
     hipLaunchKernelGGL((k_colfs<R, TO, N, MODE, Sel::E, Sel::SLOTS, COMP, true>), dim3(nb, bg ? ngrids : 1),
-                       dim3(N / Sel::E), 0, st, X, V, M, tj, tox, toy, r2n, tw, bg);
+                       dim3(N / Sel::E), 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, bord, bc);
   } else {
     hipLaunchKernelGGL((k_colfs<R, TO, N, MODE, Sel::E, Sel::SLOTS, COMP>), dim3(M, bg ? ngrids : 1),
-                       dim3(N / Sel::E), 0, st, X, V, M, tj, tox, toy, r2n, tw, bg);
+                       dim3(N / Sel::E), 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, bord, bc);
   }
 }
 
 template <typename R, typename TO, int N, int MODE>
 static hipError_t launch_colfs_m(const cx<R>* X, cx<R>* V, int M, int tj, const TO* tox, const TO* toy,
-                                 const cx<R>* r2n, const cx<R>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
+                                 const cx<R>* r2n, const cx<R>* tw, const sg_bgrid* bg, int ngrids, int bord,
+                                 const double* bc, hipStream_t st) {
   using Sel = colfs_sel<R, N>;
   if constexpr (Sel::SPLIT && SG_COLFS_XY && sizeof(R) == 4) {
     // both component passes of a column in one launch
     hipLaunchKernelGGL((k_colfs_xy<R, TO, N, MODE, Sel::E, Sel::SLOTS>), dim3(M, bg ? ngrids : 1), dim3(N / Sel::E),
-                       0, st, X, V, M, tj, tox, toy, r2n, tw, bg);
+                       0, st, X, V, M, tj, tox, toy, r2n, tw, bg, bord, bc);
   } else if constexpr (Sel::SPLIT) {
-    launch_colfs_k<R, TO, N, MODE, 1>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-    launch_colfs_k<R, TO, N, MODE, 2>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
+    launch_colfs_k<R, TO, N, MODE, 1>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, bord, bc, st);
+    launch_colfs_k<R, TO, N, MODE, 2>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, bord, bc, st);
   } else {
-    launch_colfs_k<R, TO, N, MODE, 0>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
+    launch_colfs_k<R, TO, N, MODE, 0>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, bord, bc, st);
   }
   return hipGetLastError();
 }
 
 template <typename R, typename TO, int N>
 static hipError_t launch_colfs_t(const cx<R>* X, cx<R>* V, int M, int tj, const void* tx, const void* ty, int kind,
-                                 const cx<R>* r2n, int solve, const cx<R>* tw, const sg_bgrid* bg, int ngrids,
-                                 hipStream_t st) {
+                                 const cx<R>* r2n, int solve, const double* bc, const cx<R>* tw, const sg_bgrid* bg,
+                                 int ngrids, hipStream_t st) {
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
-  // modes: 0 = k 1, 1 = k 2, 2 = k 3, 3 = k 4, 4 = k 5 (solve = k for k >= 3)
-  if (solve == 4) return launch_colfs_m<R, TO, N, 3>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-  if (solve == 5) return launch_colfs_m<R, TO, N, 4>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-  if (kind == 1) return launch_colfs_m<R, TO, N, 1>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-  if (solve) return launch_colfs_m<R, TO, N, 2>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-  return launch_colfs_m<R, TO, N, 0>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
+  if (kind == 1) return launch_colfs_m<R, TO, N, 1>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, solve, bc, st);
+  return launch_colfs_m<R, TO, N, 0>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, solve, bc, st);
 }
 
 template <typename R, int N>
@@ -224,33 +222,27 @@ static hipError_t colfs_len(int N, F f) {
 namespace sg {
 template <typename TO, int L>
 static hipError_t launch_colfs3(const cx<float>* X, cx<float>* V, int M, int tj, const void* tx, const void* ty,
-                                int kind, const cx<float>* r2n, int solve, const cx<float>* tw, const sg_bgrid* bg,
-                                int ngrids, hipStream_t st) {
+                                int kind, const cx<float>* r2n, int solve, const double* bc, const cx<float>* tw,
+                                const sg_bgrid* bg, int ngrids, hipStream_t st) {
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
   const dim3 grid(M, bg ? ngrids : 1), blk(kC3T);
-  if (solve == 4)
-    hipLaunchKernelGGL((k_colfs3<float, TO, 3, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg);
-  else if (solve == 5)
-    hipLaunchKernelGGL((k_colfs3<float, TO, 4, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg);
-  else if (kind == 1)
-    hipLaunchKernelGGL((k_colfs3<float, TO, 1, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg);
-  else if (solve)
-    hipLaunchKernelGGL((k_colfs3<float, TO, 2, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg);
+  if (kind == 1)
+    hipLaunchKernelGGL((k_colfs3<float, TO, 1, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, solve, bc);
   else
-    hipLaunchKernelGGL((k_colfs3<float, TO, 0, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg);
+    hipLaunchKernelGGL((k_colfs3<float, TO, 0, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, solve, bc);
   return hipGetLastError();
 }
 }  // namespace sg
 
 hipError_t sg_launch_colfs(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                           int kind, int tab_bytes, const void* r2n, int solve, const void* tw, const sg_bgrid* bg,
-                           int ngrids, hipStream_t st) {
+                           int kind, int tab_bytes, const void* r2n, int solve, const double* bc, const void* tw,
+                           const sg_bgrid* bg, int ngrids, hipStream_t st) {
   if (N == 1536 || N == 768) {
     if (prec != 1 || tab_bytes != 8) return hipErrorInvalidValue;
     auto go = [&](auto ll) {
       return launch_colfs3<float2, decltype(ll)::value>((const cx<float>*)X, (cx<float>*)V, M, tj, tx, ty, kind,
-                                                        (const cx<float>*)r2n, solve, (const cx<float>*)tw, bg, ngrids,
+                                                        (const cx<float>*)r2n, solve, bc, (const cx<float>*)tw, bg, ngrids,
                                                         st);
     };
     return N == 1536 ? go(std::integral_constant<int, 512>{}) : go(std::integral_constant<int, 256>{});
@@ -262,7 +254,7 @@ hipError_t sg_launch_colfs(int prec, int N, const void* X, void* V, int M, int t
     const cx<double>* rd = (const cx<double>*)r2n;
     const cx<double>* td = (const cx<double>*)tw;
     return colfs_len(N, [&](auto n) {
-      return launch_colfs_t<double, double, decltype(n)::value>(Xd, Vd, M, tj, tx, ty, kind, rd, solve, td, bg, ngrids,
+      return launch_colfs_t<double, double, decltype(n)::value>(Xd, Vd, M, tj, tx, ty, kind, rd, solve, bc, td, bg, ngrids,
                                                                 st);
     });
   }
@@ -273,8 +265,8 @@ hipError_t sg_launch_colfs(int prec, int N, const void* X, void* V, int M, int t
   return colfs_len(N, [&](auto n) {
     constexpr int NN = decltype(n)::value;
     if (tab_bytes == 8)
-      return launch_colfs_t<float, float2, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, solve, tf, bg, ngrids, st);
-    return launch_colfs_t<float, float, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, solve, tf, bg, ngrids, st);
+      return launch_colfs_t<float, float2, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
+    return launch_colfs_t<float, float, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
   });
 }
 
@@ -289,30 +281,27 @@ struct colfs_adj_sel {
 template <typename R, typename TO, int N, int MODE>
 static hipError_t launch_colfs_adj_m(const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y, int M, int tj, const TO* tox,
                                      const TO* toy, const cx<R>* r2n, const cx<R>* tw, const sg_bgrid* bg,
-                                     int ngrids, hipStream_t st) {
+                                     int ngrids, int bord, const double* bc, hipStream_t st) {
   using Sel = colfs_adj_sel<R, N>;
   hipLaunchKernelGGL((k_colfs_adj<R, TO, N, MODE, Sel::E, Sel::SLOTS>), dim3(M, bg ? ngrids : 1), dim3(N / Sel::E), 0,
-                     st, Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg);
+                     st, Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, bord, bc);
   return hipGetLastError();
 }
 
 template <typename R, typename TO, int N>
 static hipError_t launch_colfs_adj_t(const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y, int M, int tj, const void* tx,
-                                     const void* ty, int kind, const cx<R>* r2n, int solve, const cx<R>* tw,
-                                     const sg_bgrid* bg, int ngrids, hipStream_t st) {
+                                     const void* ty, int kind, const cx<R>* r2n, int solve, const double* bc,
+                                     const cx<R>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
-  if (solve == 4) return launch_colfs_adj_m<R, TO, N, 3>(Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-  if (solve == 5) return launch_colfs_adj_m<R, TO, N, 4>(Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-  if (kind == 1) return launch_colfs_adj_m<R, TO, N, 1>(Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-  if (solve) return launch_colfs_adj_m<R, TO, N, 2>(Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
-  return launch_colfs_adj_m<R, TO, N, 0>(Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, ngrids, st);
+  if (kind == 1) return launch_colfs_adj_m<R, TO, N, 1>(Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, ngrids, solve, bc, st);
+  return launch_colfs_adj_m<R, TO, N, 0>(Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, ngrids, solve, bc, st);
 }
 }  // namespace sg
 
 hipError_t sg_launch_colfs_adj(int prec, int N, const void* Xx, const void* Xy, void* Y, int M, int tj, const void* tx,
-                               const void* ty, int kind, int tab_bytes, const void* r2n, int solve, const void* tw,
-                               const sg_bgrid* bg, int ngrids, hipStream_t st) {
+                               const void* ty, int kind, int tab_bytes, const void* r2n, int solve, const double* bc,
+                               const void* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   if (prec == 0) {
     if (tab_bytes != 8) return hipErrorInvalidValue;
     const cx<double>* a = (const cx<double>*)Xx;
@@ -321,7 +310,7 @@ hipError_t sg_launch_colfs_adj(int prec, int N, const void* Xx, const void* Xy, 
     const cx<double>* rd = (const cx<double>*)r2n;
     const cx<double>* td = (const cx<double>*)tw;
     return colfs_len(N, [&](auto n) {
-      return launch_colfs_adj_t<double, double, decltype(n)::value>(a, b, y, M, tj, tx, ty, kind, rd, solve, td, bg,
+      return launch_colfs_adj_t<double, double, decltype(n)::value>(a, b, y, M, tj, tx, ty, kind, rd, solve, bc, td, bg,
                                                                     ngrids, st);
     });
   }
@@ -333,16 +322,16 @@ hipError_t sg_launch_colfs_adj(int prec, int N, const void* Xx, const void* Xy, 
   return colfs_len(N, [&](auto n) {
     constexpr int NN = decltype(n)::value;
     if (tab_bytes == 8)
-      return launch_colfs_adj_t<float, float2, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, tf, bg, ngrids, st);
-    return launch_colfs_adj_t<float, float, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, tf, bg, ngrids, st);
+      return launch_colfs_adj_t<float, float2, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
+    return launch_colfs_adj_t<float, float, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
   });
 }
 
 // ------------------------------------------------------- spectrum (plan) --
-hipError_t sg_launch_specfs(int N, const void* rowspec, int M, void* tab, int kind, int fp32, double scale,
+hipError_t sg_launch_specfs(int N, const void* rowspec, int M, void* tab, int kind, int fp32, int solve, double scale,
                             const void* r2n, const void* tw, hipStream_t st) {
   if (N != 8192) return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_specfs<8192, 16>), dim3(M), dim3(512), 0, st, (const cx<double>*)rowspec, M, tab, kind, fp32,
-                     scale, (const cx<double>*)r2n, (const cx<double>*)tw);
+                     scale, (const cx<double>*)r2n, (const cx<double>*)tw, solve);
   return hipGetLastError();
 }

@@ -24,9 +24,10 @@ hipError_t sg_set_gl_tables(const double* x /*4x16*/, const double* w /*4x16*/);
 hipError_t sg_launch_weights(int k, double hx, double hy, int M, int N, double* wx, double* wy, int layout,
                              hipStream_t st);
 // tw: stage twiddle tables of the pass (sg_twiddles).  solve: 0 for k = 1, 2,
-// else the order k (3, 4, 5) of the interpolation system solved on the way
+// else the order k (3, 4, 5) of the interpolation system that the spectra hold,
+// and bc the coefficient table of the line's padding values (bnd.hpp)
 hipError_t sg_launch_row_fwd(int prec, int M, const void* src, int64_t ld, void* X, int nrows, const void* r2m,
-                             int solve, int full, const void* tw, const sg_bgrid* bg, int ngrids, int tile,
+                             int solve, const double* bc, int full, const void* tw, const sg_bgrid* bg, int ngrids, int tile,
                              hipStream_t st);
 // Launch variants of a pass (0 = A, 1 = B, 2 = C) for a transform length
 // (kernels of the same result with other buffering or elements per
@@ -40,12 +41,13 @@ int sg_max_tile(int prec, int pass, int len, int variant);
 // odd k (tables of A, W = i A), 1 for even k (W = ph i A, ph the bin's
 // half-cell phase); tx, ty are the quarter tables of A in either case.
 hipError_t sg_launch_col(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                         int kind, const void* r2n, int solve, const void* tw, const sg_bgrid* bg, int ngrids,
-                         int tile, int variant, hipStream_t st);
+                         int kind, const void* r2n, int solve, const double* bc, const void* tw, const sg_bgrid* bg,
+                         int ngrids, int tile, int variant, hipStream_t st);
 int sg_row_tile(int prec, int M, int N);
 hipError_t sg_launch_row_inv(int prec, int M, const void* V, void* fx, void* fy, int nrows, int tj, const void* r2m,
                              const void* tw, const sg_bgrid* bg, int ngrids, int tile, int variant, hipStream_t st);
-hipError_t sg_launch_spec_col(int N, const void* S, int M, void* tab, int kind, int fp32, double scale,
+// solve: the order whose inverse symbols multiply the spectra, or 0
+hipError_t sg_launch_spec_col(int N, const void* S, int M, void* tab, int kind, int fp32, int solve, double scale,
                               const void* r2n, const void* tw, hipStream_t st);
 // Stage twiddle tables of a pass's FFT (pass 0: forward rows, 1: columns,
 // 2: inverse rows, 3: spectrum columns, FP64 only, 4: inverse rows in
@@ -58,12 +60,13 @@ hipError_t sg_launch_coeff_rows(int prec, int M, const void* src, void* dst, int
 hipError_t sg_launch_coeff_cols(int prec, int N, void* data, int M, int k, hipStream_t st);
 // Adjoint after the two forward row transforms of gx, gy (Xx, Xy
 // column-major like X): conjugate-spectrum column pass into Y (tiles of tj
-// rows), then the inverse real row pass with the x-solve into gsigma.
+// rows), then the inverse real row pass into gsigma (bcm, bcn: the coefficient
+// tables of rows and columns).
 // Batched (bg != NULL): Xx, Xy, Y and gsigma come from the descriptors (X,
 // the two halves of V, the offset into the packed gsigma base).
 hipError_t sg_launch_adjoint_tail(int prec, int M, int N, const void* Xx, const void* Xy, void* Y, void* gsigma,
                                   int tj, const void* tx, const void* ty, int kind, const void* r2m, const void* r2n,
-                                  int solve, const void* twB, const void* twA, const sg_bgrid* bg, int ngrids,
+                                  int solve, const double* bcm, const double* bcn, const void* twB, const void* twA, const sg_bgrid* bg, int ngrids,
                                   hipStream_t st);
 // Four-step column pass for long columns (sg_colfs.hip): supported
 // (precision, N); its twiddle table (entry count, and filled from long double
@@ -72,18 +75,18 @@ hipError_t sg_launch_adjoint_tail(int prec, int M, int N, const void* Xx, const 
 int sg_colfs_supported(int prec, int N);
 int sg_colfs_twiddles(int prec, int N, double* re, double* im);
 hipError_t sg_launch_colfs(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                           int kind, int tab_bytes, const void* r2n, int solve, const void* tw, const sg_bgrid* bg,
-                           int ngrids, hipStream_t st);
+                           int kind, int tab_bytes, const void* r2n, int solve, const double* bc, const void* tw,
+                           const sg_bgrid* bg, int ngrids, hipStream_t st);
 // Adjoint column pass of the long columns (the arguments of the column
 // pass of sg_launch_adjoint_tail, plus tab_bytes).
 hipError_t sg_launch_colfs_adj(int prec, int N, const void* Xx, const void* Xy, void* Y, int M, int tj, const void* tx,
-                               const void* ty, int kind, int tab_bytes, const void* r2n, int solve, const void* tw,
-                               const sg_bgrid* bg, int ngrids, hipStream_t st);
+                               const void* ty, int kind, int tab_bytes, const void* r2n, int solve, const double* bc,
+                               const void* tw, const sg_bgrid* bg, int ngrids, hipStream_t st);
 // Plan-time spectrum columns of length 8192 (FP64; tw: the FP64 four-step
 // twiddle table of that length; fp32: 0 double, 1 float hi + lo, 2 float).
-hipError_t sg_launch_specfs(int N, const void* rowspec, int M, void* tab, int kind, int fp32, double scale,
+hipError_t sg_launch_specfs(int N, const void* rowspec, int M, void* tab, int kind, int fp32, int solve, double scale,
                             const void* r2n, const void* tw, hipStream_t st);
 // The inverse real row pass of the adjoint alone (after a column pass that
 // wrote the packed gC spectra Y; batched: Y from the descriptors).
 hipError_t sg_launch_row_c2r(int prec, int M, int N, const void* Y, void* gsigma, int tj, const void* r2m, int solve,
-                             const void* twA, const sg_bgrid* bg, int ngrids, hipStream_t st);
+                             const double* bcm, const void* twA, const sg_bgrid* bg, int ngrids, hipStream_t st);

@@ -1,23 +1,23 @@
 // Device kernels of the thin-disk self-gravity library (gfx950).
 //
 // Per-step path for one M x N grid (sigma row-major [N][M], x fastest):
-//   pass A (rows):    [k >= 3: x-solve, Eq. (C_system)] + real FFT of the row
-//                     zero-padded to 2M, written as M packed complex bins
-//                     (bin 0 carries the real bins 0 and M);
-//   pass B (columns): [k >= 3: y-solve, Eq. (z_system), on the row spectra] +
-//                     FFT of the column zero-padded to 2N, products with the
+//   pass A (rows):    real FFT of the row zero-padded to 2M, written as M packed
+//                     complex bins (bin 0 carries the real bins 0 and M);
+//   pass B (columns): FFT of the column zero-padded to 2N, products with the
 //                     spectra of w^x and w^y (convolution theorem), two
 //                     inverse FFTs cropped to N outputs, written as the
 //                     combined spectrum V = Yx + i Yy of length 2M per row;
 //   pass C (rows):    inverse FFT of V, cropped to M outputs:
 //                     Fx = Re, Fy = Im.
-// The y-solve commutes with the x-transform (tensor-product operators), so
-// it runs inside pass B at no extra HBM traffic.
+// The interpolation systems of k >= 3 (Eqs. (z_system), (C_system)) are part of
+// the stored spectra, up to a few values that passes A and B put into the
+// padding of each row and column (bnd.hpp).
 //
 // Plan time: weights of Eq. (eqnwB) on the padded 2M x 2N lattice (FP64),
 // then the same row/column transforms in FP64 to get their spectra.
 #include <type_traits>
 
+#include "bnd.hpp"
 #include "fft.hpp"
 #include "kcommon.hpp"
 #include "sg_internal.h"
@@ -378,10 +378,7 @@ struct rowfwd_cfg {
   static constexpr int E = elems_for(L, E0, SG_E3);
   static constexpr int T = L / E;
   static constexpr int LL = lds_len<L>::value;
-  // per-row LDS slot (complex elements): FFT exchange buffer, also used
-  // for the reduced system of the x-solve
-  static constexpr int TRI = band_smem<double, T>::BYTES / (int)sizeof(cx<R>) + 1;
-  static constexpr int SLOT = LL > TRI ? LL : TRI;
+  static constexpr int SLOT = LL;  // per-row LDS slot (complex elements)
   static constexpr int NB = (sizeof(R) == 4 && sizeof(In) == 4) ? SG_RF_NBUF32 : 1;  // exchange buffers per row
   // rows per workgroup: more rows make longer segments of the transposed store
   static constexpr int WG = sizeof(R) == 4 ? SG_RF_THREADS32 : SG_RF_THREADS64;
@@ -392,15 +389,14 @@ struct rowfwd_cfg {
   static constexpr int EC = (SLOT / (2 * T)) < 1 ? 1 : ((SLOT / (2 * T)) > E ? E : SLOT / (2 * T));
 };
 
-// HI: the x-solve of k = 4, 5 (solve = 4, 5); otherwise that of k = 3 (solve
-// = 3) or none (solve = 0).  Separate instantiations keep the registers of
-// the k <= 3 kernels those of their own solve.
-template <typename R, typename In, int M, bool HI = false>
+// solve: the order (3, 4, 5) whose interpolation system the spectra hold, with
+// the row's coefficient table bc (bnd.hpp), or 0.
+template <typename R, typename In, int M>
 __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M>::T))
     SG_WPE(R, RF)
     k_row_fwd(const In* __restrict__ src, int64_t src_ld, cx<R>* __restrict__ X, int ldx, int nrows,
-              const cx<R>* __restrict__ r2m, int solve, int full, const cx<R>* __restrict__ tw,
-              const sg_bgrid* __restrict__ bg) {
+              const cx<R>* __restrict__ r2m, int solve, const double* __restrict__ bc, int full,
+              const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
   if (bg) {  // batched: grid blockIdx.y of the class
     const sg_bgrid d = grid_desc(bg);
     src += d.off;
@@ -421,37 +417,14 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   // afterwards), so that they issue together rather than one at a time
   // behind a branch each
   const In* s = src + (int64_t)(active ? row : 0) * src_ld;
-  const double msk = active ? (HI ? band_scale(solve) : band_scale(3)) : 0.0;
+  const R m1 = active ? (R)1 : (R)0;
   cx<R> ze[E], zo[E];
-  if (solve) {
-    // chunk of 2E reals per thread: x-solve of Eq. (C_system) (order
-    // solve = 3, 4 or 5), FP64
-    constexpr int CH = 2 * E;
-    double d[CH];
 #pragma unroll
-    for (int e = 0; e < CH; ++e) d[e] = msk * (double)s[t * CH + e];
-    if constexpr (!HI)
-      band_solve<3, CH, T>(d, t, lds);
-    else if (solve == 4)
-      band_solve<4, CH, T>(d, t, lds);
-    else
-      band_solve<5, CH, T>(d, t, lds);
-#pragma unroll
-    for (int e = 0; e < E; ++e) lds[pad(t * E + e)] = cx<R>{(R)d[2 * e], (R)d[2 * e + 1]};
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) ze[e] = lds[pad(t + e * T)];
-    __syncthreads();
-  } else {
-    const R m1 = active ? (R)1 : (R)0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int n = t + e * T;
-      ze[e] = cx<R>{m1 * (R)s[2 * n], m1 * (R)s[2 * n + 1]};
-    }
+  for (int e = 0; e < E; ++e) {
+    const int n = t + e * T;
+    ze[e] = cx<R>{m1 * (R)s[2 * n], m1 * (R)s[2 * n + 1]};
   }
   if (full) {  // rows of 2M values (plan time): fold the upper half in
-    const R m1 = active ? (R)1 : (R)0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int n = t + e * T;
@@ -462,6 +435,28 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   } else {
 #pragma unroll
     for (int e = 0; e < E; ++e) zo[e] = cmul(ze[e], root_at(r2m, r2m[2 * t], 2 * t, 2 * e * T));  // w_M^n
+    if (solve) {
+      // the values past the row's ends: x[M], x[M + 1] (folded onto element 0)
+      // and x[2M - 2], x[2M - 1] (onto element L - 1)
+      constexpr int GB = T < 64 ? T : 64;
+      double v[2][1];
+      if (t / GB == 0) {
+        bnd_sums<M, GB, 1>([&](int i, double(&x)[1]) { x[0] = (double)s[M - 1 - i]; }, solve, bc, t % GB, v);
+        if (t == 0) {
+          const cx<R> hi{m1 * (R)v[0][0], m1 * (R)v[1][0]};
+          ze[0] = ze[0] + hi;
+          zo[0] = zo[0] - hi;  // w_M^0 = 1
+        }
+      }
+      if (t / GB == (T - 1) / GB) {
+        bnd_sums<M, GB, 1>([&](int i, double(&x)[1]) { x[0] = (double)s[i]; }, solve, bc, t % GB, v);
+        if (t == T - 1) {
+          const cx<R> hi{m1 * (R)v[1][0], m1 * (R)v[0][0]};
+          ze[E - 1] = ze[E - 1] + hi;
+          zo[E - 1] = zo[E - 1] - cmul(hi, r2m[2 * (L - 1)]);
+        }
+      }
+    }
   }
   cx<R> xe[E];
   if constexpr (NB == 2) {
@@ -554,8 +549,7 @@ struct col_cfg {
   static constexpr int E = elems_for(N, E0, SG_E3);
   static constexpr int T = N / E;
   static constexpr int LL = lds_len<N>::value;
-  static constexpr int TRI = band_smem<double2, T>::BYTES / (int)sizeof(cx<R>) + 1;
-  static constexpr int SLOT = LL > TRI ? LL : TRI;  // per-column LDS slot (complex elements)
+  static constexpr int SLOT = LL;  // per-column LDS slot (complex elements)
   // exchange buffers per column: 2 or 4 let as many transforms share their
   // barriers
   static constexpr int NBUF = sizeof(R) == 4 ? (V == 1 ? 2 : SG_COL_NBUF32) : 1;
@@ -678,16 +672,13 @@ __device__ __forceinline__ void col_product(const cx<R>* f, cx<R>* g, int half, 
   __syncthreads();
 }
 
-// MODE: 0 = k 1 (no solve), 1 = k 2 (phased tables), 2 = k 3 (y-solve), 3 =
-// k 4 (phased tables, y-solve), 4 = k 5 (pentadiagonal y-solve)
-template <typename R, typename TO, int N, int MODE, int VA = 0>
+// kind: 0 odd k, 1 even k (phased tables).  solve, bc: as in k_row_fwd, for
+// the columns.
+template <typename R, typename TO, int N, int kind, int VA = 0>
 __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
     SG_WPE(R, COL) k_col(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
-          const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ tw,
-          const sg_bgrid* __restrict__ bg) {
-  constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
-  constexpr bool solve = MODE >= 2;
-  constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);  // order of the y-solve
+          const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, int solve, const double* __restrict__ bc,
+          const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
   if (bg) {  // batched: grid blockIdx.y of the class
     const sg_bgrid d = grid_desc(bg);
     X = reinterpret_cast<const cx<R>*>(d.X);
@@ -708,14 +699,13 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
   cx<R>* lds2 = lds + (NBUF - 1) * LL;
   const cx<R>* col = X + (int64_t)c * N;  // column c, contiguous (column-major X)
   const bool exch = (c0 == 0);            // this workgroup holds the packed column 0
-  // the column: chunk of E per thread for the solve, else strided
   cx<R> a[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) a[e] = col[(unsigned)(solve ? t * E + e : t + e * T)];
+  for (int e = 0; e < E; ++e) a[e] = col[(unsigned)(t + e * T)];
   // With four exchange buffers: every table entry of the four products is
   // loaded here, after the column (loads complete in order), so that their
-  // latency overlaps the solve and the forward transforms (in order x even,
-  // y even, x odd, y odd).
+  // latency overlaps the forward transforms (in order x even, y even, x odd, y
+  // odd).
   constexpr bool pre = NBUF == 4;
   TO tv[pre ? 4 : 1][pre ? E : 1];
   if constexpr (pre) {
@@ -728,8 +718,7 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
 #pragma unroll
       for (int e = 0; e < E; ++e) tv[i][e] = odd_entry<TO, N>((i & 1) ? ry : rx, t + e * T, i >> 1);
   }
-  // phases exp(-i pi j / N) of the odd-bin transforms (used twice), loaded
-  // now so that their latency hides behind the solve
+  // phases exp(-i pi j / N) of the odd-bin transforms (used twice)
   cx<R> w2n[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) w2n[e] = r2n[(unsigned)(t + e * T)];
@@ -742,33 +731,6 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
   // with four buffers the forward transforms alternate between buffers
   // {0, 1} and {2, 3} (one barrier per exchange)
   constexpr bool pp = (NBUF == 4) && SG_COL_PP;
-  if (solve) {
-    // y-solve of Eq. (z_system) on the complex row spectra, FP64, chunk of E per thread
-    double2 d[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) d[e] = make_double2(band_scale(SYS) * (double)a[e].x, band_scale(SYS) * (double)a[e].y);
-    if constexpr (pp) {
-      // the solve's LDS lies in buffer 0; the transpose goes through buffer
-      // 2, and the forward transform's first exchange (buffers 0 and 1)
-      // follows the transpose's barrier, so neither needs a barrier after it
-      band_solve<SYS, E, T, double2, false>(d, t, lds);
-      cx<R>* tb = lds + 2 * LL;
-#pragma unroll
-      for (int e = 0; e < E; ++e) tb[pad(t * E + e)] = cx<R>{(R)d[e].x, (R)d[e].y};
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < E; ++e) a[e] = tb[pad(t + e * T)];
-    } else {
-      band_solve<SYS, E, T, double2>(d, t, lds);
-#pragma unroll
-      for (int e = 0; e < E; ++e) lds[pad(t * E + e)] = cx<R>{(R)d[e].x, (R)d[e].y};
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < E; ++e) a[e] = lds[pad(t + e * T)];
-      __syncthreads();
-    }
-  }
-
   const bool packed = (c == 0);
   // forward transform of the column zero-padded to 2N: even bins
   // fe = FFT_N(a), odd bins fo = FFT_N(a_j w_2N^j)
@@ -777,6 +739,26 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
   for (int e = 0; e < E; ++e) {
     fo[e] = cmul(a[e], w2n[e]);
     fe[e] = a[e];
+  }
+  if (solve) {
+    // the values past the column's ends, folded onto elements 0, 1 (slots N, N
+    // + 1) and N - 1, N - 2 (slots -1, -2)
+    cx<R> end[2], start[2];
+    bnd_line<N, T>(col, solve, bc, t, end, start);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      // element i of thread i (or of thread 0 when it holds both)
+      constexpr int T1 = T;
+      const int e0 = i / T1, e1 = E - 1 - i / T1;
+      if (t == i % T1) {
+        fe[e0] = fe[e0] + end[i];
+        fo[e0] = fo[e0] - cmul(end[i], w2n[e0]);
+      }
+      if (t == T1 - 1 - i % T1) {
+        fe[e1] = fe[e1] + start[i];
+        fo[e1] = fo[e1] - cmul(start[i], w2n[e1]);
+      }
+    }
   }
   cx<R> accx[E], accy[E];
   if constexpr (NBUF == 4) {
@@ -1019,10 +1001,11 @@ __global__ void __launch_bounds__((rowinv_cfg<R, M, VA>::G * rowinv_cfg<R, M, VA
 // -------------------------------------------------------------- adjoint --
 // Transposed convolution: gC = crop(IFFT(FFT(pad gx) conj Wx + FFT(pad gy)
 // conj Wy)) with the forward pass's spectra and scaling, then the
-// transposed coefficient solve (the same symmetric systems).  Row
+// transposed coefficient solve (symmetric, so again part of the spectra, with
+// the padding values' share added at the line's ends, bnd.hpp).  Row
 // transforms of gx, gy reuse k_row_fwd; the column pass below multiplies by
 // the conjugate spectra, sums the two components, inverts cropped to N rows,
-// applies the y-solve and writes the packed row spectra of gC in tiles of
+// adds that share and writes the packed row spectra of gC in tiles of
 // tj rows: bin p of row j at ((j/tj*2 + p%2)*(M/2) + p/2)*tj + j%tj.
 // Even k: r2n = exp(-i pi q'/N), php and rho as in col_product.
 template <typename R, typename TO, int N, int E, int T>
@@ -1092,14 +1075,11 @@ __device__ __forceinline__ void col_products_adj(const cx<R>* fx, const cx<R>* f
   }
 }
 
-template <typename R, typename TO, int N, int MODE>
+template <typename R, typename TO, int N, int kind>
 __global__ void __launch_bounds__((col_cfg<R, N>::P * col_cfg<R, N>::T))
     k_col_adj(const cx<R>* __restrict__ Xx, const cx<R>* __restrict__ Xy, cx<R>* __restrict__ Y, int M, int tj,
-              const TO* __restrict__ tox, const TO* __restrict__ toy, const cx<R>* __restrict__ r2n,
-              const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
-  constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
-  constexpr bool solve = MODE >= 2;
-  constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);  // order of the y-solve
+              const TO* __restrict__ tox, const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, int solve,
+              const double* __restrict__ bc, const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
   if (bg) {  // batched: gx spectra in X, gy spectra in the first half of V, output in its second half
     const sg_bgrid d = grid_desc(bg);
     Xx = reinterpret_cast<const cx<R>*>(d.X);
@@ -1127,7 +1107,7 @@ __global__ void __launch_bounds__((col_cfg<R, N>::P * col_cfg<R, N>::T))
     ax[e] = Xx[(int64_t)c * N + t + e * T];
     ay[e] = Xy[(int64_t)c * N + t + e * T];
   }
-  cx<R> acc[E];
+  cx<R> acc[E], out0[2], out1[2];  // out0, out1: the outputs of slots N, N + 1 and -1, -2 (below)
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     cx<R> fx[E], fy[E];
@@ -1143,26 +1123,37 @@ __global__ void __launch_bounds__((col_cfg<R, N>::P * col_cfg<R, N>::T))
     col_products_adj<R, TO, N, E, T>(fx, fy, h, half, c0 == 0, packed, lds, kind, tox, toy, c, M, t, r2n, php, rho);
     fft<true, N, T>(h, lds, tw, t);
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = half ? acc[e] + cmulc(h[e], r2n[(unsigned)(t + e * T)]) : h[e];
+    for (int e = 0; e < E; ++e) {
+      if (half == 0) {
+        acc[e] = h[e];
+        continue;
+      }
+      const cx<R> o = cmulc(h[e], r2n[(unsigned)(t + e * T)]);
+      // slot N + j is the difference where element j is the sum
+      if (e * T < 2) out0[e * T < 2 ? e * T : 0] = acc[e] - o;
+      if ((E - 1 - e) * T < 2) out1[(E - 1 - e) * T < 2 ? (E - 1 - e) * T : 0] = acc[e] - o;
+      acc[e] = acc[e] + o;
+    }
   }
   if (solve) {
-    // transposed y-solve (Eq. (z_system) is symmetric): chunk of E per thread
-#pragma unroll
-    for (int e = 0; e < E; ++e) lds[pad(t + e * T)] = acc[e];
+    // the gradients found in slots N, N + 1 and -1, -2, from the threads that
+    // hold elements 0, 1 and N - 1, N - 2, to every thread of the column
     __syncthreads();
-    double2 d[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const cx<R> v = lds[pad(t * E + e)];
-      d[e] = make_double2(band_scale(SYS) * (double)v.x, band_scale(SYS) * (double)v.y);
+    if (t < 2) lds[t] = out0[0];
+    if (t >= T - 2) lds[2 + T - 1 - t] = out1[0];
+    if (T == 1) {
+      lds[1] = out0[1];
+      lds[3] = out1[1];
     }
     __syncthreads();
-    band_solve<SYS, E, T, double2>(d, t, lds);
+    const cx<R> e0 = lds[0], e1 = lds[1], s0 = lds[2], s1 = lds[3];
+    const int len = bnd_reach(solve) < N ? bnd_reach(solve) : N;
 #pragma unroll
-    for (int e = 0; e < E; ++e) lds[pad(t * E + e)] = cx<R>{(R)d[e].x, (R)d[e].y};
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = lds[pad(t + e * T)];
+    for (int e = 0; e < E; ++e) {
+      const int j = t + e * T;
+      if (j < len) acc[e] = bnd_add(acc[e], s0, s1, bc, j);
+      if (N - 1 - j < len) acc[e] = bnd_add(acc[e], e0, e1, bc, N - 1 - j);
+    }
   }
   cx<R>* out = Y + (int64_t)(c & 1) * (M / 2) * tj + (int64_t)(c >> 1) * tj;
   const int64_t jstride = (int64_t)M * tj;
@@ -1176,20 +1167,12 @@ __global__ void __launch_bounds__((col_cfg<R, N>::P * col_cfg<R, N>::T))
 // Rows of the packed gC spectra -> real row of length 2M cropped to M via
 // the half-length complex inverse FFT (z = x_even + i x_odd, its first M/2
 // outputs from the even and odd input bins: two inverse FFTs of length M/2),
-// then the transposed x-solve (Eq. (C_system) is symmetric).
-// Rows per workgroup: those of the forward row pass, but at most 512
-// threads for the banded x-solve of k = 4, 5 (HI), whose registers would
-// not fit 1024 threads without spilling.
-template <typename R, int M, bool HI>
-struct rowc2r_cfg {
-  using F = rowfwd_cfg<R, R, M>;
-  static constexpr int G = (HI && F::G * F::T > 512) ? (512 / F::T > 0 ? 512 / F::T : 1) : F::G;
-};
-
-template <typename R, typename Out, int M, bool HI = false>  // HI: as in k_row_fwd
-__global__ void __launch_bounds__((rowc2r_cfg<R, M, HI>::G * rowfwd_cfg<R, R, M>::T))
+// with the padding values' share of k >= 3 added at the row's ends (bnd.hpp).
+template <typename R, typename Out, int M>
+__global__ void __launch_bounds__((rowfwd_cfg<R, R, M>::G * rowfwd_cfg<R, R, M>::T))
     k_row_c2r(const cx<R>* __restrict__ Y, Out* __restrict__ out, int nrows, int tj, const cx<R>* __restrict__ r2m,
-              int solve, const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
+              int solve, const double* __restrict__ bc, const cx<R>* __restrict__ tw,
+              const sg_bgrid* __restrict__ bg) {
   if (bg) {  // batched: packed spectra in the second half of V
     const sg_bgrid d = grid_desc(bg);
     Y = reinterpret_cast<const cx<R>*>(d.V) + (int64_t)M * nrows;
@@ -1197,7 +1180,7 @@ __global__ void __launch_bounds__((rowc2r_cfg<R, M, HI>::G * rowfwd_cfg<R, R, M>
   }
   using C = rowfwd_cfg<R, R, M>;
   constexpr int L = C::L, E = C::E, T = C::T, SLOT = C::SLOT;
-  __shared__ cx<R> smem[rowc2r_cfg<R, M, HI>::G * SLOT];
+  __shared__ cx<R> smem[C::G * SLOT];
   const int G = blockDim.x / T;
   const int g = threadIdx.x / T, t = threadIdx.x % T;
   const int row = xcd_tile(blockIdx.x, gridDim.x) * G + g;
@@ -1228,36 +1211,36 @@ __global__ void __launch_bounds__((rowc2r_cfg<R, M, HI>::G * rowfwd_cfg<R, R, M>
   }
   fft<true, L, T>(ze, lds, tw, t);
   fft<true, L, T>(zo, lds, tw, t);
-  // z[n'] = ze + exp(2 pi i n'/M) zo, n' < M/2: x[2n'] = Re z, x[2n'+1] = Im z
+  // z[n'] = ze + exp(2 pi i n'/M) zo, n' < M/2: x[2n'] = Re z, x[2n'+1] = Im
+  // z; z[n' + M/2] is the difference
+  cx<R> past{(R)0, (R)0}, before{(R)0, (R)0};  // x[M], x[M + 1] (thread 0); x[2M - 2], x[2M - 1] (thread T - 1)
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const int n = t + e * T;
-    ze[e] = ze[e] + cmulc(zo[e], root_at(r2m, r2m[2 * t], 2 * t, 2 * e * T));
+    const cx<R> o = cmulc(zo[e], root_at(r2m, r2m[2 * t], 2 * t, 2 * e * T));
+    if (e == 0) past = ze[e] - o;
+    if (e == E - 1) before = ze[e] - o;
+    ze[e] = ze[e] + o;
   }
   if (solve) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) lds[pad(t + e * T)] = ze[e];
+    // the gradients found in the padding slots, to every thread of the row
     __syncthreads();
-    constexpr int CH = 2 * E;
-    double d[CH];
+    if (t == 0) lds[0] = past;
+    if (t == T - 1) lds[1] = before;
+    __syncthreads();
+    const cx<R> pe = lds[0], ps = lds[1];
+    const int len = bnd_reach(solve) < M ? bnd_reach(solve) : M;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const cx<R> v = lds[pad(t * E + e)];
-      d[2 * e] = (HI ? band_scale(solve) : band_scale(3)) * (double)v.x;
-      d[2 * e + 1] = (HI ? band_scale(solve) : band_scale(3)) * (double)v.y;
-    }
-    __syncthreads();
-    if constexpr (!HI)
-      band_solve<3, CH, T>(d, t, lds);
-    else if (solve == 4)
-      band_solve<4, CH, T>(d, t, lds);
-    else
-      band_solve<5, CH, T>(d, t, lds);
-    if (active) {
+      const int n = 2 * (t + e * T);
+      R* x[2] = {&ze[e].x, &ze[e].y};
 #pragma unroll
-      for (int e = 0; e < CH; ++e) out[(int64_t)row * M + t * CH + e] = (Out)d[e];
+      for (int i = 0; i < 2; ++i) {
+        if (n + i < len) *x[i] = bnd_add(*x[i], ps.y, ps.x, bc, n + i);
+        if (M - 1 - n - i < len) *x[i] = bnd_add(*x[i], pe.x, pe.y, bc, M - 1 - n - i);
+      }
     }
-  } else if (active) {
+  }
+  if (active) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int n = t + e * T;
@@ -1273,7 +1256,8 @@ __global__ void __launch_bounds__((rowc2r_cfg<R, M, HI>::G * rowfwd_cfg<R, R, M>
 // table, then the stored form of W^d(p, q) / (4MN):
 //   odd k : A = Im W (W is purely imaginary), q in [0, N], split by parity;
 //   even k: A = Im(W conj(ph)), ph = exp(-i pi (p / 2M + q / 2N)) the
-//           half-cell phase, on the same quarter.
+//           half-cell phase, on the same quarter;
+//   solve (k >= 3): times the inverse symbols of the interpolation systems.
 // Output element type: double (FP64 plans) or a hi+lo float pair.
 template <int N>
 struct spec_cfg {
@@ -1296,7 +1280,7 @@ __device__ __forceinline__ void put_odd(void* tab, int fp32, int64_t idx, double
 
 template <int N>
 __global__ void __launch_bounds__((spec_cfg<N>::T))
-    k_spec_col(const cx<double>* __restrict__ S, int M, void* __restrict__ tab, int kind, int fp32,
+    k_spec_col(const cx<double>* __restrict__ S, int M, void* __restrict__ tab, int kind, int fp32, int solve,
                double scale, const cx<double>* __restrict__ r2n, const cx<double>* __restrict__ tw) {
   using C = spec_cfg<N>;
   constexpr int E = C::E, T = C::T, LL = C::LL;
@@ -1346,6 +1330,7 @@ __global__ void __launch_bounds__((spec_cfg<N>::T))
           sincospi((double)rows[h] / (2.0 * M) + (double)(2 * qq + half) / (2.0 * N), &sn, &cs);
           a = w.y * cs + w.x * sn;
         }
+        if (solve) a *= bnd_symbol(solve, rows[h], M) * bnd_symbol(solve, 2 * qq + half, N);
         if (half == 0 && qq <= N / 2) put_odd(tab, fp32, (int64_t)rows[h] * (N + 1) + qq, a);
         if (half == 1 && qq < N / 2) put_odd(tab, fp32, (int64_t)rows[h] * (N + 1) + N / 2 + 1 + qq, a);
       }
@@ -1489,27 +1474,21 @@ static inline int pick_tile(int tile, int cap, int n) {
 
 template <typename R, typename In, int M>
 static hipError_t launch_row_fwd_t(const In* src, int64_t src_ld, cx<R>* X, int nrows, const cx<R>* r2m,
-                                   int solve, int full, const cx<R>* tw, const sg_bgrid* bg, int ngrids, int tile,
+                                   int solve, const double* bc, int full, const cx<R>* tw, const sg_bgrid* bg, int ngrids, int tile,
                                    hipStream_t st) {
   using C = rowfwd_cfg<R, In, M>;
   const int G = pick_tile(tile, C::G, nrows);
   const int blocks = (nrows + G - 1) / G;
   constexpr int row_bytes = C::SLOT * C::NB * (int)sizeof(cx<R>);
-  if (solve >= 4) {
-    dyn_lds_optin<&k_row_fwd<R, In, M, true>>(C::G * row_bytes);
-    hipLaunchKernelGGL((k_row_fwd<R, In, M, true>), dim3(blocks, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes,
-                       st, src, src_ld, X, nrows, nrows, r2m, solve, full, tw, bg);
-  } else {
-    dyn_lds_optin<&k_row_fwd<R, In, M>>(C::G * row_bytes);
-    hipLaunchKernelGGL((k_row_fwd<R, In, M>), dim3(blocks, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st, src,
-                       src_ld, X, nrows, nrows, r2m, solve, full, tw, bg);
-  }
+  dyn_lds_optin<&k_row_fwd<R, In, M>>(C::G * row_bytes);
+  hipLaunchKernelGGL((k_row_fwd<R, In, M>), dim3(blocks, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st, src,
+                     src_ld, X, nrows, nrows, r2m, solve, bc, full, tw, bg);
   return hipGetLastError();
 }
 
 template <typename R, int N, int VA = 0>
 static hipError_t launch_col_t(const cx<R>* X, cx<R>* V, int M, int tj, const void* tx, const void* ty, int kind,
-                               const cx<R>* r2n, int solve, const cx<R>* tw, const sg_bgrid* bg, int ngrids,
+                               const cx<R>* r2n, int solve, const double* bc, const cx<R>* tw, const sg_bgrid* bg, int ngrids,
                                int tile, hipStream_t st) {
   using C = col_cfg<R, N, VA>;
   using TO = typename tabs<R>::odd;
@@ -1519,20 +1498,14 @@ static hipError_t launch_col_t(const cx<R>* X, cx<R>* V, int M, int tj, const vo
   const TO* toy = (const TO*)ty;
   constexpr int col_bytes = C::SLOT * C::NBUF * (int)sizeof(cx<R>);
   const int lds = P * col_bytes;
-  // modes: 0 = k 1, 1 = k 2, 2 = k 3, 3 = k 4, 4 = k 5 (solve = k for k >= 3)
-  auto go = [&](auto mode) {
-    constexpr int MD = decltype(mode)::value;
-    dyn_lds_optin<&k_col<R, TO, N, MD, VA>>(C::P * col_bytes);
-    hipLaunchKernelGGL((k_col<R, TO, N, MD, VA>), grid, dim3(P * C::T), lds, st, X, V, M, tj, tox, toy, r2n, tw, bg);
+  auto go = [&](auto kd) {
+    constexpr int KD = decltype(kd)::value;
+    dyn_lds_optin<&k_col<R, TO, N, KD, VA>>(C::P * col_bytes);
+    hipLaunchKernelGGL((k_col<R, TO, N, KD, VA>), grid, dim3(P * C::T), lds, st, X, V, M, tj, tox, toy, r2n, solve, bc,
+                       tw, bg);
   };
-  if (solve == 4)
-    go(std::integral_constant<int, 3>{});
-  else if (solve == 5)
-    go(std::integral_constant<int, 4>{});
-  else if (kind == 1)
+  if (kind == 1)
     go(std::integral_constant<int, 1>{});
-  else if (solve)
-    go(std::integral_constant<int, 2>{});
   else
     go(std::integral_constant<int, 0>{});
   return hipGetLastError();
@@ -1550,10 +1523,10 @@ static hipError_t launch_row_inv_t(const cx<R>* V, Out* fx, Out* fy, int nrows, 
 }
 
 template <int N>
-static hipError_t launch_spec_col_t(const cx<double>* S, int M, void* tab, int kind, int fp32, double scale,
+static hipError_t launch_spec_col_t(const cx<double>* S, int M, void* tab, int kind, int fp32, int solve, double scale,
                                     const cx<double>* r2n, const cx<double>* tw, hipStream_t st) {
   using C = spec_cfg<N>;
-  hipLaunchKernelGGL((k_spec_col<N>), dim3(M), dim3(C::T), 0, st, S, M, tab, kind, fp32, scale, r2n, tw);
+  hipLaunchKernelGGL((k_spec_col<N>), dim3(M), dim3(C::T), 0, st, S, M, tab, kind, fp32, solve, scale, r2n, tw);
   return hipGetLastError();
 }
 
@@ -1583,12 +1556,12 @@ hipError_t sg_set_gl_tables(const double* x, const double* w) {
 #if SG_IN_PART(1)
 template <typename R, typename In>
 static hipError_t row_fwd_dispatch(int M, const In* src, int64_t ld, cx<R>* X, int nrows, const cx<R>* r2m,
-                                   int solve, int full, const cx<R>* tw, const sg_bgrid* bg, int ngrids, int tile,
+                                   int solve, const double* bc, int full, const cx<R>* tw, const sg_bgrid* bg, int ngrids, int tile,
                                    hipStream_t st) {
   switch (M) {
 #define CASE(SZ) \
   case SZ:       \
-    return launch_row_fwd_t<R, In, SZ>(src, ld, X, nrows, r2m, solve, full, tw, bg, ngrids, tile, st);
+    return launch_row_fwd_t<R, In, SZ>(src, ld, X, nrows, r2m, solve, bc, full, tw, bg, ngrids, tile, st);
     SG_ROW_SIZES(CASE)
 #undef CASE
     default:
@@ -1601,15 +1574,15 @@ static hipError_t row_fwd_dispatch(int M, const In* src, int64_t ld, cx<R>* X, i
 #if SG_IN_PART(2)
 template <typename R>
 static hipError_t col_dispatch(int N, const cx<R>* X, cx<R>* V, int M, int tj, const void* tx, const void* ty,
-                               int kind, const cx<R>* r2n, int solve, const cx<R>* tw, const sg_bgrid* bg,
+                               int kind, const cx<R>* r2n, int solve, const double* bc, const cx<R>* tw, const sg_bgrid* bg,
                                int ngrids, int tile, int variant, hipStream_t st) {
   switch (N) {
 #define CASE(SZ)                                                                                        \
   case SZ:                                                                                              \
     if (sizeof(R) == 4 && variant == 1 && col_variants<SZ>())                                           \
-      return launch_col_t<R, SZ, col_variants<SZ>() ? 1 : 0>(X, V, M, tj, tx, ty, kind, r2n, solve, tw, bg, \
+      return launch_col_t<R, SZ, col_variants<SZ>() ? 1 : 0>(X, V, M, tj, tx, ty, kind, r2n, solve, bc, tw, bg, \
                                                               ngrids, tile, st);                        \
-    return launch_col_t<R, SZ>(X, V, M, tj, tx, ty, kind, r2n, solve, tw, bg, ngrids, tile, st);
+    return launch_col_t<R, SZ>(X, V, M, tj, tx, ty, kind, r2n, solve, bc, tw, bg, ngrids, tile, st);
     SG_SIZES(CASE)
 #undef CASE
     default:
@@ -1642,27 +1615,27 @@ static hipError_t row_inv_dispatch(int M, const cx<R>* V, Out* fx, Out* fy, int 
 
 #if SG_IN_PART(1)
 hipError_t sg_launch_row_fwd(int prec, int M, const void* src, int64_t ld, void* X, int nrows, const void* r2m,
-                             int solve, int full, const void* tw, const sg_bgrid* bg, int ngrids, int tile,
+                             int solve, const double* bc, int full, const void* tw, const sg_bgrid* bg, int ngrids, int tile,
                              hipStream_t st) {
   if (prec == 0)
     return row_fwd_dispatch<double, double>(M, (const double*)src, ld, (cx<double>*)X, nrows,
-                                            (const cx<double>*)r2m, solve, full, (const cx<double>*)tw, bg, ngrids,
+                                            (const cx<double>*)r2m, solve, bc, full, (const cx<double>*)tw, bg, ngrids,
                                             tile, st);
   return row_fwd_dispatch<float, float>(M, (const float*)src, ld, (cx<float>*)X, nrows, (const cx<float>*)r2m,
-                                        solve, full, (const cx<float>*)tw, bg, ngrids, tile, st);
+                                        solve, bc, full, (const cx<float>*)tw, bg, ngrids, tile, st);
 }
 
 #endif
 
 #if SG_IN_PART(2)
 hipError_t sg_launch_col(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                         int kind, const void* r2n, int solve, const void* tw, const sg_bgrid* bg, int ngrids,
-                         int tile, int variant, hipStream_t st) {
+                         int kind, const void* r2n, int solve, const double* bc, const void* tw, const sg_bgrid* bg,
+                         int ngrids, int tile, int variant, hipStream_t st) {
   if (prec == 0)
     return col_dispatch<double>(N, (const cx<double>*)X, (cx<double>*)V, M, tj, tx, ty, kind,
-                                (const cx<double>*)r2n, solve, (const cx<double>*)tw, bg, ngrids, tile, 0, st);
+                                (const cx<double>*)r2n, solve, bc, (const cx<double>*)tw, bg, ngrids, tile, 0, st);
   return col_dispatch<float>(N, (const cx<float>*)X, (cx<float>*)V, M, tj, tx, ty, kind, (const cx<float>*)r2n,
-                             solve, (const cx<float>*)tw, bg, ngrids, tile, variant, st);
+                             solve, bc, (const cx<float>*)tw, bg, ngrids, tile, variant, st);
 }
 
 int sg_row_tile(int prec, int M, int N) {
@@ -1727,12 +1700,12 @@ int sg_max_tile(int prec, int pass, int len, int variant) {
 #endif
 
 #if SG_IN_PART(0)
-hipError_t sg_launch_spec_col(int N, const void* rowspec, int M, void* tab, int kind, int fp32, double scale,
+hipError_t sg_launch_spec_col(int N, const void* rowspec, int M, void* tab, int kind, int fp32, int solve, double scale,
                               const void* r2n, const void* tw, hipStream_t st) {
   switch (N) {
 #define CASE(SZ) \
   case SZ:       \
-    return launch_spec_col_t<SZ>((const cx<double>*)rowspec, M, tab, kind, fp32, scale, (const cx<double>*)r2n, \
+    return launch_spec_col_t<SZ>((const cx<double>*)rowspec, M, tab, kind, fp32, solve, scale, (const cx<double>*)r2n, \
                                 (const cx<double>*)tw, st);
     SG_SIZES(CASE)
 #undef CASE
@@ -1854,7 +1827,7 @@ int sg_twiddles(int prec, int pass, int len, const void* roots, void* out, hipSt
 // ------------------------------------------------------ adjoint launches --
 template <typename R, int N>
 static hipError_t launch_col_adj_t(const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y, int M, int tj, const void* tx,
-                                   const void* ty, int kind, const cx<R>* r2n, int solve, const cx<R>* tw,
+                                   const void* ty, int kind, const cx<R>* r2n, int solve, const double* bc, const cx<R>* tw,
                                    const sg_bgrid* bg, int ngrids, hipStream_t st) {
   using C = col_cfg<R, N>;
   using TO = typename tabs<R>::odd;
@@ -1862,52 +1835,36 @@ static hipError_t launch_col_adj_t(const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y, i
   const dim3 grid(M / P, bg ? ngrids : 1);
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
-  // modes: 0 = k 1, 1 = k 2, 2 = k 3, 3 = k 4, 4 = k 5 (solve = k for k >= 3)
-  if (solve == 4)
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 3>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy,
-                       r2n, tw, bg);
-  else if (solve == 5)
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 4>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy,
-                       r2n, tw, bg);
-  else if (kind == 1)
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 1>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy,
-                       r2n, tw, bg);
-  else if (solve)
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 2>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy,
-                       r2n, tw, bg);
+  if (kind == 1)
+    hipLaunchKernelGGL((k_col_adj<R, TO, N, 1>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
+                       bc, tw, bg);
   else
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 0>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy,
-                       r2n, tw, bg);
+    hipLaunchKernelGGL((k_col_adj<R, TO, N, 0>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
+                       bc, tw, bg);
   return hipGetLastError();
 }
 
 template <typename R, int M>
 static hipError_t launch_row_c2r_t(const cx<R>* Y, R* out, int nrows, int tj, const cx<R>* r2m, int solve,
+                                   const double* bc,
                                    const cx<R>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   using C = rowfwd_cfg<R, R, M>;
-  if (solve >= 4) {
-    constexpr int GH = rowc2r_cfg<R, M, true>::G;
-    const int G = GH < nrows ? GH : nrows;
-    hipLaunchKernelGGL((k_row_c2r<R, R, M, true>), dim3((nrows + G - 1) / G, bg ? ngrids : 1), dim3(G * C::T), 0, st,
-                       Y, out, nrows, tj, r2m, solve, tw, bg);
-  } else {
-    const int G = C::G < nrows ? C::G : nrows;
-    hipLaunchKernelGGL((k_row_c2r<R, R, M>), dim3((nrows + G - 1) / G, bg ? ngrids : 1), dim3(G * C::T), 0, st, Y,
-                       out, nrows, tj, r2m, solve, tw, bg);
-  }
+  const int G = C::G < nrows ? C::G : nrows;
+  hipLaunchKernelGGL((k_row_c2r<R, R, M>), dim3((nrows + G - 1) / G, bg ? ngrids : 1), dim3(G * C::T), 0, st, Y, out,
+                     nrows, tj, r2m, solve, bc, tw, bg);
   return hipGetLastError();
 }
 
 template <typename R>
 static hipError_t adj_dispatch(int M, int N, const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y, R* out, int tj,
                                const void* tx, const void* ty, int kind, const cx<R>* r2m, const cx<R>* r2n,
-                               int solve, const cx<R>* twB, const cx<R>* twA, const sg_bgrid* bg, int ngrids,
+                               int solve, const double* bcm, const double* bcn, const cx<R>* twB, const cx<R>* twA, const sg_bgrid* bg, int ngrids,
                                hipStream_t st) {
   hipError_t e = hipErrorInvalidValue;
   switch (N) {
 #define CASE(SZ)                                                                                  \
   case SZ:                                                                                        \
-    e = launch_col_adj_t<R, SZ>(Xx, Xy, Y, M, tj, tx, ty, kind, r2n, solve, twB, bg, ngrids, st); \
+    e = launch_col_adj_t<R, SZ>(Xx, Xy, Y, M, tj, tx, ty, kind, r2n, solve, bcn, twB, bg, ngrids, st); \
     break;
     SG_SIZES(CASE)
 #undef CASE
@@ -1918,7 +1875,7 @@ static hipError_t adj_dispatch(int M, int N, const cx<R>* Xx, const cx<R>* Xy, c
   switch (M) {
 #define CASE(SZ) \
   case SZ:       \
-    return launch_row_c2r_t<R, SZ>(Y, out, N, tj, r2m, solve, twA, bg, ngrids, st);
+    return launch_row_c2r_t<R, SZ>(Y, out, N, tj, r2m, solve, bcm, twA, bg, ngrids, st);
     SG_ROW_SIZES(CASE)
 #undef CASE
     default:
@@ -1928,11 +1885,11 @@ static hipError_t adj_dispatch(int M, int N, const cx<R>* Xx, const cx<R>* Xy, c
 
 template <typename R>
 static hipError_t c2r_dispatch(int M, int N, const cx<R>* Y, R* out, int tj, const cx<R>* r2m, int solve,
-                               const cx<R>* twA, const sg_bgrid* bg, int ngrids, hipStream_t st) {
+                               const double* bcm, const cx<R>* twA, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   switch (M) {
 #define CASE(SZ) \
   case SZ:       \
-    return launch_row_c2r_t<R, SZ>(Y, out, N, tj, r2m, solve, twA, bg, ngrids, st);
+    return launch_row_c2r_t<R, SZ>(Y, out, N, tj, r2m, solve, bcm, twA, bg, ngrids, st);
     SG_ROW_SIZES(CASE)
 #undef CASE
     default:
@@ -1941,24 +1898,24 @@ static hipError_t c2r_dispatch(int M, int N, const cx<R>* Y, R* out, int tj, con
 }
 
 hipError_t sg_launch_row_c2r(int prec, int M, int N, const void* Y, void* gsigma, int tj, const void* r2m, int solve,
-                             const void* twA, const sg_bgrid* bg, int ngrids, hipStream_t st) {
+                             const double* bcm, const void* twA, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   if (prec == 0)
     return c2r_dispatch<double>(M, N, (const cx<double>*)Y, (double*)gsigma, tj, (const cx<double>*)r2m, solve,
-                                (const cx<double>*)twA, bg, ngrids, st);
+                                bcm, (const cx<double>*)twA, bg, ngrids, st);
   return c2r_dispatch<float>(M, N, (const cx<float>*)Y, (float*)gsigma, tj, (const cx<float>*)r2m, solve,
-                             (const cx<float>*)twA, bg, ngrids, st);
+                             bcm, (const cx<float>*)twA, bg, ngrids, st);
 }
 
 hipError_t sg_launch_adjoint_tail(int prec, int M, int N, const void* Xx, const void* Xy, void* Y, void* gsigma,
                                   int tj, const void* tx, const void* ty, int kind, const void* r2m, const void* r2n,
-                                  int solve, const void* twB, const void* twA, const sg_bgrid* bg, int ngrids,
+                                  int solve, const double* bcm, const double* bcn, const void* twB, const void* twA, const sg_bgrid* bg, int ngrids,
                                   hipStream_t st) {
   if (prec == 0)
     return adj_dispatch<double>(M, N, (const cx<double>*)Xx, (const cx<double>*)Xy, (cx<double>*)Y, (double*)gsigma,
-                                tj, tx, ty, kind, (const cx<double>*)r2m, (const cx<double>*)r2n, solve,
+                                tj, tx, ty, kind, (const cx<double>*)r2m, (const cx<double>*)r2n, solve, bcm, bcn,
                                 (const cx<double>*)twB, (const cx<double>*)twA, bg, ngrids, st);
   return adj_dispatch<float>(M, N, (const cx<float>*)Xx, (const cx<float>*)Xy, (cx<float>*)Y, (float*)gsigma, tj, tx,
-                             ty, kind, (const cx<float>*)r2m, (const cx<float>*)r2n, solve, (const cx<float>*)twB,
+                             ty, kind, (const cx<float>*)r2m, (const cx<float>*)r2n, solve, bcm, bcn, (const cx<float>*)twB,
                              (const cx<float>*)twA, bg, ngrids, st);
 }
 #endif
