@@ -124,4 +124,26 @@ __device__ __forceinline__ void bnd_line(const cx<R>* __restrict__ col, int orde
   if (t / G == (T - 1) / G) sums(false, start);
 }
 
+// The value that thread t of a column c's T threads folds in: that of slot N + t
+// for t < 2, of slot t - T for the last two, from the parts that pass A left (xb,
+// pg parts per value); zero elsewhere.
+template <int T, typename R>
+__device__ __forceinline__ cx<R> bnd_value(const cx<R>* __restrict__ xb, int pg, int c, int t) {
+  if (!xb || (t >= 2 && t < T - 2)) return cx<R>{(R)0, (R)0};
+  const cx<R>* p = xb + (int64_t)(4 * c + (t < 2 ? t : 2 + T - 1 - t)) * pg;
+  double x = 0.0, y = 0.0;
+  for (int w0 = 0; w0 < pg; w0 += 8) {
+    // eight loads together, those past pg masked
+    cx<R> z[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = p[w0 + i < pg ? w0 + i : pg - 1];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      x += w0 + i < pg ? (double)z[i].x : 0.0;
+      y += w0 + i < pg ? (double)z[i].y : 0.0;
+    }
+  }
+  return cx<R>{(R)x, (R)y};
+}
+
 }  // namespace sg

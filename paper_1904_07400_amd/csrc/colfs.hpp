@@ -3,9 +3,9 @@
 //
 // Per column p (a bin of the row transforms; column 0 carries the real bins
 // p = 0 and p = M packed as U = C_0 + i C_M):
-//   [k >= 3: the values past the column's ends that stand for the interpolation
-//    system (bnd.hpp; bord, bc), or, MODE >= 2, the system solved on the
-//    column, FP64, for tables that do not hold its symbol],
+//   [k >= 3: the column's padding values, which stand for the interpolation
+//    system (bnd.hpp; xb), or, MODE >= 2, the system solved on the column,
+//    FP64, for tables that do not hold its symbol],
 //   forward transform of the column zero-padded to 2N as its even and odd
 //   output bins: fe = FFT_N(a), fo = FFT_N(a_j w_2N^j),
 //   products with the spectra of w^x and w^y (convolution theorem, Eq. (eqnF)),
@@ -139,8 +139,8 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS, int COMP, 
 __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj,
                                            const TO* __restrict__ tox, const TO* __restrict__ toy,
                                            const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-                                           const sg_bgrid* __restrict__ bg, cx<R>* smem, int bord,
-                                           const double* __restrict__ bc) {
+                                           const sg_bgrid* __restrict__ bg, cx<R>* smem,
+                                           const cx<R>* __restrict__ xb, int pg) {
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
   constexpr bool solve = MODE >= 2;
   constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);
@@ -156,6 +156,7 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
     V = reinterpret_cast<cx<R>*>(d.V);
     tox = reinterpret_cast<const TO*>(d.tabx);
     toy = reinterpret_cast<const TO*>(d.taby);
+    xb = reinterpret_cast<const cx<R>*>(d.xb);
   }
   // exchange areas: A0 (slots 0, 1) and A1 (slots 2, 3, or A0 again)
   cx<R>* A0 = smem;
@@ -214,9 +215,8 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
   const TO* rowx = tox + (int64_t)c * (N + 1);
   const TO* rowy = toy + (int64_t)c * (N + 1);
   const int itn = it + (int)gridDim.x;
-  // bord (the order, with bc: bnd.hpp): the values past the column's ends
-  cx<R> end[2], start[2];
-  if (!solve && bord) bnd_line<N, T>(X + (int64_t)c * N, bord, bc, t, end, start);
+  // the column's padding values (bnd.hpp), in the threads that fold them in
+  const cx<R> xv = solve ? cx<R>{(R)0, (R)0} : bnd_value<T>(xb, pg, c, t);
   // this column's table entries first, then (PF) the next column: loads
   // complete in order, so waiting for the entries leaves the prefetch in
   // flight
@@ -258,18 +258,15 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
     f[0][e] = a[e];
     f[1][e] = cmul(a[e], w2n_at(t, e));
   }
-  if (!solve && bord) {
-    // folded onto elements 0, 1 (threads 0, 1) and N - 1, N - 2 (the last two)
+  if (!solve && xb) {
+    // onto elements 0, 1 (threads 0, 1) and N - 1, N - 2 (the last two)
     const cx<R> w0 = w2n_at(t, 0), w1 = w2n_at(t, E - 1);
     if (t < 2) {
-      const cx<R> z = t ? end[1] : end[0];
-      f[0][0] = f[0][0] + z;
-      f[1][0] = f[1][0] - cmul(z, w0);
-    }
-    if (t >= T - 2) {
-      const cx<R> z = t == T - 1 ? start[0] : start[1];
-      f[0][E - 1] = f[0][E - 1] + z;
-      f[1][E - 1] = f[1][E - 1] - cmul(z, w1);
+      f[0][0] = f[0][0] + xv;
+      f[1][0] = f[1][0] - cmul(xv, w0);
+    } else {  // zero but in the last two
+      f[0][E - 1] = f[0][E - 1] + xv;
+      f[1][E - 1] = f[1][E - 1] - cmul(xv, w1);
     }
   }
   if constexpr (SLOTS == 1) {
@@ -479,9 +476,9 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS, int COMP, 
 __global__ void __launch_bounds__(N / E) SG_WAVES_PER_EU(colfs_wpe<R, N>::value)
     k_colfs(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
             const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-            const sg_bgrid* __restrict__ bg, int bord = 0, const double* __restrict__ bc = nullptr) {
+            const sg_bgrid* __restrict__ bg, const cx<R>* __restrict__ xb = nullptr, int pg = 0) {
   __shared__ cx<R> smem[colfs_cfg<R, N, E, SLOTS>::LDS];
-  colfs_body<R, TO, N, MODE, E, SLOTS, COMP, PF>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, bord, bc);
+  colfs_body<R, TO, N, MODE, E, SLOTS, COMP, PF>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg);
 }
 
 // Both force components of a column in one launch: the x pass (Yx into
@@ -492,11 +489,11 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS>
 __global__ void __launch_bounds__(N / E) SG_WAVES_PER_EU(colfs_wpe<R, N>::value)
     k_colfs_xy(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
                const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-               const sg_bgrid* __restrict__ bg, int bord = 0, const double* __restrict__ bc = nullptr) {
+               const sg_bgrid* __restrict__ bg, const cx<R>* __restrict__ xb = nullptr, int pg = 0) {
   __shared__ cx<R> smem[colfs_cfg<R, N, E, SLOTS>::LDS];
-  colfs_body<R, TO, N, MODE, E, SLOTS, 1, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, bord, bc);
+  colfs_body<R, TO, N, MODE, E, SLOTS, 1, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg);
   __syncthreads();
-  colfs_body<R, TO, N, MODE, E, SLOTS, 2, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, bord, bc);
+  colfs_body<R, TO, N, MODE, E, SLOTS, 2, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg);
 }
 
 // Plan-time spectrum columns of the long columns (FP64): column c of the

@@ -210,7 +210,7 @@ template <typename R, typename TO, int MODE, int L = 512>
 __global__ void __launch_bounds__(kC3T) SG_WAVES_PER_EU(SG_COLFS3_WPE)
     k_colfs3(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
              const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-             const sg_bgrid* __restrict__ bg, int bord = 0, const double* __restrict__ bc = nullptr) {
+             const sg_bgrid* __restrict__ bg, const cx<R>* __restrict__ xb = nullptr, int pg = 0) {
   using S3 = c3_shape<L>;
   constexpr int N = S3::N, E = S3::E, T = S3::T, SL = S3::SL;
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
@@ -225,6 +225,7 @@ __global__ void __launch_bounds__(kC3T) SG_WAVES_PER_EU(SG_COLFS3_WPE)
     V = reinterpret_cast<cx<R>*>(d.V);
     tox = reinterpret_cast<const TO*>(d.tabx);
     toy = reinterpret_cast<const TO*>(d.taby);
+    xb = reinterpret_cast<const cx<R>*>(d.xb);
   }
   const int t = threadIdx.x;
   const int q = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
@@ -242,16 +243,10 @@ __global__ void __launch_bounds__(kC3T) SG_WAVES_PER_EU(SG_COLFS3_WPE)
   cx<R> a[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) a[e] = col[(unsigned)at(e)];
-  // bord (the order, with bc: bnd.hpp): the values past the column's ends,
-  // folded onto elements 0, 1 (lanes 0, 1) and N - 2, N - 1 (lanes 62, 63); each
-  // wave of the radix-3 step meets all four
-  cx<R> end{(R)0, (R)0}, start{(R)0, (R)0};
-  if (!solve && bord) {
-    cx<R> ev[2], sv[2];
-    bnd_line<N, 64>(col, bord, bc, lane, ev, sv);
-    if (lane < 2) end = ev[lane & 1];
-    if (lane >= 62) start = sv[(63 - lane) & 1];
-  }
+  // the column's padding values (bnd.hpp), folded onto elements 0, 1 (lanes 0, 1)
+  // and N - 1, N - 2 (lanes 63, 62); each wave of the radix-3 step meets all four
+  const cx<R> xv = solve ? cx<R>{(R)0, (R)0} : bnd_value<64>(xb, pg, c, lane);
+  const cx<R> end = lane < 2 ? xv : cx<R>{(R)0, (R)0}, start = lane >= 62 ? xv : cx<R>{(R)0, (R)0};
   TO tv[pre ? 4 : 1][pre ? E : 1];
   if constexpr (pre) {
 #pragma unroll

@@ -56,6 +56,7 @@ __device__ __forceinline__ sg_bgrid grid_desc(const sg_bgrid* bg) {
   d.V = k->V;
   d.tabx = k->tabx;
   d.taby = k->taby;
+  d.xb = k->xb;
   return d;
 }
 

@@ -241,6 +241,8 @@ struct GridPlan {
   void* twfs = nullptr;     // its twiddle table
   double* bcm = nullptr;    // k >= 3: coefficient tables of the padding values of rows and columns
   double* bcn = nullptr;
+  void* xb = nullptr;       // k >= 3 with a long column kernel: parts of the columns' padding values
+  int tab_row = 0;          // row length of the spectra in the column pass's order (sg_tab_row); 0: natural
   int tab_bytes = 8;        // bytes per spectrum entry: double, float hi + lo, or float
 };
 
@@ -479,12 +481,13 @@ sg_status build_spectra(sg_plan p, GridPlan& G, const void* r2m64, const void* r
   auto spec = [&](void* tab) {
     const int solve = G.k >= 3 ? G.k : 0;
     return N == 8192 ? sg_launch_specfs(N, S, M, tab, G.kind, fp32, solve, scale, r2n64, twfs64, p->st)
-                     : sg_launch_spec_col(N, S, M, tab, G.kind, fp32, solve, scale, r2n64, twS64, p->st);
+                     : sg_launch_spec_col(N, S, M, tab, G.kind, fp32, solve, G.tab_row, scale, r2n64, twS64,
+                                          p->st);
   };
   e = sg_launch_weights(G.k, G.hx, G.hy, M, N, wpx, wpy, 0, p->st);
-  if (e == hipSuccess) e = sg_launch_row_fwd(0, M, wpx, 2 * M, S, 2 * N, r2m64, 0, nullptr, 1, twA64, nullptr, 1, 0, p->st);
+  if (e == hipSuccess) e = sg_launch_row_fwd(0, M, wpx, 2 * M, S, 2 * N, r2m64, 0, nullptr, nullptr, 1, twA64, nullptr, 1, 0, p->st);
   if (e == hipSuccess) e = spec(G.tabx);
-  if (e == hipSuccess) e = sg_launch_row_fwd(0, M, wpy, 2 * M, S, 2 * N, r2m64, 0, nullptr, 1, twA64, nullptr, 1, 0, p->st);
+  if (e == hipSuccess) e = sg_launch_row_fwd(0, M, wpy, 2 * M, S, 2 * N, r2m64, 0, nullptr, nullptr, 1, twA64, nullptr, 1, 0, p->st);
   if (e == hipSuccess) e = spec(G.taby);
   if (e == hipSuccess) e = hipStreamSynchronize(p->st);
   if (e != hipSuccess) st = hip_check(p, e, "plan-time spectrum");
@@ -497,8 +500,10 @@ constexpr size_t kMaxGraphs = 4;
 constexpr int kSideStreams = 4;
 
 // The column pass of one class: the four-step kernel for long columns, the
-// Stockham kernel otherwise.
-hipError_t launch_cols(sg_plan p, const GridClass& c, int tile, hipStream_t q, const sg_bgrid* desc = nullptr) {
+// Stockham kernel otherwise.  tile_a: pass A's tile, which decides the parts of
+// the padding values that it leaves.
+hipError_t launch_cols(sg_plan p, const GridClass& c, int tile_a, int tile, hipStream_t q,
+                       const sg_bgrid* desc = nullptr) {
   const int prec = p->prec == SG_FP64 ? 0 : 1;
   const GridPlan& G = p->grids[c.members[0]];
   const int solve = c.k >= 3 ? c.k : 0;
@@ -506,8 +511,8 @@ hipError_t launch_cols(sg_plan p, const GridClass& c, int tile, hipStream_t q, c
   const int tj = sg_row_tile(prec, c.M, c.N);
   const sg_bgrid* d = desc ? desc : c.desc;
   if (G.fs)
-    return sg_launch_colfs(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.tab_bytes, G.r2n, solve, G.bcn,
-                           G.twfs, d, ng, q);
+    return sg_launch_colfs(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.tab_bytes, G.r2n,
+                           G.xb ? sg_pad_groups(prec, c.M, c.N, tile_a, c.k) : 0, G.twfs, d, ng, q);
   return sg_launch_col(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.r2n, solve, G.bcn, G.twB, d, ng,
                        tile, c.var[1], q);
 }
@@ -530,8 +535,8 @@ hipError_t issue_class(sg_plan p, const GridClass& c, const void* sigma, void* f
   const GridPlan& G = p->grids[c.members[0]];
   const int solve = c.k >= 3 ? c.k : 0;
   const int ng = (int)c.members.size();
-  hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, 0, G.twA, c.desc, ng, tile[0], q);
-  if (e == hipSuccess) e = launch_cols(p, c, tile[1], q);
+  hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, G.xb ? G.bcn : nullptr, 0, G.twA, c.desc, ng, tile[0], q);
+  if (e == hipSuccess) e = launch_cols(p, c, tile[0], tile[1], q);
   if (e == hipSuccess) e = launch_rows_inv(p, c, fx, fy, tile[2], q, c.desc);
   return e;
 }
@@ -592,8 +597,8 @@ sg_status time_tile(sg_plan p, GridClass& c, int pass, int tile, const void* sig
   hipError_t e = hipSuccess;
   auto launch = [&](int ps) -> hipError_t {
     if (ps == 0)
-      return sg_launch_row_fwd(prec, c.M, sig, c.M, nullptr, c.N, G.r2m, solve, G.bcm, 0, G.twA, c.desc, ng, t3[0], p->st);
-    if (ps == 1) return launch_cols(p, c, t3[1], p->st);
+      return sg_launch_row_fwd(prec, c.M, sig, c.M, nullptr, c.N, G.r2m, solve, G.bcm, G.xb ? G.bcn : nullptr, 0, G.twA, c.desc, ng, t3[0], p->st);
+    if (ps == 1) return launch_cols(p, c, t3[0], t3[1], p->st);
     return launch_rows_inv(p, c, fx, fy, t3[2], p->st, c.desc);
   };
   // each repetition runs the class's whole step and times the pass under
@@ -939,7 +944,8 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
     // in the column pass.
     G.tab_bytes = (prec == SG_FP32_SPLIT && G.fs_adj && !(flags & SG_FLAG_SPECTRA_SPLIT)) ? 4 : 8;
     const size_t tab_el = (size_t)G.tab_bytes;
-    const size_t tab_n = (size_t)(G.M + 1) * (G.N + 1);
+    G.tab_row = G.fs ? sg_tab_row(prec == SG_FP64 ? 0 : 1, G.N) : 0;
+    const size_t tab_n = (size_t)(G.M + 1) * (G.tab_row ? G.tab_row : G.N + 1);
     // grids of equal size, order, cell shape and table form share one pair of spectra
     const auto key = std::make_tuple(G.M, G.N, G.k, G.hx, G.hy, G.tab_bytes);
     const bool fresh = !spectra.count(key);
@@ -1011,6 +1017,10 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
         }
         if (s == SG_OK) (ax ? G.bcn : G.bcm) = (double*)bnd[bk];
       }
+      // columns of the four-step and radix-3 kernels take their padding values from
+      // pass A, in as many parts as its smallest tile leaves
+      if (s == SG_OK && G.k >= 3 && G.fs)
+        s = dev_alloc(p, &G.xb, cb * 4 * (size_t)G.M * sg_pad_groups(pc, G.M, G.N, 1, G.k));
       if (s == SG_OK && fresh) s = build_spectra(p, G, roots64[2 * G.M], roots64[2 * G.N]);
     }
     p->grids.push_back(G);
@@ -1042,7 +1052,7 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
     std::vector<sg_bgrid> h(c.members.size());
     for (size_t j = 0; j < c.members.size(); ++j) {
       const GridPlan& G = p->grids[c.members[j]];
-      h[j] = sg_bgrid{G.off, G.X, G.V, G.tabx, G.taby};
+      h[j] = sg_bgrid{G.off, G.X, G.V, G.tabx, G.taby, G.xb};
     }
     s = dev_alloc(p, (void**)&c.desc, h.size() * sizeof(sg_bgrid));
     if (s == SG_OK)
@@ -1080,7 +1090,7 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
       for (size_t j = 0; j < c.members.size(); ++j) {
         const int gi = c.members[j];
         const GridPlan& G = p->grids[gi];
-        h[j] = sg_bgrid{G.off, (char*)base + xo[gi], (char*)base + vo[gi], G.tabx, G.taby};
+        h[j] = sg_bgrid{G.off, (char*)base + xo[gi], (char*)base + vo[gi], G.tabx, G.taby, G.xb};
       }
       s = dev_alloc(p, (void**)&c.desc_s, h.size() * sizeof(sg_bgrid));
       if (s == SG_OK)
@@ -1269,9 +1279,9 @@ sg_status sg_forces(sg_plan p, const void* sigma, void* fx, void* fy) {
     const int ng = (int)c.members.size();
     const int tj = sg_row_tile(prec, c.M, c.N);
     if (e == hipSuccess)
-      e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, 0, G.twA, c.desc, ng, c.tile[0], p->st);
+      e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, G.xb ? G.bcn : nullptr, 0, G.twA, c.desc, ng, c.tile[0], p->st);
     if (e == hipSuccess) e = mark(p);
-    if (e == hipSuccess) e = launch_cols(p, c, c.tile[1], p->st);
+    if (e == hipSuccess) e = launch_cols(p, c, c.tile[0], c.tile[1], p->st);
     if (e == hipSuccess) e = mark(p);
     if (e == hipSuccess) e = launch_rows_inv(p, c, fx, fy, c.tile[2], p->st, c.desc);
     if (e == hipSuccess) e = mark(p);
@@ -1299,9 +1309,9 @@ sg_status sg_forces_noalloc(sg_plan p, const void* sigma, void* fx, void* fy) {
     const int solve = c.k >= 3 ? c.k : 0;
     const int ng = (int)c.members.size();
     const int tj = sg_row_tile(prec, c.M, c.N);
-    hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, 0, G.twA, c.desc_s, ng,
+    hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, G.xb ? G.bcn : nullptr, 0, G.twA, c.desc_s, ng,
                                      c.tile[0], p->st);
-    if (e == hipSuccess) e = launch_cols(p, c, c.tile[1], p->st, c.desc_s);
+    if (e == hipSuccess) e = launch_cols(p, c, c.tile[0], c.tile[1], p->st, c.desc_s);
     if (e == hipSuccess) e = launch_rows_inv(p, c, fx, fy, c.tile[2], p->st, c.desc_s);
     if (e != hipSuccess) return hip_check(p, e, "force launch (no allocation)");
   }
@@ -1402,9 +1412,9 @@ sg_status sg_forces_adjoint(sg_plan p, const void* gfx, const void* gfy, void* g
     const int ng = (int)c.members.size();
     const int tj = sg_row_tile(prec, c.M, c.N);
     hipError_t e =
-        sg_launch_row_fwd(prec, c.M, gfx, c.M, nullptr, c.N, G.r2m, 0, nullptr, 0, G.twA, c.desc, ng, c.tile[0], p->st);
+        sg_launch_row_fwd(prec, c.M, gfx, c.M, nullptr, c.N, G.r2m, 0, nullptr, nullptr, 0, G.twA, c.desc, ng, c.tile[0], p->st);
     if (e == hipSuccess)
-      e = sg_launch_row_fwd(prec, c.M, gfy, c.M, nullptr, c.N, G.r2m, 0, nullptr, 0, G.twA, c.desc_y, ng, c.tile[0], p->st);
+      e = sg_launch_row_fwd(prec, c.M, gfy, c.M, nullptr, c.N, G.r2m, 0, nullptr, nullptr, 0, G.twA, c.desc_y, ng, c.tile[0], p->st);
     if (e == hipSuccess && G.fs_adj) {
       e = sg_launch_colfs_adj(prec, c.N, nullptr, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.tab_bytes, G.r2n,
                               solve, G.bcn, G.twfs, c.desc, ng, p->st);

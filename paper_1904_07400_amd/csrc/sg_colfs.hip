@@ -6,33 +6,27 @@
 #include <type_traits>
 
 #include "colfs3.hpp"
+#include "colw.hpp"
 
-#ifndef SG_COLFS_SPLIT_F4096
-#define SG_COLFS_SPLIT_F4096 0
-#endif
-#ifndef SG_COLFS_E_F4096
-#define SG_COLFS_E_F4096 8
-#endif
-#ifndef SG_COLFS_SLOTS_F4096
-#define SG_COLFS_SLOTS_F4096 4
-#endif
 #ifndef SG_COLFS_SPLIT_D4096
 #define SG_COLFS_SPLIT_D4096 0
-#endif
-// the prefetching persistent loop (FP32, 4096, single-float tables)
-#ifndef SG_COLFS_PF
-#define SG_COLFS_PF 1
 #endif
 // component split (FP32 columns of 8192): both passes in one launch (1) or two
 #ifndef SG_COLFS_XY
 #define SG_COLFS_XY 1
 #endif
-// ... and for columns of 2048 (two workgroups per compute unit)
-#ifndef SG_COLFS_PF2048
-#define SG_COLFS_PF2048 0
-#endif
-
 namespace sg {
+
+// Lengths of the 16-element column kernel (colw.hpp) in both directions.  At
+// 4096^2 it takes 0.196 ms against 0.242 of the four-step kernel with its
+// prefetching loop (odd k; even k 0.226 against 0.314), the adjoint 0.192
+// against 0.314.  At 2048 the forward passes are level for odd k (0.055 against
+// 0.054 ms) and it spills for even k (0.069 against 0.057), and both directions
+// read one order of the tables.
+template <typename R, int N>
+constexpr bool colw_len() {
+  return sizeof(R) == 4 && N == 4096;
+}
 
 // elements per thread, LDS slots and component split per precision and
 // length (chosen so that no kernel spills registers)
@@ -47,11 +41,6 @@ struct colfs_sel {
 #define SG_COLFS_SLOTS_F2048 2
 #endif
 template <>
-struct colfs_sel<float, 1024> {
-  static constexpr bool ok = true;
-  static constexpr int E = 8, SLOTS = 4, SPLIT = 0;
-};
-template <>
 struct colfs_sel<double, 1024> {
   static constexpr bool ok = true;
   static constexpr int E = 8, SLOTS = 2, SPLIT = 0;
@@ -65,11 +54,6 @@ template <>
 struct colfs_sel<double, 2048> {
   static constexpr bool ok = true;
   static constexpr int E = 8, SLOTS = 2, SPLIT = 0;
-};
-template <>
-struct colfs_sel<float, 4096> {
-  static constexpr bool ok = true;
-  static constexpr int E = SG_COLFS_E_F4096, SLOTS = SG_COLFS_SLOTS_F4096, SPLIT = SG_COLFS_SPLIT_F4096;
 };
 template <>
 struct colfs_sel<float, 8192> {
@@ -95,75 +79,58 @@ static int device_cus() {
   return n > 0 ? n : 256;
 }
 
-// The prefetching loop for FP32 columns of 4096 with single-float tables
-// (its registers fit only then): one workgroup per compute unit.
-template <typename R, typename TO, int N, int MODE>
-struct colfs_pf {
-  // odd orders only: the even orders' bin phases leave no registers for it
-  static constexpr bool on = sizeof(R) == 4 && sizeof(TO) == 4 && (MODE % 2 == 0) &&
-                             ((N == 4096 && SG_COLFS_PF) || (N == 2048 && SG_COLFS_PF2048));
-  static constexpr int per_cu = N == 2048 ? 2 : 1;  // resident workgroups per compute unit
-};
-
 template <typename R, typename TO, int N, int MODE, int COMP>
-static void launch_colfs_k(const cx<R>* X, cx<R>* V, int M, int tj, const TO* tox, const TO* toy, const cx<R>* r2n,
-                           const cx<R>* tw, const sg_bgrid* bg, int ngrids, int bord, const double* bc,
-                           hipStream_t st) {
+static void launch_colfs_k(const cx<R>* X, cx<R>* V, int M, int tj, const TO* tox, const TO* toy, const cx<R>* r2n, int pg,
+                           const cx<R>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   using Sel = colfs_sel<R, N>;
-  if constexpr (colfs_pf<R, TO, N, MODE>::on && COMP == 0) {
-    static const int cus = device_cus();
-    const int slots = cus * colfs_pf<R, TO, N, MODE>::per_cu;
-    const int nb = M < slots ? M : slots;
-    hipLaunchKernelGGL((k_colfs<R, TO, N, MODE, Sel::E, Sel::SLOTS, COMP, true>), dim3(nb, bg ? ngrids : 1),
-                       dim3(N / Sel::E), 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, bord, bc);
-  } else {
-    hipLaunchKernelGGL((k_colfs<R, TO, N, MODE, Sel::E, Sel::SLOTS, COMP>), dim3(M, bg ? ngrids : 1),
-                       dim3(N / Sel::E), 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, bord, bc);
-  }
+  hipLaunchKernelGGL((k_colfs<R, TO, N, MODE, Sel::E, Sel::SLOTS, COMP>), dim3(M, bg ? ngrids : 1), dim3(N / Sel::E), 0,
+                     st, X, V, M, tj, tox, toy, r2n, tw, bg, (const cx<R>*)nullptr, pg);
 }
 
 template <typename R, typename TO, int N, int MODE>
 static hipError_t launch_colfs_m(const cx<R>* X, cx<R>* V, int M, int tj, const TO* tox, const TO* toy,
-                                 const cx<R>* r2n, const cx<R>* tw, const sg_bgrid* bg, int ngrids, int bord,
-                                 const double* bc, hipStream_t st) {
+                                 const cx<R>* r2n, int pg, const cx<R>* tw, const sg_bgrid* bg, int ngrids,
+                                 hipStream_t st) {
   using Sel = colfs_sel<R, N>;
   if constexpr (Sel::SPLIT && SG_COLFS_XY && sizeof(R) == 4) {
     // both component passes of a column in one launch
     hipLaunchKernelGGL((k_colfs_xy<R, TO, N, MODE, Sel::E, Sel::SLOTS>), dim3(M, bg ? ngrids : 1), dim3(N / Sel::E),
-                       0, st, X, V, M, tj, tox, toy, r2n, tw, bg, bord, bc);
+                       0, st, X, V, M, tj, tox, toy, r2n, tw, bg, (const cx<R>*)nullptr, pg);
   } else if constexpr (Sel::SPLIT) {
-    launch_colfs_k<R, TO, N, MODE, 1>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, bord, bc, st);
-    launch_colfs_k<R, TO, N, MODE, 2>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, bord, bc, st);
+    launch_colfs_k<R, TO, N, MODE, 1>(X, V, M, tj, tox, toy, r2n, pg, tw, bg, ngrids, st);
+    launch_colfs_k<R, TO, N, MODE, 2>(X, V, M, tj, tox, toy, r2n, pg, tw, bg, ngrids, st);
   } else {
-    launch_colfs_k<R, TO, N, MODE, 0>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, bord, bc, st);
+    launch_colfs_k<R, TO, N, MODE, 0>(X, V, M, tj, tox, toy, r2n, pg, tw, bg, ngrids, st);
   }
   return hipGetLastError();
 }
 
 template <typename R, typename TO, int N>
 static hipError_t launch_colfs_t(const cx<R>* X, cx<R>* V, int M, int tj, const void* tx, const void* ty, int kind,
-                                 const cx<R>* r2n, int solve, const double* bc, const cx<R>* tw, const sg_bgrid* bg,
+                                 const cx<R>* r2n, int pg, const cx<R>* tw, const sg_bgrid* bg,
                                  int ngrids, hipStream_t st) {
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
-  if (kind == 1) return launch_colfs_m<R, TO, N, 1>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, solve, bc, st);
-  return launch_colfs_m<R, TO, N, 0>(X, V, M, tj, tox, toy, r2n, tw, bg, ngrids, solve, bc, st);
+  if (kind == 1) return launch_colfs_m<R, TO, N, 1>(X, V, M, tj, tox, toy, r2n, pg, tw, bg, ngrids, st);
+  return launch_colfs_m<R, TO, N, 0>(X, V, M, tj, tox, toy, r2n, pg, tw, bg, ngrids, st);
 }
 
 template <typename R, int N>
 static int colfs_twiddles_t(double* re, double* im) {
-  using Sel = colfs_sel<R, N>;
-  using S = fs_shape<N, Sel::E>;
-  if (re && im)
-    fs_fill_twiddles<N, Sel::E>(
-        [](int m, int L, double* cr, double* ci) {
-          // exp(-2 pi i m / L) from long double, rounded once
-          const long double a = 6.283185307179586476925286766559005768L * (long double)m / (long double)L;
-          *cr = (double)cosl(a);
-          *ci = (double)-sinl(a);
-        },
-        re, im);
-  return S::TW_SIZE;
+  // exp(-2 pi i m / L) from long double, rounded once
+  auto root = [](int m, int L, double* cr, double* ci) {
+    const long double a = 6.283185307179586476925286766559005768L * (long double)m / (long double)L;
+    *cr = (double)cosl(a);
+    *ci = (double)-sinl(a);
+  };
+  if constexpr (colw_len<R, N>()) {
+    if (re && im) cw_fill_twiddles<N>(root, re, im);
+    return cw_shape<N>::TW_SIZE;
+  } else {
+    using Sel = colfs_sel<R, N>;
+    if (re && im) fs_fill_twiddles<N, Sel::E>(root, re, im);
+    return fs_shape<N, Sel::E>::TW_SIZE;
+  }
 }
 
 }  // namespace sg
@@ -178,6 +145,10 @@ int sg_colfs_supported(int prec, int N) {
   if (N == 2048 || N == 4096 || N == 8192) return 1;
   if (N == 1024) return prec == 0 ? 1 : 0;
   return ((N == 1536 || N == 768) && prec == 1) ? 2 : 0;
+}
+
+int sg_tab_row(int prec, int N) {
+  return prec == 1 && N == 4096 ? cw_shape<4096>::TAB : 0;
 }
 
 int sg_colfs_twiddles(int prec, int N, double* re, double* im) {
@@ -201,17 +172,17 @@ int sg_colfs_twiddles(int prec, int N, double* re, double* im) {
                      : N == 2048 ? colfs_twiddles_t<double, 2048>(re, im)
                                  : (N == 4096 ? colfs_twiddles_t<double, 4096>(re, im)
                                               : colfs_twiddles_t<double, 8192>(re, im));
-  return N == 1024 ? colfs_twiddles_t<float, 1024>(re, im)
-                   : N == 2048 ? colfs_twiddles_t<float, 2048>(re, im)
+  return N == 2048 ? colfs_twiddles_t<float, 2048>(re, im)
                                : (N == 4096 ? colfs_twiddles_t<float, 4096>(re, im)
                                             : colfs_twiddles_t<float, 8192>(re, im));
 }
 
 namespace sg {
-// f(integral_constant<N>) for the supported lengths
-template <typename F>
+// f(integral_constant<N>) for the supported lengths (1024: FP64)
+template <bool F64, typename F>
 static hipError_t colfs_len(int N, F f) {
-  if (N == 1024) return f(std::integral_constant<int, 1024>{});
+  if constexpr (F64)
+    if (N == 1024) return f(std::integral_constant<int, 1024>{});
   if (N == 2048) return f(std::integral_constant<int, 2048>{});
   if (N == 4096) return f(std::integral_constant<int, 4096>{});
   if (N == 8192) return f(std::integral_constant<int, 8192>{});
@@ -220,29 +191,71 @@ static hipError_t colfs_len(int N, F f) {
 }  // namespace sg
 
 namespace sg {
+// Columns of 16-element threads (colw.hpp): as many workgroups as fit the chip
+// at once (two per compute unit at N = 4096), shared out over the grids, each
+// looping over its columns.
+template <int N>
+static dim3 colw_grid(int M, int ngrids) {
+  using S = cw_shape<N>;
+  constexpr int per_cu = 512 / (S::T * S::P);  // eight waves of 256 registers
+  static const int cus = device_cus();
+  const int tiles = M / S::P;
+  int nb = cus * per_cu / ngrids;
+  nb = nb < 8 ? 8 : nb / 8 * 8;  // whole rounds over the XCDs
+  return dim3(nb < tiles ? nb : tiles, ngrids);
+}
+template <typename TO, int N>
+static hipError_t launch_colw(const cx<float>* X, cx<float>* V, int M, int tj, const void* tx, const void* ty, int kind,
+                              const cx<float>* r2n, int pg, const cx<float>* tw, const sg_bgrid* bg, int ngrids,
+                              hipStream_t st) {
+  using S = cw_shape<N>;
+  const dim3 grid = colw_grid<N>(M, bg ? ngrids : 1), blk(S::T * S::P);
+  const cx<float>* xb = nullptr;
+  if (kind == 1)
+    hipLaunchKernelGGL((k_colw<float, TO, N, 1>), grid, blk, 0, st, X, V, M, tj, (const TO*)tx, (const TO*)ty, r2n, tw,
+                       bg, xb, pg);
+  else
+    hipLaunchKernelGGL((k_colw<float, TO, N, 0>), grid, blk, 0, st, X, V, M, tj, (const TO*)tx, (const TO*)ty, r2n, tw,
+                       bg, xb, pg);
+  return hipGetLastError();
+}
+template <typename TO, int N>
+static hipError_t launch_colw_adj(const cx<float>* Xx, const cx<float>* Xy, cx<float>* Y, int M, int tj, const void* tx,
+                                  const void* ty, int kind, const cx<float>* r2n, int solve, const double* bc,
+                                  const cx<float>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
+  const dim3 grid = colw_grid<N>(M, bg ? ngrids : 1), blk(cw_shape<N>::T);
+  if (kind == 1)
+    hipLaunchKernelGGL((k_colw_adj<float, TO, N, 1>), grid, blk, 0, st, Xx, Xy, Y, M, tj, (const TO*)tx, (const TO*)ty,
+                       r2n, tw, bg, solve, bc);
+  else
+    hipLaunchKernelGGL((k_colw_adj<float, TO, N, 0>), grid, blk, 0, st, Xx, Xy, Y, M, tj, (const TO*)tx, (const TO*)ty,
+                       r2n, tw, bg, solve, bc);
+  return hipGetLastError();
+}
+
 template <typename TO, int L>
 static hipError_t launch_colfs3(const cx<float>* X, cx<float>* V, int M, int tj, const void* tx, const void* ty,
-                                int kind, const cx<float>* r2n, int solve, const double* bc, const cx<float>* tw,
+                                int kind, const cx<float>* r2n, int pg, const cx<float>* tw,
                                 const sg_bgrid* bg, int ngrids, hipStream_t st) {
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
   const dim3 grid(M, bg ? ngrids : 1), blk(kC3T);
   if (kind == 1)
-    hipLaunchKernelGGL((k_colfs3<float, TO, 1, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, solve, bc);
+    hipLaunchKernelGGL((k_colfs3<float, TO, 1, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, (const cx<float>*)nullptr, pg);
   else
-    hipLaunchKernelGGL((k_colfs3<float, TO, 0, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, solve, bc);
+    hipLaunchKernelGGL((k_colfs3<float, TO, 0, L>), grid, blk, 0, st, X, V, M, tj, tox, toy, r2n, tw, bg, (const cx<float>*)nullptr, pg);
   return hipGetLastError();
 }
 }  // namespace sg
 
 hipError_t sg_launch_colfs(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                           int kind, int tab_bytes, const void* r2n, int solve, const double* bc, const void* tw,
+                           int kind, int tab_bytes, const void* r2n, int pg, const void* tw,
                            const sg_bgrid* bg, int ngrids, hipStream_t st) {
   if (N == 1536 || N == 768) {
     if (prec != 1 || tab_bytes != 8) return hipErrorInvalidValue;
     auto go = [&](auto ll) {
       return launch_colfs3<float2, decltype(ll)::value>((const cx<float>*)X, (cx<float>*)V, M, tj, tx, ty, kind,
-                                                        (const cx<float>*)r2n, solve, bc, (const cx<float>*)tw, bg, ngrids,
+                                                        (const cx<float>*)r2n, pg, (const cx<float>*)tw, bg, ngrids,
                                                         st);
     };
     return N == 1536 ? go(std::integral_constant<int, 512>{}) : go(std::integral_constant<int, 256>{});
@@ -253,8 +266,8 @@ hipError_t sg_launch_colfs(int prec, int N, const void* X, void* V, int M, int t
     cx<double>* Vd = (cx<double>*)V;
     const cx<double>* rd = (const cx<double>*)r2n;
     const cx<double>* td = (const cx<double>*)tw;
-    return colfs_len(N, [&](auto n) {
-      return launch_colfs_t<double, double, decltype(n)::value>(Xd, Vd, M, tj, tx, ty, kind, rd, solve, bc, td, bg, ngrids,
+    return colfs_len<true>(N, [&](auto n) {
+      return launch_colfs_t<double, double, decltype(n)::value>(Xd, Vd, M, tj, tx, ty, kind, rd, pg, td, bg, ngrids,
                                                                 st);
     });
   }
@@ -262,11 +275,16 @@ hipError_t sg_launch_colfs(int prec, int N, const void* X, void* V, int M, int t
   cx<float>* Vf = (cx<float>*)V;
   const cx<float>* rf = (const cx<float>*)r2n;
   const cx<float>* tf = (const cx<float>*)tw;
-  return colfs_len(N, [&](auto n) {
+  return colfs_len<false>(N, [&](auto n) {
     constexpr int NN = decltype(n)::value;
-    if (tab_bytes == 8)
-      return launch_colfs_t<float, float2, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
-    return launch_colfs_t<float, float, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
+    if constexpr (colw_len<float, NN>()) {
+      if (tab_bytes == 8) return launch_colw<float2, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, pg, tf, bg, ngrids, st);
+      return launch_colw<float, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, pg, tf, bg, ngrids, st);
+    } else {
+      if (tab_bytes == 8)
+        return launch_colfs_t<float, float2, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, pg, tf, bg, ngrids, st);
+      return launch_colfs_t<float, float, NN>(Xf, Vf, M, tj, tx, ty, kind, rf, pg, tf, bg, ngrids, st);
+    }
   });
 }
 
@@ -309,7 +327,7 @@ hipError_t sg_launch_colfs_adj(int prec, int N, const void* Xx, const void* Xy, 
     cx<double>* y = (cx<double>*)Y;
     const cx<double>* rd = (const cx<double>*)r2n;
     const cx<double>* td = (const cx<double>*)tw;
-    return colfs_len(N, [&](auto n) {
+    return colfs_len<true>(N, [&](auto n) {
       return launch_colfs_adj_t<double, double, decltype(n)::value>(a, b, y, M, tj, tx, ty, kind, rd, solve, bc, td, bg,
                                                                     ngrids, st);
     });
@@ -319,11 +337,17 @@ hipError_t sg_launch_colfs_adj(int prec, int N, const void* Xx, const void* Xy, 
   cx<float>* y = (cx<float>*)Y;
   const cx<float>* rf = (const cx<float>*)r2n;
   const cx<float>* tf = (const cx<float>*)tw;
-  return colfs_len(N, [&](auto n) {
+  return colfs_len<false>(N, [&](auto n) {
     constexpr int NN = decltype(n)::value;
-    if (tab_bytes == 8)
-      return launch_colfs_adj_t<float, float2, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
-    return launch_colfs_adj_t<float, float, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
+    if constexpr (colw_len<float, NN>()) {
+      if (tab_bytes == 8)
+        return launch_colw_adj<float2, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
+      return launch_colw_adj<float, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
+    } else {
+      if (tab_bytes == 8)
+        return launch_colfs_adj_t<float, float2, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
+      return launch_colfs_adj_t<float, float, NN>(a, b, y, M, tj, tx, ty, kind, rf, solve, bc, tf, bg, ngrids, st);
+    }
   });
 }
 

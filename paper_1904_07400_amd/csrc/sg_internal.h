@@ -12,6 +12,10 @@ struct sg_bgrid {
   void* V;
   const void* tabx;
   const void* taby;
+  // k >= 3, columns of the long kernels: the parts of the columns' padding values
+  // (bnd.hpp) in slots N, N + 1, -1, -2, part w of value i of column p at xb[(4 p +
+  // i) pg + w], pg = sg_pad_groups; else NULL
+  void* xb;
 };
 
 // precision code: 0 = FP64, 1 = FP32 (complex arrays are interleaved pairs)
@@ -26,8 +30,10 @@ hipError_t sg_launch_weights(int k, double hx, double hy, int M, int N, double* 
 // tw: stage twiddle tables of the pass (sg_twiddles).  solve: 0 for k = 1, 2,
 // else the order k (3, 4, 5) of the interpolation system that the spectra hold,
 // and bc the coefficient table of the line's padding values (bnd.hpp)
+// With bcn (columns' table; batched) the pass also leaves the parts of the
+// columns' padding values in the descriptors' xb.
 hipError_t sg_launch_row_fwd(int prec, int M, const void* src, int64_t ld, void* X, int nrows, const void* r2m,
-                             int solve, const double* bc, int full, const void* tw, const sg_bgrid* bg, int ngrids, int tile,
+                             int solve, const double* bc, const double* bcn, int full, const void* tw, const sg_bgrid* bg, int ngrids, int tile,
                              hipStream_t st);
 // Launch variants of a pass (0 = A, 1 = B, 2 = C) for a transform length
 // (kernels of the same result with other buffering or elements per
@@ -36,6 +42,8 @@ int sg_variants(int prec, int pass, int len);
 int sg_default_variant(int prec, int pass, int len);
 // largest tile (rows or columns per workgroup) of a pass in a variant
 int sg_max_tile(int prec, int pass, int len, int variant);
+// parts per padding value that pass A with this tile leaves (descriptors' xb)
+int sg_pad_groups(int prec, int M, int nrows, int tile, int order);
 // X: column-major row spectra (bin p of row j at X[p*N + j]); V: tiles of
 // tj rows (sg_row_tile), the layout the inverse row pass reads.  kind: 0 for
 // odd k (tables of A, W = i A), 1 for even k (W = ph i A, ph the bin's
@@ -46,9 +54,10 @@ hipError_t sg_launch_col(int prec, int N, const void* X, void* V, int M, int tj,
 int sg_row_tile(int prec, int M, int N);
 hipError_t sg_launch_row_inv(int prec, int M, const void* V, void* fx, void* fy, int nrows, int tj, const void* r2m,
                              const void* tw, const sg_bgrid* bg, int ngrids, int tile, int variant, hipStream_t st);
-// solve: the order whose inverse symbols multiply the spectra, or 0
-hipError_t sg_launch_spec_col(int N, const void* S, int M, void* tab, int kind, int fp32, int solve, double scale,
-                              const void* r2n, const void* tw, hipStream_t st);
+// solve: the order whose inverse symbols multiply the spectra, or 0; tab_row: the
+// tables' row length if they are in the column pass's order (sg_tab_row), or 0
+hipError_t sg_launch_spec_col(int N, const void* S, int M, void* tab, int kind, int fp32, int solve, int tab_row,
+                              double scale, const void* r2n, const void* tw, hipStream_t st);
 // Stage twiddle tables of a pass's FFT (pass 0: forward rows, 1: columns,
 // 2: inverse rows, 3: spectrum columns, FP64 only, 4: inverse rows in
 // launch variant 1, FP32 only); len = M or N; roots =
@@ -73,10 +82,13 @@ hipError_t sg_launch_adjoint_tail(int prec, int M, int N, const void* Xx, const 
 // when re and im are given); the launch (the arguments of sg_launch_col, plus
 // tab_bytes: 8 for double or float hi+lo tables, 4 for float tables).
 int sg_colfs_supported(int prec, int N);
+// Entries per row of the spectrum tables of a length whose column pass reads
+// them in its threads' order (colw.hpp); 0: natural order, rows of N + 1.
+int sg_tab_row(int prec, int N);
 int sg_colfs_twiddles(int prec, int N, double* re, double* im);
 hipError_t sg_launch_colfs(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                           int kind, int tab_bytes, const void* r2n, int solve, const double* bc, const void* tw,
-                           const sg_bgrid* bg, int ngrids, hipStream_t st);
+                           int kind, int tab_bytes, const void* r2n, int pg, const void* tw, const sg_bgrid* bg,
+                           int ngrids, hipStream_t st);
 // Adjoint column pass of the long columns (the arguments of the column
 // pass of sg_launch_adjoint_tail, plus tab_bytes).
 hipError_t sg_launch_colfs_adj(int prec, int N, const void* Xx, const void* Xy, void* Y, int M, int tj, const void* tx,

@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "bnd.hpp"
+#include "colw.hpp"
 #include "fft.hpp"
 #include "kcommon.hpp"
 #include "sg_internal.h"
@@ -390,17 +391,26 @@ struct rowfwd_cfg {
 };
 
 // solve: the order (3, 4, 5) whose interpolation system the spectra hold, with
-// the row's coefficient table bc (bnd.hpp), or 0.
+// the row's coefficient table bc (bnd.hpp), or 0.  bcn (the columns' table): the
+// workgroups of a grid's first and last rows also leave, per bin, the part of
+// the columns' padding values that their rows give, in the descriptor's xb: pg
+// parts per value, which the column pass adds.  (Summed in the column pass from
+// the column itself, a load and a reduction before the first butterfly, the
+// values cost 0.219 against 0.197 ms in pass B at 4096^2, FP32; formed here as
+// whole rows by one workgroup they outlast the pass.)
 template <typename R, typename In, int M>
 __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M>::T))
     SG_WPE(R, RF)
     k_row_fwd(const In* __restrict__ src, int64_t src_ld, cx<R>* __restrict__ X, int ldx, int nrows,
-              const cx<R>* __restrict__ r2m, int solve, const double* __restrict__ bc, int full,
-              const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
+              const cx<R>* __restrict__ r2m, int solve, const double* __restrict__ bc,
+              const double* __restrict__ bcn, int pg, int full, const cx<R>* __restrict__ tw,
+              const sg_bgrid* __restrict__ bg) {
+  cx<R>* xb = nullptr;
   if (bg) {  // batched: grid blockIdx.y of the class
     const sg_bgrid d = grid_desc(bg);
     src += d.off;
     X = reinterpret_cast<cx<R>*>(d.X);
+    xb = reinterpret_cast<cx<R>*>(d.xb);
   }
   using C = rowfwd_cfg<R, In, M>;
   constexpr int L = C::L, E = C::E, T = C::T, SLOT = C::SLOT, EC = C::EC, NB = C::NB;
@@ -409,10 +419,22 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   cx<R>* const smem = reinterpret_cast<cx<R>*>(sg_dyn_lds);
   const int G = blockDim.x / T;  // rows per workgroup (<= C::G)
   const int g = threadIdx.x / T, t = threadIdx.x % T;
-  const int row0 = xcd_tile(blockIdx.x, gridDim.x) * G, row = row0 + g;
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int row0 = tile * G, row = row0 + g;
   const bool active = row < nrows;
   cx<R>* lds = smem + g * SLOT * NB;
   cx<R>* lds2 = lds + (NB - 1) * SLOT;
+  // the weights of this workgroup's rows in the padding values beyond the end
+  // (side 0) and the start (side 1) of the columns
+  const int tail = (int)gridDim.x - 1 - tile;  // workgroups after this one
+  const bool edge = bcn && (tile < pg || tail < pg);
+  __shared__ double pw[2][2][C::G];
+  if (edge)
+    for (int i = threadIdx.x; i < 4 * G; i += blockDim.x) {
+      const int v = i / (2 * G), side = i / G % 2, r = row0 + i % G;
+      const int far = side ? r : nrows - 1 - r;  // distance from that end
+      pw[v][side][i % G] = (r < nrows && far < kBndLen) ? bcn[v * kBndLen + far] : 0.0;
+    }
   // loads are unconditional (a row past nrows reads row 0 and is masked
   // afterwards), so that they issue together rather than one at a time
   // behind a branch each
@@ -523,6 +545,31 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
     for (int idx = threadIdx.x; idx < nchunk; idx += blockDim.x) {
       const int pl = idx / G, gg = idx % G;
       if (row0 + gg < nrows) X[(int64_t)(2 * e0 * T + pl) * ldx + row0 + gg] = smem[SKW ? pad(idx) : idx];
+    }
+    if (edge) {
+      // this workgroup's part of value v beyond the end (side 0) or the start
+      // (side 1) of the columns, at ((4 p + 2 side + v) pg + its place)
+      for (int pl = threadIdx.x; pl < nchunk / G; pl += blockDim.x) {
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+          const int at = side ? tile : tail;
+          if (at >= pg) continue;
+          double s0x = 0.0, s0y = 0.0, s1x = 0.0, s1y = 0.0;
+#pragma unroll 4
+          for (int gg = 0; gg < G; ++gg) {
+            const cx<R> z = smem[SKW ? pad(pl * G + gg) : pl * G + gg];
+            s0x += pw[0][side][gg] * (double)z.x;
+            s0y += pw[0][side][gg] * (double)z.y;
+            if (solve == 5) {
+              s1x += pw[1][side][gg] * (double)z.x;
+              s1y += pw[1][side][gg] * (double)z.y;
+            }
+          }
+          cx<R>* o = xb + ((int64_t)(2 * e0 * T + pl) * 4 + 2 * side) * pg + at;
+          o[0] = cx<R>{(R)s0x, (R)s0y};
+          o[pg] = cx<R>{(R)s1x, (R)s1y};
+        }
+      }
     }
     __syncthreads();
   }
@@ -1281,7 +1328,7 @@ __device__ __forceinline__ void put_odd(void* tab, int fp32, int64_t idx, double
 template <int N>
 __global__ void __launch_bounds__((spec_cfg<N>::T))
     k_spec_col(const cx<double>* __restrict__ S, int M, void* __restrict__ tab, int kind, int fp32, int solve,
-               double scale, const cx<double>* __restrict__ r2n, const cx<double>* __restrict__ tw) {
+               int tab_row, double scale, const cx<double>* __restrict__ r2n, const cx<double>* __restrict__ tw) {
   using C = spec_cfg<N>;
   constexpr int E = C::E, T = C::T, LL = C::LL;
   __shared__ cx<double> lds[LL];
@@ -1331,6 +1378,15 @@ __global__ void __launch_bounds__((spec_cfg<N>::T))
           a = w.y * cs + w.x * sn;
         }
         if (solve) a *= bnd_symbol(solve, rows[h], M) * bnd_symbol(solve, 2 * qq + half, N);
+        if constexpr (N >= 256 && N <= 4096 && pow2_part(N) == N) {
+          if (tab_row) {  // the order of the 16-element column kernel
+            using W = cw_shape<N>;
+            const int64_t row = (int64_t)rows[h] * tab_row;
+            if (qq < N / 2) put_odd(tab, fp32, row + W::tab_index(qq, half), a);
+            if (half == 0 && qq <= N / 2 && W::tab_again(qq) >= 0) put_odd(tab, fp32, row + W::tab_again(qq), a);
+            continue;
+          }
+        }
         if (half == 0 && qq <= N / 2) put_odd(tab, fp32, (int64_t)rows[h] * (N + 1) + qq, a);
         if (half == 1 && qq < N / 2) put_odd(tab, fp32, (int64_t)rows[h] * (N + 1) + N / 2 + 1 + qq, a);
       }
@@ -1472,17 +1528,22 @@ static inline int pick_tile(int tile, int cap, int n) {
   return g < n ? g : n;
 }
 
+// Workgroups of G rows that the first (or last) rows of a column within the
+// reach of order's padding values can fall in.
+static inline int pad_groups(int order, int G) { return (bnd_reach(order) + 2 * G - 2) / G; }
+
 template <typename R, typename In, int M>
 static hipError_t launch_row_fwd_t(const In* src, int64_t src_ld, cx<R>* X, int nrows, const cx<R>* r2m,
-                                   int solve, const double* bc, int full, const cx<R>* tw, const sg_bgrid* bg, int ngrids, int tile,
-                                   hipStream_t st) {
+                                   int solve, const double* bc, const double* bcn, int full, const cx<R>* tw,
+                                   const sg_bgrid* bg, int ngrids, int tile, hipStream_t st) {
   using C = rowfwd_cfg<R, In, M>;
   const int G = pick_tile(tile, C::G, nrows);
   const int blocks = (nrows + G - 1) / G;
+  const int pg = bcn ? pad_groups(solve, G) : 0;
   constexpr int row_bytes = C::SLOT * C::NB * (int)sizeof(cx<R>);
   dyn_lds_optin<&k_row_fwd<R, In, M>>(C::G * row_bytes);
   hipLaunchKernelGGL((k_row_fwd<R, In, M>), dim3(blocks, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st, src,
-                     src_ld, X, nrows, nrows, r2m, solve, bc, full, tw, bg);
+                     src_ld, X, nrows, nrows, r2m, solve, bc, bcn, pg, full, tw, bg);
   return hipGetLastError();
 }
 
@@ -1523,10 +1584,11 @@ static hipError_t launch_row_inv_t(const cx<R>* V, Out* fx, Out* fy, int nrows, 
 }
 
 template <int N>
-static hipError_t launch_spec_col_t(const cx<double>* S, int M, void* tab, int kind, int fp32, int solve, double scale,
+static hipError_t launch_spec_col_t(const cx<double>* S, int M, void* tab, int kind, int fp32, int solve, int tab_row,
+                                    double scale,
                                     const cx<double>* r2n, const cx<double>* tw, hipStream_t st) {
   using C = spec_cfg<N>;
-  hipLaunchKernelGGL((k_spec_col<N>), dim3(M), dim3(C::T), 0, st, S, M, tab, kind, fp32, solve, scale, r2n, tw);
+  hipLaunchKernelGGL((k_spec_col<N>), dim3(M), dim3(C::T), 0, st, S, M, tab, kind, fp32, solve, tab_row, scale, r2n, tw);
   return hipGetLastError();
 }
 
@@ -1556,12 +1618,12 @@ hipError_t sg_set_gl_tables(const double* x, const double* w) {
 #if SG_IN_PART(1)
 template <typename R, typename In>
 static hipError_t row_fwd_dispatch(int M, const In* src, int64_t ld, cx<R>* X, int nrows, const cx<R>* r2m,
-                                   int solve, const double* bc, int full, const cx<R>* tw, const sg_bgrid* bg, int ngrids, int tile,
-                                   hipStream_t st) {
+                                   int solve, const double* bc, const double* bcn, int full, const cx<R>* tw,
+                                   const sg_bgrid* bg, int ngrids, int tile, hipStream_t st) {
   switch (M) {
 #define CASE(SZ) \
   case SZ:       \
-    return launch_row_fwd_t<R, In, SZ>(src, ld, X, nrows, r2m, solve, bc, full, tw, bg, ngrids, tile, st);
+    return launch_row_fwd_t<R, In, SZ>(src, ld, X, nrows, r2m, solve, bc, bcn, full, tw, bg, ngrids, tile, st);
     SG_ROW_SIZES(CASE)
 #undef CASE
     default:
@@ -1615,14 +1677,14 @@ static hipError_t row_inv_dispatch(int M, const cx<R>* V, Out* fx, Out* fy, int 
 
 #if SG_IN_PART(1)
 hipError_t sg_launch_row_fwd(int prec, int M, const void* src, int64_t ld, void* X, int nrows, const void* r2m,
-                             int solve, const double* bc, int full, const void* tw, const sg_bgrid* bg, int ngrids, int tile,
-                             hipStream_t st) {
+                             int solve, const double* bc, const double* bcn, int full, const void* tw, const sg_bgrid* bg,
+                             int ngrids, int tile, hipStream_t st) {
   if (prec == 0)
     return row_fwd_dispatch<double, double>(M, (const double*)src, ld, (cx<double>*)X, nrows,
-                                            (const cx<double>*)r2m, solve, bc, full, (const cx<double>*)tw, bg, ngrids,
+                                            (const cx<double>*)r2m, solve, bc, bcn, full, (const cx<double>*)tw, bg, ngrids,
                                             tile, st);
   return row_fwd_dispatch<float, float>(M, (const float*)src, ld, (cx<float>*)X, nrows, (const cx<float>*)r2m,
-                                        solve, bc, full, (const cx<float>*)tw, bg, ngrids, tile, st);
+                                        solve, bc, bcn, full, (const cx<float>*)tw, bg, ngrids, tile, st);
 }
 
 #endif
@@ -1692,6 +1754,10 @@ int sg_default_variant(int prec, int pass, int len) {
   return (prec == 1 && pass == 2 && len >= SG_RI_BIG32 && sg_variants(prec, pass, len) > 1) ? 1 : 0;
 }
 
+int sg_pad_groups(int prec, int M, int nrows, int tile, int order) {
+  return pad_groups(order, pick_tile(tile, sg_max_tile(prec, 0, M, 0), nrows));
+}
+
 int sg_max_tile(int prec, int pass, int len, int variant) {
   if (variant < 0 || variant >= sg_variants(prec, pass, len)) return 0;
   return prec == 0 ? max_tile_t<double>(pass, len, 0) : max_tile_t<float>(pass, len, variant);
@@ -1700,12 +1766,12 @@ int sg_max_tile(int prec, int pass, int len, int variant) {
 #endif
 
 #if SG_IN_PART(0)
-hipError_t sg_launch_spec_col(int N, const void* rowspec, int M, void* tab, int kind, int fp32, int solve, double scale,
-                              const void* r2n, const void* tw, hipStream_t st) {
+hipError_t sg_launch_spec_col(int N, const void* rowspec, int M, void* tab, int kind, int fp32, int solve, int tab_row,
+                              double scale, const void* r2n, const void* tw, hipStream_t st) {
   switch (N) {
 #define CASE(SZ) \
   case SZ:       \
-    return launch_spec_col_t<SZ>((const cx<double>*)rowspec, M, tab, kind, fp32, solve, scale, (const cx<double>*)r2n, \
+    return launch_spec_col_t<SZ>((const cx<double>*)rowspec, M, tab, kind, fp32, solve, tab_row, scale, (const cx<double>*)r2n, \
                                 (const cx<double>*)tw, st);
     SG_SIZES(CASE)
 #undef CASE
