@@ -172,7 +172,7 @@ sg_status sg_plan_classes(sg_plan p, int32_t* nclasses, int32_t* info, int32_t c
  * in out: the launch variant of passes A, B, C (kernels of the same
  * transforms with other buffering or elements per thread; variant
  * choices that change the elements per thread change rounding, within the
- * precision of the plan), the tile of each pass (0 = compiled maximum), how
+ * precision of the plan), the tile of each pass (0 = the launch's default), how
  * they were chosen (0 defaults, 1 timed at this plan's creation, 2 taken
  * from the tuning store), then 0.
  *

@@ -27,25 +27,6 @@ namespace sg {
 constexpr int kBndLen = 48;  // entries of c0, then of c1, in a coefficient table (zero past the reach)
 __host__ __device__ constexpr int bnd_reach(int order) { return order == 3 ? 24 : (order == 4 ? 32 : 42); }
 
-// Value of the lane whose index differs by the mask m, within w lanes.  A host
-// build that emulates the kernels and takes this path defines it itself.
-#ifndef SG_SHFL_XOR
-#ifdef __HIPCC__
-#define SG_SHFL_XOR(v, m, w) __shfl_xor(v, m, w)
-#else
-#include <stdlib.h>
-#define SG_SHFL_XOR(v, m, w) (abort(), (v))
-#endif
-#endif
-
-// Sum over the G consecutive threads of a group (a power of two, at most 64).
-template <int G>
-__device__ __forceinline__ double group_sum(double v) {
-#pragma unroll
-  for (int m = G / 2; m > 0; m /= 2) v += SG_SHFL_XOR(v, m, G);
-  return v;
-}
-
 // The inverse symbol of order's system at bin p of a period of 2n.
 __device__ __forceinline__ double bnd_symbol(int order, int p, int n) {
   double s1, c1;  // sin, cos of th
@@ -66,71 +47,38 @@ __device__ __forceinline__ cx<R> bnd_add(cx<R> v, cx<R> u0, cx<R> u1, const doub
   return {bnd_add(v.x, u0.x, u1.x, bc, i), bnd_add(v.y, u0.y, u1.y, bc, i)};
 }
 
-// The two sums of the line x(0), x(1), ... of N values, by the G threads q of
-// a group, for NC independent lines (the components of x).  Loads past the
-// line's end or the table's are clamped and masked, not branched around, so
-// that all of a thread's loads issue together.
-template <int N, int G, int NC, typename F>
-__device__ __forceinline__ void bnd_sums(F x, int order, const double* __restrict__ bc, int q, double (&s)[2][NC]) {
-  constexpr int LEN = N < kBndLen ? N : kBndLen, IT = (LEN + G - 1) / G;
-  double v[IT][NC], c[2][IT];
+// The two sums of the line x(0), x(1), ... of N real values by one thread, its
+// loads 24 together.
+template <int N, typename F>
+__device__ __forceinline__ void bnd_sums(F x, int order, const double* __restrict__ bc, double (&s)[2]) {
+  constexpr int LEN = N < kBndLen ? N : kBndLen, B = LEN < 24 ? LEN : 24;
+  s[0] = s[1] = 0.0;
+#pragma unroll 1
+  for (int i0 = 0; i0 < LEN && i0 < bnd_reach(order); i0 += B) {
+    double v[B];
 #pragma unroll
-  for (int k = 0; k < IT; ++k) {
-    const int i = q + k * G < LEN ? q + k * G : LEN - 1;
-    x(i, v[k]);
-    c[0][k] = bc[i];
-    c[1][k] = bc[kBndLen + i];
-  }
+    for (int k = 0; k < B; ++k) v[k] = x(i0 + k < LEN ? i0 + k : LEN - 1);
 #pragma unroll
-  for (int a = 0; a < NC; ++a) s[0][a] = s[1][a] = 0.0;
+    for (int k = 0; k < B; ++k)  // zero past the line's end and the reach
+      s[0] += (i0 + k < kBndLen ? bc[i0 + k] : 0.0) * v[k];
+    if (order == 5) {
 #pragma unroll
-  for (int k = 0; k < IT; ++k) {
-    const bool in = (k + 1) * G <= LEN || q + k * G < LEN;
-#pragma unroll
-    for (int a = 0; a < NC; ++a) {
-      s[0][a] += in ? c[0][k] * v[k][a] : 0.0;
-      s[1][a] += in ? c[1][k] * v[k][a] : 0.0;
+      for (int k = 0; k < B; ++k) s[1] += (i0 + k < kBndLen ? bc[kBndLen + i0 + k] : 0.0) * v[k];
     }
   }
-#pragma unroll
-  for (int a = 0; a < NC; ++a) {
-    s[0][a] = group_sum<G>(s[0][a]);
-    if (order == 5) s[1][a] = group_sum<G>(s[1][a]);  // else zero: c1 is
-  }
 }
 
-// The values of a complex line (N values) past its ends, by the T threads of
-// its slice of the workgroup (t: this thread): end holds those of slots N, N + 1
-// in the slice's first group of threads, start those of slots -1, -2 in its
-// last; both are zero elsewhere.
-template <int N, int T, typename R>
-__device__ __forceinline__ void bnd_line(const cx<R>* __restrict__ col, int order, const double* __restrict__ bc,
-                                         int t, cx<R> (&end)[2], cx<R> (&start)[2]) {
-  constexpr int G = T < 64 ? T : 64;
-  auto sums = [&](bool rev, cx<R>(&o)[2]) {
-    double s[2][2];
-    bnd_sums<N, G, 2>(
-        [&](int i, double(&v)[2]) {
-          const cx<R> z = col[(unsigned)(rev ? N - 1 - i : i)];
-          v[0] = (double)z.x;
-          v[1] = (double)z.y;
-        },
-        order, bc, t % G, s);
-    o[0] = cx<R>{(R)s[0][0], (R)s[0][1]};
-    o[1] = cx<R>{(R)s[1][0], (R)s[1][1]};
-  };
-  end[0] = end[1] = start[0] = start[1] = cx<R>{(R)0, (R)0};
-  if (t / G == 0) sums(true, end);
-  if (t / G == (T - 1) / G) sums(false, start);
+// The columns' padding values come from pass A in parts, one per group of rows of
+// a size that depends on the row length and the precision only, so that the result
+// does not depend on the rows per workgroup (bnd_parts of them, in groups of gp
+// rows): part w of the value of slot N, N + 1, -1, -2 (i = 0 .. 3) of column c at
+// xb[(4 c + i) pg + w].
+__host__ __device__ constexpr int bnd_parts(int order, int n, int gp) {
+  const int len = bnd_reach(order) < n ? bnd_reach(order) : n;
+  return (len + gp - 1) / gp;
 }
-
-// The value that thread t of a column c's T threads folds in: that of slot N + t
-// for t < 2, of slot t - T for the last two, from the parts that pass A left (xb,
-// pg parts per value); zero elsewhere.
-template <int T, typename R>
-__device__ __forceinline__ cx<R> bnd_value(const cx<R>* __restrict__ xb, int pg, int c, int t) {
-  if (!xb || (t >= 2 && t < T - 2)) return cx<R>{(R)0, (R)0};
-  const cx<R>* p = xb + (int64_t)(4 * c + (t < 2 ? t : 2 + T - 1 - t)) * pg;
+template <typename R>
+__device__ __forceinline__ cx<R> bnd_total(const cx<R>* __restrict__ p, int pg) {
   double x = 0.0, y = 0.0;
   for (int w0 = 0; w0 < pg; w0 += 8) {
     // eight loads together, those past pg masked
@@ -144,6 +92,13 @@ __device__ __forceinline__ cx<R> bnd_value(const cx<R>* __restrict__ xb, int pg,
     }
   }
   return cx<R>{(R)x, (R)y};
+}
+// The value that thread t of the column's T >= 4 threads folds in: that of slot
+// N + t for t < 2, of slot t - T for the last two; zero elsewhere.
+template <int T, typename R>
+__device__ __forceinline__ cx<R> bnd_value(const cx<R>* __restrict__ xb, int pg, int c, int t) {
+  if (!xb || (t >= 2 && t < T - 2)) return cx<R>{(R)0, (R)0};
+  return bnd_total(xb + (int64_t)(4 * c + (t < 2 ? t : 2 + T - 1 - t)) * pg, pg);
 }
 
 }  // namespace sg

@@ -4,7 +4,7 @@
 // Per column p (a bin of the row transforms; column 0 carries the real bins
 // p = 0 and p = M packed as U = C_0 + i C_M):
 //   [k >= 3: the column's padding values, which stand for the interpolation
-//    system (bnd.hpp; xb), or, MODE >= 2, the system solved on the column,
+//    system (bnd.hpp; xb, pg), or, MODE >= 2, the system solved on the column,
 //    FP64, for tables that do not hold its symbol],
 //   forward transform of the column zero-padded to 2N as its even and odd
 //   output bins: fe = FFT_N(a), fo = FFT_N(a_j w_2N^j),

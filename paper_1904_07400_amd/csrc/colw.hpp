@@ -459,7 +459,7 @@ __device__ __forceinline__ void cw_column(const cx<R>* __restrict__ X, cx<R>* __
   }
 }
 
-// kind and xb as in k_colfs (kind: its MODE 0 or 1), the tables in the
+// kind, xb and pg as in k_colfs (kind: its MODE 0 or 1), the tables in the
 // order of cw_shape.  A workgroup loops over tiles of P columns
 // blockIdx.x, blockIdx.x + gridDim.x, ..., so that its twiddles are read once.
 template <typename R, typename TO, int N, int kind>

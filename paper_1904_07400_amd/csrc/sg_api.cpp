@@ -241,7 +241,7 @@ struct GridPlan {
   void* twfs = nullptr;     // its twiddle table
   double* bcm = nullptr;    // k >= 3: coefficient tables of the padding values of rows and columns
   double* bcn = nullptr;
-  void* xb = nullptr;       // k >= 3 with a long column kernel: parts of the columns' padding values
+  void* xb = nullptr;       // k >= 3: parts of the columns' padding values (bnd.hpp)
   int tab_row = 0;          // row length of the spectra in the column pass's order (sg_tab_row); 0: natural
   int tab_bytes = 8;        // bytes per spectrum entry: double, float hi + lo, or float
 };
@@ -254,7 +254,7 @@ struct GridClass {
   sg_bgrid* desc = nullptr;
   sg_bgrid* desc_y = nullptr;  // the same with X = V (adjoint: row spectra of gy)
   sg_bgrid* desc_s = nullptr;  // the same with X and V in the no-allocation scratch
-  int tile[3] = {0, 0, 0};  // rows / columns per workgroup of passes A, B, C (0 = compiled maximum)
+  int tile[3] = {0, 0, 0};  // rows / columns per workgroup of passes A, B, C (0 = the launch's default)
   int var[3] = {0, 0, 0};   // launch variant of passes A, B, C (sg_variants)
   int src = 0;              // how var and tile were chosen: 0 defaults, 1 timed here, 2 the tuning store
 };
@@ -500,21 +500,19 @@ constexpr size_t kMaxGraphs = 4;
 constexpr int kSideStreams = 4;
 
 // The column pass of one class: the four-step kernel for long columns, the
-// Stockham kernel otherwise.  tile_a: pass A's tile, which decides the parts of
-// the padding values that it leaves.
-hipError_t launch_cols(sg_plan p, const GridClass& c, int tile_a, int tile, hipStream_t q,
-                       const sg_bgrid* desc = nullptr) {
+// Stockham kernel otherwise.
+hipError_t launch_cols(sg_plan p, const GridClass& c, int tile, hipStream_t q, const sg_bgrid* desc = nullptr) {
   const int prec = p->prec == SG_FP64 ? 0 : 1;
   const GridPlan& G = p->grids[c.members[0]];
-  const int solve = c.k >= 3 ? c.k : 0;
+  const int pg = c.k >= 3 ? sg_pad_parts(prec, c.M, c.N, c.k) : 0;
   const int ng = (int)c.members.size();
   const int tj = sg_row_tile(prec, c.M, c.N);
   const sg_bgrid* d = desc ? desc : c.desc;
   if (G.fs)
     return sg_launch_colfs(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.tab_bytes, G.r2n,
-                           G.xb ? sg_pad_groups(prec, c.M, c.N, tile_a, c.k) : 0, G.twfs, d, ng, q);
-  return sg_launch_col(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.r2n, solve, G.bcn, G.twB, d, ng,
-                       tile, c.var[1], q);
+                           pg, G.twfs, d, ng, q);
+  return sg_launch_col(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.r2n, pg, G.twB, d, ng, tile,
+                       c.var[1], q);
 }
 
 // The inverse row pass of one class (its launch variant and that variant's
@@ -536,7 +534,7 @@ hipError_t issue_class(sg_plan p, const GridClass& c, const void* sigma, void* f
   const int solve = c.k >= 3 ? c.k : 0;
   const int ng = (int)c.members.size();
   hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, G.xb ? G.bcn : nullptr, 0, G.twA, c.desc, ng, tile[0], q);
-  if (e == hipSuccess) e = launch_cols(p, c, tile[0], tile[1], q);
+  if (e == hipSuccess) e = launch_cols(p, c, tile[1], q);
   if (e == hipSuccess) e = launch_rows_inv(p, c, fx, fy, tile[2], q, c.desc);
   return e;
 }
@@ -598,7 +596,7 @@ sg_status time_tile(sg_plan p, GridClass& c, int pass, int tile, const void* sig
   auto launch = [&](int ps) -> hipError_t {
     if (ps == 0)
       return sg_launch_row_fwd(prec, c.M, sig, c.M, nullptr, c.N, G.r2m, solve, G.bcm, G.xb ? G.bcn : nullptr, 0, G.twA, c.desc, ng, t3[0], p->st);
-    if (ps == 1) return launch_cols(p, c, t3[0], t3[1], p->st);
+    if (ps == 1) return launch_cols(p, c, t3[1], p->st);
     return launch_rows_inv(p, c, fx, fy, t3[2], p->st, c.desc);
   };
   // each repetition runs the class's whole step and times the pass under
@@ -1017,10 +1015,8 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
         }
         if (s == SG_OK) (ax ? G.bcn : G.bcm) = (double*)bnd[bk];
       }
-      // columns of the four-step and radix-3 kernels take their padding values from
-      // pass A, in as many parts as its smallest tile leaves
-      if (s == SG_OK && G.k >= 3 && G.fs)
-        s = dev_alloc(p, &G.xb, cb * 4 * (size_t)G.M * sg_pad_groups(pc, G.M, G.N, 1, G.k));
+      // the columns' padding values, which pass A leaves for pass B
+      if (s == SG_OK && G.k >= 3) s = dev_alloc(p, &G.xb, cb * 4 * (size_t)G.M * sg_pad_parts(pc, G.M, G.N, G.k));
       if (s == SG_OK && fresh) s = build_spectra(p, G, roots64[2 * G.M], roots64[2 * G.N]);
     }
     p->grids.push_back(G);
@@ -1281,7 +1277,7 @@ sg_status sg_forces(sg_plan p, const void* sigma, void* fx, void* fy) {
     if (e == hipSuccess)
       e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, G.xb ? G.bcn : nullptr, 0, G.twA, c.desc, ng, c.tile[0], p->st);
     if (e == hipSuccess) e = mark(p);
-    if (e == hipSuccess) e = launch_cols(p, c, c.tile[0], c.tile[1], p->st);
+    if (e == hipSuccess) e = launch_cols(p, c, c.tile[1], p->st);
     if (e == hipSuccess) e = mark(p);
     if (e == hipSuccess) e = launch_rows_inv(p, c, fx, fy, c.tile[2], p->st, c.desc);
     if (e == hipSuccess) e = mark(p);
@@ -1311,7 +1307,7 @@ sg_status sg_forces_noalloc(sg_plan p, const void* sigma, void* fx, void* fy) {
     const int tj = sg_row_tile(prec, c.M, c.N);
     hipError_t e = sg_launch_row_fwd(prec, c.M, sigma, c.M, nullptr, c.N, G.r2m, solve, G.bcm, G.xb ? G.bcn : nullptr, 0, G.twA, c.desc_s, ng,
                                      c.tile[0], p->st);
-    if (e == hipSuccess) e = launch_cols(p, c, c.tile[0], c.tile[1], p->st, c.desc_s);
+    if (e == hipSuccess) e = launch_cols(p, c, c.tile[1], p->st, c.desc_s);
     if (e == hipSuccess) e = launch_rows_inv(p, c, fx, fy, c.tile[2], p->st, c.desc_s);
     if (e != hipSuccess) return hip_check(p, e, "force launch (no allocation)");
   }
@@ -1332,16 +1328,8 @@ sg_status sg_plan_classes(sg_plan p, int32_t* nclasses, int32_t* info, int32_t c
       o[2] = c.k;
       o[3] = (int32_t)c.members.size();
       for (int pass = 0; pass < 3; ++pass) {
-        // the tile the launch uses: rows capped by the row count; columns the
-        // largest power of two that divides nx
-        int t = c.tile[pass] > 0 ? c.tile[pass] : sg_max_tile(prec, pass, pass == 1 ? c.N : c.M, c.var[pass]);
-        if (pass == 1) {
-          int d = 1;
-          while (d < t && c.M % (2 * d) == 0) d *= 2;
-          t = d;
-        } else if (t > c.N) {
-          t = c.N;
-        }
+        const int t = sg_tile(prec, pass, pass == 1 ? c.N : c.M, c.var[pass], pass == 1 ? c.M : c.N,
+                              (int)c.members.size(), c.tile[pass], pass == 0 && c.k >= 3);
         o[4 + pass] = t;
       }
       o[7] = c.src;

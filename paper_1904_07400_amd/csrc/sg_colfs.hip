@@ -210,13 +210,12 @@ static hipError_t launch_colw(const cx<float>* X, cx<float>* V, int M, int tj, c
                               hipStream_t st) {
   using S = cw_shape<N>;
   const dim3 grid = colw_grid<N>(M, bg ? ngrids : 1), blk(S::T * S::P);
-  const cx<float>* xb = nullptr;
   if (kind == 1)
     hipLaunchKernelGGL((k_colw<float, TO, N, 1>), grid, blk, 0, st, X, V, M, tj, (const TO*)tx, (const TO*)ty, r2n, tw,
-                       bg, xb, pg);
+                       bg, (const cx<float>*)nullptr, pg);
   else
     hipLaunchKernelGGL((k_colw<float, TO, N, 0>), grid, blk, 0, st, X, V, M, tj, (const TO*)tx, (const TO*)ty, r2n, tw,
-                       bg, xb, pg);
+                       bg, (const cx<float>*)nullptr, pg);
   return hipGetLastError();
 }
 template <typename TO, int N>

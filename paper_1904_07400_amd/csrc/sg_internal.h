@@ -12,9 +12,8 @@ struct sg_bgrid {
   void* V;
   const void* tabx;
   const void* taby;
-  // k >= 3, columns of the long kernels: the parts of the columns' padding values
-  // (bnd.hpp) in slots N, N + 1, -1, -2, part w of value i of column p at xb[(4 p +
-  // i) pg + w], pg = sg_pad_groups; else NULL
+  // k >= 3: the parts of the columns' padding values that pass A leaves (bnd.hpp);
+  // else NULL
   void* xb;
 };
 
@@ -23,14 +22,14 @@ struct sg_bgrid {
 // pointer arguments; otherwise ngrids grids of the same sizes and order from
 // bg (blockIdx.y = grid), with the buffer arguments as bases of the packed
 // buffers.  tile: rows (passes A, C) or columns (pass B) per workgroup,
-// 0 = the compiled maximum.
+// 0 = the launch's default.
 hipError_t sg_set_gl_tables(const double* x /*4x16*/, const double* w /*4x16*/);
 hipError_t sg_launch_weights(int k, double hx, double hy, int M, int N, double* wx, double* wy, int layout,
                              hipStream_t st);
 // tw: stage twiddle tables of the pass (sg_twiddles).  solve: 0 for k = 1, 2,
 // else the order k (3, 4, 5) of the interpolation system that the spectra hold,
 // and bc the coefficient table of the line's padding values (bnd.hpp)
-// With bcn (columns' table; batched) the pass also leaves the parts of the
+// With bcn (the columns' table; batched) the pass also leaves the parts of the
 // columns' padding values in the descriptors' xb.
 hipError_t sg_launch_row_fwd(int prec, int M, const void* src, int64_t ld, void* X, int nrows, const void* r2m,
                              int solve, const double* bc, const double* bcn, int full, const void* tw, const sg_bgrid* bg, int ngrids, int tile,
@@ -42,14 +41,19 @@ int sg_variants(int prec, int pass, int len);
 int sg_default_variant(int prec, int pass, int len);
 // largest tile (rows or columns per workgroup) of a pass in a variant
 int sg_max_tile(int prec, int pass, int len, int variant);
-// parts per padding value that pass A with this tile leaves (descriptors' xb)
-int sg_pad_groups(int prec, int M, int nrows, int tile, int order);
+// parts per padding value that pass A leaves for a grid of N rows of M
+int sg_pad_parts(int prec, int M, int N, int order);
+// rows (passes 0, 2) or columns (1) per workgroup that a launch over ngrids grids
+// with `lines` of them uses when asked for tile (0: its default); parts: pass 0 of a
+// plan with k >= 3
+int sg_tile(int prec, int pass, int len, int variant, int lines, int ngrids, int tile, int parts);
 // X: column-major row spectra (bin p of row j at X[p*N + j]); V: tiles of
 // tj rows (sg_row_tile), the layout the inverse row pass reads.  kind: 0 for
 // odd k (tables of A, W = i A), 1 for even k (W = ph i A, ph the bin's
-// half-cell phase); tx, ty are the quarter tables of A in either case.
+// half-cell phase); tx, ty are the quarter tables of A in either case; pg: the
+// parts per padding value in the descriptors' xb, or 0.
 hipError_t sg_launch_col(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                         int kind, const void* r2n, int solve, const double* bc, const void* tw, const sg_bgrid* bg,
+                         int kind, const void* r2n, int pg, const void* tw, const sg_bgrid* bg,
                          int ngrids, int tile, int variant, hipStream_t st);
 int sg_row_tile(int prec, int M, int N);
 hipError_t sg_launch_row_inv(int prec, int M, const void* V, void* fx, void* fy, int nrows, int tj, const void* r2m,

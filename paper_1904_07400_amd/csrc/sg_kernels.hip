@@ -36,7 +36,7 @@
 #define SG_RI_THREADS32 256
 #endif
 #ifndef SG_RI_THREADS64
-#define SG_RI_THREADS64 1024
+#define SG_RI_THREADS64 256
 #endif
 #ifndef SG_RI_E32
 #define SG_RI_E32 8
@@ -385,25 +385,29 @@ struct rowfwd_cfg {
   static constexpr int WG = sizeof(R) == 4 ? SG_RF_THREADS32 : SG_RF_THREADS64;
   static constexpr int G0 = WG / T < 1 ? 1 : (WG / T < 16 ? WG / T : 16);
   static constexpr int GL = kLdsBudget / (NB * SLOT * (int)sizeof(cx<R>));
-  static constexpr int G = (G0 < GL ? G0 : GL) < 1 ? 1 : (G0 < GL ? G0 : GL);
+  static constexpr int G1 = (G0 < GL ? G0 : GL) < 1 ? 1 : (G0 < GL ? G0 : GL);
+  // rows per part of the columns' padding values (bnd.hpp), and whole groups of
+  // them per workgroup
+  static constexpr int GP = G1 >= 4 ? 4 : (G1 >= 2 ? 2 : 1);
+  static constexpr int G = G1 / GP * GP;
   // e-values per transposed-store chunk (2T bins per e, G rows)
   static constexpr int EC = (SLOT / (2 * T)) < 1 ? 1 : ((SLOT / (2 * T)) > E ? E : SLOT / (2 * T));
 };
 
 // solve: the order (3, 4, 5) whose interpolation system the spectra hold, with
 // the row's coefficient table bc (bnd.hpp), or 0.  bcn (the columns' table): the
-// workgroups of a grid's first and last rows also leave, per bin, the part of
-// the columns' padding values that their rows give, in the descriptor's xb: pg
-// parts per value, which the column pass adds.  (Summed in the column pass from
-// the column itself, a load and a reduction before the first butterfly, the
-// values cost 0.219 against 0.197 ms in pass B at 4096^2, FP32; formed here as
-// whole rows by one workgroup they outlast the pass.)
+// workgroups of a grid's first and last rows also leave, per bin and group of GP
+// rows, the part of the columns' padding values that those rows give, pg parts
+// per value.  (Summed in the column pass from the column itself the values cost
+// 0.218 against 0.191 ms in pass B at 4096^2, FP32, and registers in the shorter
+// columns' kernels; formed here as whole rows by one workgroup they outlast the
+// pass.)
 template <typename R, typename In, int M>
 __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M>::T))
     SG_WPE(R, RF)
     k_row_fwd(const In* __restrict__ src, int64_t src_ld, cx<R>* __restrict__ X, int ldx, int nrows,
               const cx<R>* __restrict__ r2m, int solve, const double* __restrict__ bc,
-              const double* __restrict__ bcn, int pg, int full, const cx<R>* __restrict__ tw,
+              const double* __restrict__ bcn, int full, const cx<R>* __restrict__ tw,
               const sg_bgrid* __restrict__ bg) {
   cx<R>* xb = nullptr;
   if (bg) {  // batched: grid blockIdx.y of the class
@@ -419,15 +423,15 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   cx<R>* const smem = reinterpret_cast<cx<R>*>(sg_dyn_lds);
   const int G = blockDim.x / T;  // rows per workgroup (<= C::G)
   const int g = threadIdx.x / T, t = threadIdx.x % T;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int row0 = tile * G, row = row0 + g;
+  const int row0 = xcd_tile(blockIdx.x, gridDim.x) * G, row = row0 + g;
   const bool active = row < nrows;
   cx<R>* lds = smem + g * SLOT * NB;
   cx<R>* lds2 = lds + (NB - 1) * SLOT;
   // the weights of this workgroup's rows in the padding values beyond the end
   // (side 0) and the start (side 1) of the columns
-  const int tail = (int)gridDim.x - 1 - tile;  // workgroups after this one
-  const bool edge = bcn && (tile < pg || tail < pg);
+  constexpr int GP = C::GP;
+  const int pg = bcn ? bnd_parts(solve, nrows, GP) : 0;
+  const bool edge = bcn && (row0 < pg * GP || nrows - row0 - G < pg * GP);
   __shared__ double pw[2][2][C::G];
   if (edge)
     for (int i = threadIdx.x; i < 4 * G; i += blockDim.x) {
@@ -460,23 +464,18 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
     if (solve) {
       // the values past the row's ends: x[M], x[M + 1] (folded onto element 0)
       // and x[2M - 2], x[2M - 1] (onto element L - 1)
-      constexpr int GB = T < 64 ? T : 64;
-      double v[2][1];
-      if (t / GB == 0) {
-        bnd_sums<M, GB, 1>([&](int i, double(&x)[1]) { x[0] = (double)s[M - 1 - i]; }, solve, bc, t % GB, v);
-        if (t == 0) {
-          const cx<R> hi{m1 * (R)v[0][0], m1 * (R)v[1][0]};
-          ze[0] = ze[0] + hi;
-          zo[0] = zo[0] - hi;  // w_M^0 = 1
-        }
+      double v[2];
+      if (t == 0) {
+        bnd_sums<M>([&](int i) { return (double)s[M - 1 - i]; }, solve, bc, v);
+        const cx<R> hi{m1 * (R)v[0], m1 * (R)v[1]};
+        ze[0] = ze[0] + hi;
+        zo[0] = zo[0] - hi;  // w_M^0 = 1
       }
-      if (t / GB == (T - 1) / GB) {
-        bnd_sums<M, GB, 1>([&](int i, double(&x)[1]) { x[0] = (double)s[i]; }, solve, bc, t % GB, v);
-        if (t == T - 1) {
-          const cx<R> hi{m1 * (R)v[1][0], m1 * (R)v[0][0]};
-          ze[E - 1] = ze[E - 1] + hi;
-          zo[E - 1] = zo[E - 1] - cmul(hi, r2m[2 * (L - 1)]);
-        }
+      if (t == T - 1) {
+        bnd_sums<M>([&](int i) { return (double)s[i]; }, solve, bc, v);
+        const cx<R> hi{m1 * (R)v[1], m1 * (R)v[0]};
+        ze[E - 1] = ze[E - 1] + hi;
+        zo[E - 1] = zo[E - 1] - cmul(hi, r2m[2 * (L - 1)]);
       }
     }
   }
@@ -547,23 +546,21 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
       if (row0 + gg < nrows) X[(int64_t)(2 * e0 * T + pl) * ldx + row0 + gg] = smem[SKW ? pad(idx) : idx];
     }
     if (edge) {
-      // this workgroup's part of value v beyond the end (side 0) or the start
-      // (side 1) of the columns, at ((4 p + 2 side + v) pg + its place)
-      for (int pl = threadIdx.x; pl < nchunk / G; pl += blockDim.x) {
+      // group q's part of values v beyond the end and the start of the columns
+      for (int i = threadIdx.x; i < nchunk / GP; i += blockDim.x) {
+        const int pl = i / (G / GP), q = i % (G / GP) * GP;
 #pragma unroll
         for (int side = 0; side < 2; ++side) {
-          const int at = side ? tile : tail;
-          if (at >= pg) continue;
+          const int at = (side ? row0 + q : nrows - GP - row0 - q) / GP;
+          if (at >= pg || row0 + q >= nrows) continue;
           double s0x = 0.0, s0y = 0.0, s1x = 0.0, s1y = 0.0;
-#pragma unroll 4
-          for (int gg = 0; gg < G; ++gg) {
-            const cx<R> z = smem[SKW ? pad(pl * G + gg) : pl * G + gg];
-            s0x += pw[0][side][gg] * (double)z.x;
-            s0y += pw[0][side][gg] * (double)z.y;
-            if (solve == 5) {
-              s1x += pw[1][side][gg] * (double)z.x;
-              s1y += pw[1][side][gg] * (double)z.y;
-            }
+#pragma unroll
+          for (int gg = 0; gg < GP; ++gg) {
+            const cx<R> z = smem[SKW ? pad(pl * G + q + gg) : pl * G + q + gg];
+            s0x += pw[0][side][q + gg] * (double)z.x;
+            s0y += pw[0][side][q + gg] * (double)z.y;
+            s1x += pw[1][side][q + gg] * (double)z.x;
+            s1y += pw[1][side][q + gg] * (double)z.y;
           }
           cx<R>* o = xb + ((int64_t)(2 * e0 * T + pl) * 4 + 2 * side) * pg + at;
           o[0] = cx<R>{(R)s0x, (R)s0y};
@@ -680,23 +677,14 @@ __device__ __forceinline__ cx<R> spec_mul(cx<R> z, int kind, const TO* to, int p
 // C_0 = (U(q) + conj U(-q))/2, C_M = (U(q) - conj U(-q))/(2i), and the
 // products are re-packed as G_0 + i G_M.  Even k: w2n = exp(-i pi q'/N),
 // php = exp(-i pi c / 2M), rho = exp(-i pi / 2N) make the bin phases.
+// packed_product: the exchange and column 0's share (every thread of the
+// workgroup calls it).
 template <typename R, typename TO, int N, int E, int T>
-__device__ __forceinline__ void col_product(const cx<R>* f, cx<R>* g, int half, bool exch, bool packed, cx<R>* lds,
-                                            int kind, const TO* to, R eps, int c, int M, int t, const cx<R>* w2n,
-                                            cx<R> php, cx<R> rho) {
-  const cx<R> phh = half ? cmul(php, rho) : php;  // column and half part of the phase
-  if (!exch) {
-    // no packed column in this workgroup: independent loads, no branches
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      g[e] = spec_mul<R, TO, N>(f[e], kind, to, c, t + e * T, half, eps, cmul(w2n[e], phh));
-    return;
-  }
+__device__ __forceinline__ void packed_product(const cx<R>* f, cx<R>* g, int half, bool packed, cx<R>* lds, int kind,
+                                               const TO* to, R eps, int M, int t, const cx<R>* w2n, cx<R> rho) {
 #pragma unroll
   for (int e = 0; e < E; ++e) lds[pad(t + e * T)] = f[e];
   __syncthreads();
-  // one branch around each loop (uniform per column group), so that the
-  // loads of a loop issue together
   if (packed) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -711,20 +699,32 @@ __device__ __forceinline__ void col_product(const cx<R>* f, cx<R>* g, int half, 
       const cx<R> wm = spec_mul<R, TO, N>(cmv, kind, to, M, qq, half, eps, cx<R>{ph0.y, -ph0.x});
       g[e] = cx<R>{w0.x - wm.y, w0.y + wm.x};
     }
-  } else {
+  }
+  __syncthreads();
+}
+template <typename R, typename TO, int N, int E, int T>
+__device__ __forceinline__ void col_product(const cx<R>* f, cx<R>* g, int half, bool exch, bool packed, cx<R>* lds,
+                                            int kind, const TO* to, R eps, int c, int M, int t, const cx<R>* w2n,
+                                            cx<R> php, cx<R> rho) {
+  const cx<R> phh = half ? cmul(php, rho) : php;  // column and half part of the phase
+  // one branch around each loop (uniform per column group), so that the
+  // loads of a loop issue together; the other columns share one loop whether or
+  // not the packed column is in their workgroup, so that their rounding does not
+  // depend on the columns per workgroup
+  if (exch) packed_product<R, TO, N, E, T>(f, g, half, packed, lds, kind, to, eps, M, t, w2n, rho);
+  if (!packed) {
 #pragma unroll
     for (int e = 0; e < E; ++e)
       g[e] = spec_mul<R, TO, N>(f[e], kind, to, c, t + e * T, half, eps, cmul(w2n[e], phh));
   }
-  __syncthreads();
 }
 
-// kind: 0 odd k, 1 even k (phased tables).  solve, bc: as in k_row_fwd, for
-// the columns.
+// kind: 0 odd k, 1 even k (phased tables).  xb, pg: the parts of the
+// columns' padding values (bnd.hpp), or NULL.
 template <typename R, typename TO, int N, int kind, int VA = 0>
 __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
     SG_WPE(R, COL) k_col(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
-          const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, int solve, const double* __restrict__ bc,
+          const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ xb, int pg,
           const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
   if (bg) {  // batched: grid blockIdx.y of the class
     const sg_bgrid d = grid_desc(bg);
@@ -732,6 +732,7 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
     V = reinterpret_cast<cx<R>*>(d.V);
     tox = reinterpret_cast<const TO*>(d.tabx);
     toy = reinterpret_cast<const TO*>(d.taby);
+    xb = reinterpret_cast<const cx<R>*>(d.xb);
   }
   using C = col_cfg<R, N, VA>;
   constexpr int E = C::E, T = C::T, LL = C::SLOT, NBUF = C::NBUF;
@@ -787,11 +788,19 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
     fo[e] = cmul(a[e], w2n[e]);
     fe[e] = a[e];
   }
-  if (solve) {
+  if (xb) {
     // the values past the column's ends, folded onto elements 0, 1 (slots N, N
     // + 1) and N - 1, N - 2 (slots -1, -2)
     cx<R> end[2], start[2];
-    bnd_line<N, T>(col, solve, bc, t, end, start);
+    if constexpr (T >= 4) {
+      end[0] = end[1] = start[0] = start[1] = bnd_value<T>(xb, pg, c, t);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        end[i] = bnd_total(xb + (int64_t)(4 * c + i) * pg, pg);
+        start[i] = bnd_total(xb + (int64_t)(4 * c + 2 + i) * pg, pg);
+      }
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       // element i of thread i (or of thread 0 when it holds both)
@@ -829,9 +838,14 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
       }
     }
     cx<R> g4[4][E];
-    bool done = false;
     if constexpr (pre) {
-      if (!exch) {
+      if (exch) {
+        packed_product<R, TO, N, E, T>(fe, g4[0], 0, packed, lds, kind, tox, (R)1, M, t, w2n, rho);
+        packed_product<R, TO, N, E, T>(fe, g4[1], 0, packed, lds, kind, toy, (R)-1, M, t, w2n, rho);
+        packed_product<R, TO, N, E, T>(fo, g4[2], 1, packed, lds, kind, tox, (R)1, M, t, w2n, rho);
+        packed_product<R, TO, N, E, T>(fo, g4[3], 1, packed, lds, kind, toy, (R)-1, M, t, w2n, rho);
+      }
+      if (!packed) {
         if constexpr (kind == 1) {
           // even k: the bin phases, shared by both components
           const cx<R> pho = cmul(php, rho);
@@ -848,14 +862,7 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
           for (int e = 0; e < E; ++e)
             g4[i][e] = apply_iA((i >> 1) ? fo[e] : fe[e], tv[i][e],
                                 odd_sign<R, N>(t + e * T, i >> 1, (i & 1) ? -ex : ex));
-        done = true;
       }
-    }
-    if (!done) {
-      col_product<R, TO, N, E, T>(fe, g4[0], 0, exch, packed, lds, kind, tox, (R)1, c, M, t, w2n, php, rho);
-      col_product<R, TO, N, E, T>(fe, g4[1], 0, exch, packed, lds, kind, toy, (R)-1, c, M, t, w2n, php, rho);
-      col_product<R, TO, N, E, T>(fo, g4[2], 1, exch, packed, lds, kind, tox, (R)1, c, M, t, w2n, php, rho);
-      col_product<R, TO, N, E, T>(fo, g4[3], 1, exch, packed, lds, kind, toy, (R)-1, c, M, t, w2n, php, rho);
     }
     fftn<true, N, T, 4>(g4, lds, LL, tw, t);
 #pragma unroll
@@ -983,6 +990,11 @@ struct rowinv_wpe {
                                    : (sizeof(R) == 4 ? SG_RI_WPE32 : SG_RI_WPE64);
 };
 
+template <typename R, int M, int VA>
+constexpr bool rowinv_static() {
+  return rowinv_wpe<R, M, VA>::value > 1;
+}
+
 template <typename R, typename Out, int M, int VA = 0>
 __global__ void __launch_bounds__((rowinv_cfg<R, M, VA>::G * rowinv_cfg<R, M, VA>::T))
     __attribute__((amdgpu_waves_per_eu(rowinv_wpe<R, M, VA>::value)))
@@ -996,9 +1008,14 @@ __global__ void __launch_bounds__((rowinv_cfg<R, M, VA>::G * rowinv_cfg<R, M, VA
   }
   using C = rowinv_cfg<R, M, VA>;
   constexpr int E = C::E, T = C::T, LL = C::LL, NB = C::NB;
-  // static, for the compiled maximum of rows (LDS sized at launch measured
-  // slower here: its 128 registers then spill)
-  __shared__ cx<R> smem[C::G * C::RS];
+  // sized at launch (dyn_lds), but static, for the compiled maximum of rows, in
+  // the kernels held to 128 registers, which spill otherwise
+  extern __shared__ __align__(16) unsigned char sg_dyn_lds[];
+  cx<R>* smem = reinterpret_cast<cx<R>*>(sg_dyn_lds);
+  if constexpr (rowinv_static<R, M, VA>()) {
+    __shared__ cx<R> fixed[C::G * C::RS];
+    smem = fixed;
+  }
   // G rows per workgroup, interleaved lane by lane (thread t of row g is
   // thread t G + g), so that the G rows' elements of one bin, adjacent in a
   // tile, are read by adjacent lanes
@@ -1060,8 +1077,8 @@ __device__ __forceinline__ void col_products_adj(const cx<R>* fx, const cx<R>* f
                                                  bool packed, cx<R>* lds, int kind, const TO* tox, const TO* toy,
                                                  int c, int M, int t, const cx<R>* r2n, cx<R> php, cx<R> rho) {
   const cx<R> phh = half ? cmul(php, rho) : php;
-  if (!exch) {
-    // no packed column in this workgroup: independent loads, no branches
+  // (as in col_product: one loop for the columns other than the packed one)
+  if (!packed) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int qq = t + e * T;
@@ -1069,8 +1086,8 @@ __device__ __forceinline__ void col_products_adj(const cx<R>* fx, const cx<R>* f
       h[e] = spec_mul<R, TO, N, true>(fx[e], kind, tox, c, qq, half, (R)1, ph) +
              spec_mul<R, TO, N, true>(fy[e], kind, toy, c, qq, half, (R)-1, ph);
     }
-    return;
   }
+  if (!exch) return;
   // packed column: each spectrum U carries bins p = 0 and p = M; split both
   cx<R> umx[E], umy[E];
   {
@@ -1097,28 +1114,23 @@ __device__ __forceinline__ void col_products_adj(const cx<R>* fx, const cx<R>* f
     }
     __syncthreads();
   }
+  if (!packed) return;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int qq = t + e * T;
     const cx<R> w = kind == 1 ? r2n[(unsigned)qq] : cx<R>{(R)1, (R)0};
-    if (packed) {
-      const cx<R> ux = fx[e], uy = fy[e];
-      const cx<R> x0v{(R)0.5 * (ux.x + umx[e].x), (R)0.5 * (ux.y + umx[e].y)};
-      const cx<R> xmv{(R)0.5 * (ux.y - umx[e].y), (R)-0.5 * (ux.x - umx[e].x)};
-      const cx<R> y0v{(R)0.5 * (uy.x + umy[e].x), (R)0.5 * (uy.y + umy[e].y)};
-      const cx<R> ymv{(R)0.5 * (uy.y - umy[e].y), (R)-0.5 * (uy.x - umy[e].x)};
-      const cx<R> ph0 = half ? cmul(w, rho) : w;  // bins p = 0 and p = M (-i ph0)
-      const cx<R> phm{ph0.y, -ph0.x};
-      const cx<R> h0 = spec_mul<R, TO, N, true>(x0v, kind, tox, 0, qq, half, (R)1, ph0) +
-                       spec_mul<R, TO, N, true>(y0v, kind, toy, 0, qq, half, (R)-1, ph0);
-      const cx<R> hm = spec_mul<R, TO, N, true>(xmv, kind, tox, M, qq, half, (R)1, phm) +
-                       spec_mul<R, TO, N, true>(ymv, kind, toy, M, qq, half, (R)-1, phm);
-      h[e] = cx<R>{h0.x - hm.y, h0.y + hm.x};
-    } else {
-      const cx<R> ph = cmul(w, phh);
-      h[e] = spec_mul<R, TO, N, true>(fx[e], kind, tox, c, qq, half, (R)1, ph) +
-             spec_mul<R, TO, N, true>(fy[e], kind, toy, c, qq, half, (R)-1, ph);
-    }
+    const cx<R> ux = fx[e], uy = fy[e];
+    const cx<R> x0v{(R)0.5 * (ux.x + umx[e].x), (R)0.5 * (ux.y + umx[e].y)};
+    const cx<R> xmv{(R)0.5 * (ux.y - umx[e].y), (R)-0.5 * (ux.x - umx[e].x)};
+    const cx<R> y0v{(R)0.5 * (uy.x + umy[e].x), (R)0.5 * (uy.y + umy[e].y)};
+    const cx<R> ymv{(R)0.5 * (uy.y - umy[e].y), (R)-0.5 * (uy.x - umy[e].x)};
+    const cx<R> ph0 = half ? cmul(w, rho) : w;  // bins p = 0 and p = M (-i ph0)
+    const cx<R> phm{ph0.y, -ph0.x};
+    const cx<R> h0 = spec_mul<R, TO, N, true>(x0v, kind, tox, 0, qq, half, (R)1, ph0) +
+                     spec_mul<R, TO, N, true>(y0v, kind, toy, 0, qq, half, (R)-1, ph0);
+    const cx<R> hm = spec_mul<R, TO, N, true>(xmv, kind, tox, M, qq, half, (R)1, phm) +
+                     spec_mul<R, TO, N, true>(ymv, kind, toy, M, qq, half, (R)-1, phm);
+    h[e] = cx<R>{h0.x - hm.y, h0.y + hm.x};
   }
 }
 
@@ -1137,7 +1149,8 @@ __global__ void __launch_bounds__((col_cfg<R, N>::P * col_cfg<R, N>::T))
   }
   using C = col_cfg<R, N>;
   constexpr int E = C::E, T = C::T, LL = C::SLOT;
-  __shared__ cx<R> smem[C::P * LL];
+  extern __shared__ __align__(16) unsigned char sg_dyn_lds[];  // P * LL elements, sized at launch
+  cx<R>* const smem = reinterpret_cast<cx<R>*>(sg_dyn_lds);
   const int P = blockDim.x / T;
   const int g = threadIdx.x / T, t = threadIdx.x % T;
   const int c0 = xcd_tile(blockIdx.x, gridDim.x) * P, c = c0 + g;
@@ -1227,7 +1240,8 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, R, M>::G * rowfwd_cfg<R, R, M>:
   }
   using C = rowfwd_cfg<R, R, M>;
   constexpr int L = C::L, E = C::E, T = C::T, SLOT = C::SLOT;
-  __shared__ cx<R> smem[C::G * SLOT];
+  extern __shared__ __align__(16) unsigned char sg_dyn_lds[];  // G * SLOT elements, sized at launch
+  cx<R>* const smem = reinterpret_cast<cx<R>*>(sg_dyn_lds);
   const int G = blockDim.x / T;
   const int g = threadIdx.x / T, t = threadIdx.x % T;
   const int row = xcd_tile(blockIdx.x, gridDim.x) * G + g;
@@ -1523,37 +1537,69 @@ static void dyn_lds_optin(int max_bytes) {
   (void)once;
 }
 
-static inline int pick_tile(int tile, int cap, int n) {
-  int g = (tile > 0 && tile <= cap) ? tile : cap;
+// Rows per workgroup of the row passes where no tile is given: as many as the
+// kernel takes (longer pieces of the transposed arrays), but fewer while that
+// leaves fewer than `blocks` workgroups for the 256 compute units, down to a
+// whole wave (64 threads) or `least` rows.  FP64 inverse rows of 512, one grid: 32
+// workgroups of 16 rows 33 us, 256 of two rows 10 us; FP32 forward rows of 1024:
+// 64 workgroups 16.7 us, 256 of four rows 11.8 us.
+static inline int default_rows(int cap, int T, int n, int ngrids, int blocks, int least) {
+  int g = 1;
+  while (2 * g <= cap) g *= 2;
+  if ((int64_t)n * ngrids >= (int64_t)blocks * cap) return cap;
+  while (g > least && g * T > 64 && (int64_t)n * ngrids < (int64_t)blocks * g) g /= 2;
+  return g;
+}
+// Columns per workgroup of the Stockham column pass where no tile is given: one
+// wave's worth (its barriers then cost next to nothing), fewer while that
+// leaves fewer than 256 workgroups.  FP64 columns of 64, one grid: one workgroup
+// of 32 columns 15.5 us, 64 of one column 10.9 us.
+static inline int default_cols(int cap, int T, int M, int ngrids) {
+  int p = T >= 64 ? 1 : 64 / T;
+  if (p > cap) p = cap;
+  while (p > 1 && (int64_t)M * ngrids < (int64_t)256 * p) p /= 2;
+  return p;
+}
+// the tile asked for, if there is one within the compiled maximum, else the
+// default; at most n
+static inline int pick_tile(int tile, int cap, int n, int dflt) {
+  const int g = (tile > 0 && tile <= cap) ? tile : dflt;
   return g < n ? g : n;
 }
-
-// Workgroups of G rows that the first (or last) rows of a column within the
-// reach of order's padding values can fall in.
-static inline int pad_groups(int order, int G) { return (bnd_reach(order) + 2 * G - 2) / G; }
+template <typename R, int M>
+static int rows_fwd_tile(int tile, int nrows, int ngrids, bool parts) {
+  using C = rowfwd_cfg<R, R, M>;
+  // two rows: 16- or 32-byte pieces of X; whole groups where it leaves parts
+  const int g = pick_tile(tile, C::G, nrows, default_rows(C::G, C::T, nrows, ngrids, 256, 2));
+  return parts ? (g + C::GP - 1) / C::GP * C::GP : g;
+}
+template <typename R, int M, int VA>
+static int rows_inv_tile(int tile, int nrows, int ngrids) {
+  using C = rowinv_cfg<R, M, VA>;
+  return pick_tile(tile, C::G, nrows, default_rows(C::G, C::T, nrows, ngrids, 512, 1));
+}
 
 template <typename R, typename In, int M>
 static hipError_t launch_row_fwd_t(const In* src, int64_t src_ld, cx<R>* X, int nrows, const cx<R>* r2m,
                                    int solve, const double* bc, const double* bcn, int full, const cx<R>* tw,
                                    const sg_bgrid* bg, int ngrids, int tile, hipStream_t st) {
   using C = rowfwd_cfg<R, In, M>;
-  const int G = pick_tile(tile, C::G, nrows);
+  const int G = rows_fwd_tile<R, M>(tile, nrows, bg ? ngrids : 1, bcn != nullptr);
   const int blocks = (nrows + G - 1) / G;
-  const int pg = bcn ? pad_groups(solve, G) : 0;
   constexpr int row_bytes = C::SLOT * C::NB * (int)sizeof(cx<R>);
   dyn_lds_optin<&k_row_fwd<R, In, M>>(C::G * row_bytes);
   hipLaunchKernelGGL((k_row_fwd<R, In, M>), dim3(blocks, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st, src,
-                     src_ld, X, nrows, nrows, r2m, solve, bc, bcn, pg, full, tw, bg);
+                     src_ld, X, nrows, nrows, r2m, solve, bc, bcn, full, tw, bg);
   return hipGetLastError();
 }
 
 template <typename R, int N, int VA = 0>
 static hipError_t launch_col_t(const cx<R>* X, cx<R>* V, int M, int tj, const void* tx, const void* ty, int kind,
-                               const cx<R>* r2n, int solve, const double* bc, const cx<R>* tw, const sg_bgrid* bg, int ngrids,
+                               const cx<R>* r2n, int pg, const cx<R>* tw, const sg_bgrid* bg, int ngrids,
                                int tile, hipStream_t st) {
   using C = col_cfg<R, N, VA>;
   using TO = typename tabs<R>::odd;
-  const int P = pow2_div(M, (tile > 0 && tile <= C::P) ? tile : C::P);
+  const int P = pow2_div(M, pick_tile(tile, C::P, M, default_cols(C::P, C::T, M, bg ? ngrids : 1)));
   const dim3 grid(M / P, bg ? ngrids : 1);
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
@@ -1562,8 +1608,8 @@ static hipError_t launch_col_t(const cx<R>* X, cx<R>* V, int M, int tj, const vo
   auto go = [&](auto kd) {
     constexpr int KD = decltype(kd)::value;
     dyn_lds_optin<&k_col<R, TO, N, KD, VA>>(C::P * col_bytes);
-    hipLaunchKernelGGL((k_col<R, TO, N, KD, VA>), grid, dim3(P * C::T), lds, st, X, V, M, tj, tox, toy, r2n, solve, bc,
-                       tw, bg);
+    hipLaunchKernelGGL((k_col<R, TO, N, KD, VA>), grid, dim3(P * C::T), lds, st, X, V, M, tj, tox, toy, r2n,
+                       (const cx<R>*)nullptr, pg, tw, bg);
   };
   if (kind == 1)
     go(std::integral_constant<int, 1>{});
@@ -1576,10 +1622,12 @@ template <typename R, typename Out, int M, int VA = 0>
 static hipError_t launch_row_inv_t(const cx<R>* V, Out* fx, Out* fy, int nrows, int tj, const cx<R>* r2m,
                                    const cx<R>* tw, const sg_bgrid* bg, int ngrids, int tile, hipStream_t st) {
   using C = rowinv_cfg<R, M, VA>;
-  const int G = pick_tile(tile, C::G, nrows);
+  const int G = rows_inv_tile<R, M, VA>(tile, nrows, bg ? ngrids : 1);
   const int blocks = (nrows + G - 1) / G;
-  hipLaunchKernelGGL((k_row_inv<R, Out, M, VA>), dim3(blocks, bg ? ngrids : 1), dim3(G * C::T), 0, st, V, fx, fy, nrows,
-                     tj, r2m, tw, bg);
+  constexpr int row_bytes = rowinv_static<R, M, VA>() ? 0 : C::RS * (int)sizeof(cx<R>);
+  if (row_bytes > 0) dyn_lds_optin<&k_row_inv<R, Out, M, VA>>(C::G * row_bytes);
+  hipLaunchKernelGGL((k_row_inv<R, Out, M, VA>), dim3(blocks, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st, V, fx,
+                     fy, nrows, tj, r2m, tw, bg);
   return hipGetLastError();
 }
 
@@ -1636,15 +1684,15 @@ static hipError_t row_fwd_dispatch(int M, const In* src, int64_t ld, cx<R>* X, i
 #if SG_IN_PART(2)
 template <typename R>
 static hipError_t col_dispatch(int N, const cx<R>* X, cx<R>* V, int M, int tj, const void* tx, const void* ty,
-                               int kind, const cx<R>* r2n, int solve, const double* bc, const cx<R>* tw, const sg_bgrid* bg,
+                               int kind, const cx<R>* r2n, int pg, const cx<R>* tw, const sg_bgrid* bg,
                                int ngrids, int tile, int variant, hipStream_t st) {
   switch (N) {
 #define CASE(SZ)                                                                                        \
   case SZ:                                                                                              \
     if (sizeof(R) == 4 && variant == 1 && col_variants<SZ>())                                           \
-      return launch_col_t<R, SZ, col_variants<SZ>() ? 1 : 0>(X, V, M, tj, tx, ty, kind, r2n, solve, bc, tw, bg, \
+      return launch_col_t<R, SZ, col_variants<SZ>() ? 1 : 0>(X, V, M, tj, tx, ty, kind, r2n, pg, tw, bg, \
                                                               ngrids, tile, st);                        \
-    return launch_col_t<R, SZ>(X, V, M, tj, tx, ty, kind, r2n, solve, bc, tw, bg, ngrids, tile, st);
+    return launch_col_t<R, SZ>(X, V, M, tj, tx, ty, kind, r2n, pg, tw, bg, ngrids, tile, st);
     SG_SIZES(CASE)
 #undef CASE
     default:
@@ -1691,13 +1739,13 @@ hipError_t sg_launch_row_fwd(int prec, int M, const void* src, int64_t ld, void*
 
 #if SG_IN_PART(2)
 hipError_t sg_launch_col(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                         int kind, const void* r2n, int solve, const double* bc, const void* tw, const sg_bgrid* bg,
+                         int kind, const void* r2n, int pg, const void* tw, const sg_bgrid* bg,
                          int ngrids, int tile, int variant, hipStream_t st) {
   if (prec == 0)
     return col_dispatch<double>(N, (const cx<double>*)X, (cx<double>*)V, M, tj, tx, ty, kind,
-                                (const cx<double>*)r2n, solve, bc, (const cx<double>*)tw, bg, ngrids, tile, 0, st);
+                                (const cx<double>*)r2n, pg, (const cx<double>*)tw, bg, ngrids, tile, 0, st);
   return col_dispatch<float>(N, (const cx<float>*)X, (cx<float>*)V, M, tj, tx, ty, kind, (const cx<float>*)r2n,
-                             solve, bc, (const cx<float>*)tw, bg, ngrids, tile, variant, st);
+                             pg, (const cx<float>*)tw, bg, ngrids, tile, variant, st);
 }
 
 int sg_row_tile(int prec, int M, int N) {
@@ -1735,6 +1783,46 @@ static int max_tile_t(int pass, int len, int v) {
   }
 }
 
+template <typename R>
+static int tile_t(int pass, int len, int v, int lines, int ngrids, int tile, int parts) {
+  switch (len) {
+#define CASE(SZ)                                                                                                  \
+  case SZ:                                                                                                        \
+    if (pass == 0) return rows_fwd_tile<R, SZ>(tile, lines, ngrids, parts);                                              \
+    if (pass == 2) return v ? rows_inv_tile<R, SZ, 1>(tile, lines, ngrids) : rows_inv_tile<R, SZ, 0>(tile, lines, ngrids); \
+    if (SZ > 4096) return 1;                                                                                      \
+    if (v)                                                                                                        \
+      return pow2_div(lines, pick_tile(tile, col_cfg<R, SZ, 1>::P, lines,                                         \
+                                       default_cols(col_cfg<R, SZ, 1>::P, col_cfg<R, SZ, 1>::T, lines, ngrids))); \
+    return pow2_div(lines, pick_tile(tile, col_cfg<R, SZ>::P, lines,                                              \
+                                     default_cols(col_cfg<R, SZ>::P, col_cfg<R, SZ>::T, lines, ngrids)));
+    SG_ROW_SIZES(CASE)
+#undef CASE
+    default:
+      return 0;
+  }
+}
+template <typename R>
+static int pad_rows_t(int M) {
+  switch (M) {
+#define CASE(SZ) \
+  case SZ:       \
+    return rowfwd_cfg<R, R, SZ>::GP;
+    SG_ROW_SIZES(CASE)
+#undef CASE
+    default:
+      return 1;
+  }
+}
+int sg_pad_parts(int prec, int M, int N, int order) {
+  return bnd_parts(order, N, prec == 0 ? pad_rows_t<double>(M) : pad_rows_t<float>(M));
+}
+
+int sg_tile(int prec, int pass, int len, int variant, int lines, int ngrids, int tile, int parts) {
+  return prec == 0 ? tile_t<double>(pass, len, 0, lines, ngrids, tile, parts)
+                   : tile_t<float>(pass, len, variant, lines, ngrids, tile, parts);
+}
+
 int sg_variants(int prec, int pass, int len) {
   if (prec == 0) return 1;
   switch (len) {
@@ -1751,11 +1839,12 @@ int sg_variants(int prec, int pass, int len) {
 }
 
 int sg_default_variant(int prec, int pass, int len) {
-  return (prec == 1 && pass == 2 && len >= SG_RI_BIG32 && sg_variants(prec, pass, len) > 1) ? 1 : 0;
-}
-
-int sg_pad_groups(int prec, int M, int nrows, int tile, int order) {
-  return pad_groups(order, pick_tile(tile, sg_max_tile(prec, 0, M, 0), nrows));
+  if (prec != 1 || sg_variants(prec, pass, len) < 2) return 0;
+  // Stockham columns of 3 * 2^a: two exchange buffers, the table entries read
+  // where they are used (four of 12 elements held 96 registers of them: columns of
+  // 384, one grid, 25.7 us against 18.6)
+  if (pass == 1) return len % 3 == 0 ? 1 : 0;
+  return len >= SG_RI_BIG32 ? 1 : 0;
 }
 
 int sg_max_tile(int prec, int pass, int len, int variant) {
@@ -1897,15 +1986,16 @@ static hipError_t launch_col_adj_t(const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y, i
                                    const sg_bgrid* bg, int ngrids, hipStream_t st) {
   using C = col_cfg<R, N>;
   using TO = typename tabs<R>::odd;
-  const int P = pow2_div(M, C::P);
+  const int P = pow2_div(M, pick_tile(0, C::P, M, default_cols(C::P, C::T, M, bg ? ngrids : 1)));
   const dim3 grid(M / P, bg ? ngrids : 1);
+  const int lds = P * C::SLOT * (int)sizeof(cx<R>);
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
   if (kind == 1)
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 1>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
+    hipLaunchKernelGGL((k_col_adj<R, TO, N, 1>), grid, dim3(P * C::T), lds, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
                        bc, tw, bg);
   else
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 0>), grid, dim3(P * C::T), 0, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
+    hipLaunchKernelGGL((k_col_adj<R, TO, N, 0>), grid, dim3(P * C::T), lds, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
                        bc, tw, bg);
   return hipGetLastError();
 }
@@ -1915,9 +2005,11 @@ static hipError_t launch_row_c2r_t(const cx<R>* Y, R* out, int nrows, int tj, co
                                    const double* bc,
                                    const cx<R>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   using C = rowfwd_cfg<R, R, M>;
-  const int G = C::G < nrows ? C::G : nrows;
-  hipLaunchKernelGGL((k_row_c2r<R, R, M>), dim3((nrows + G - 1) / G, bg ? ngrids : 1), dim3(G * C::T), 0, st, Y, out,
-                     nrows, tj, r2m, solve, bc, tw, bg);
+  const int G = rows_fwd_tile<R, M>(0, nrows, bg ? ngrids : 1, false);
+  constexpr int row_bytes = C::SLOT * (int)sizeof(cx<R>);
+  dyn_lds_optin<&k_row_c2r<R, R, M>>(C::G * row_bytes);
+  hipLaunchKernelGGL((k_row_c2r<R, R, M>), dim3((nrows + G - 1) / G, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st,
+                     Y, out, nrows, tj, r2m, solve, bc, tw, bg);
   return hipGetLastError();
 }
 

@@ -46,6 +46,18 @@ def _symbol(k, N):
     return np.concatenate([sym[0:N + 1:2], sym[1:N:2]])
 
 
+def _padding(k, N):
+    """The padding values' coefficients c0, c1 (48 each) of order k's system on lines of N values."""
+    bc = np.zeros((2, 48))
+    if k >= 3:
+        st, n = cr.STENCIL[k], min(N, 300)
+        h, m = len(st) // 2, {3: 24, 4: 32, 5: 42}[k]
+        G = np.linalg.inv(sum(np.diag([st[h + d]] * (n - abs(d)), d) for d in range(-h, h + 1)))
+        bc[0, :m] = 76 * G[0, :m] + G[1, :m] if k == 5 else G[0, :m]
+        bc[1, :m] = G[0, :m] if k == 5 else 0
+    return bc
+
+
 @pytest.mark.parametrize("N,k,to", CASES, ids=[f"{c[0]}-k{c[1]}-{c[2]}" for c in CASES])
 def test_column_pass(tmp_path, N, k, to):
     exe = _build(tmp_path, N, k, to, 0)
@@ -53,17 +65,10 @@ def test_column_pass(tmp_path, N, k, to):
     rng = np.random.default_rng(k * 17 + N)
     X = rng.standard_normal((M, N)) + 1j * rng.standard_normal((M, N))
     tx, ty, stored = fs._tables(rng, M, N, to)
-    xb = np.zeros((M, 4), complex)
     if k >= 3:  # the kernel's tables hold the system's symbol along y; the reference solves the system
-        st, sym = cr.STENCIL[k], _symbol(k, N)
-        tx, ty = (t * sym for t in (tx, ty))
-        # and takes the system's values in slots N, N + 1, -1, -2: of the coefficients C = y / sum(st) (integer stencil)
-        Xs = X.astype(np.complex64).astype(complex)
-        C = np.stack([cr.band_solve(k, x.real) + 1j * cr.band_solve(k, x.imag) for x in Xs]) / sum(st)
-        if k == 5:
-            xb = np.stack([76 * C[:, -1] + C[:, -2], C[:, -1], 76 * C[:, 0] + C[:, 1], C[:, 0]], 1)
-        else:
-            xb[:, 0], xb[:, 2] = C[:, -1], C[:, 0]
+        tx, ty = (t * _symbol(k, N) for t in (tx, ty))
+    bc = _padding(k, N)
+    xb = np.stack([X[:, ::-1][:, :48] @ bc[0], X[:, ::-1][:, :48] @ bc[1], X[:, :48] @ bc[0], X[:, :48] @ bc[1]], 1)
     fin, fout = str(tmp_path / "in.bin"), str(tmp_path / "out.bin")
     with open(fin, "wb") as f:
         X.astype(np.complex64).tofile(f)
@@ -90,16 +95,8 @@ def test_adjoint_column_pass(tmp_path, N, k, to):
     rng = np.random.default_rng(k * 19 + N)
     Xx, Xy = (rng.standard_normal((M, N)) + 1j * rng.standard_normal((M, N)) for _ in range(2))
     tx, ty, stored = fs._tables(rng, M, N, to)
-    bc = np.zeros((2, 48))
     if k >= 3:  # the kernel's tables hold the symbol; the reference solves the system
         tx, ty = (t * _symbol(k, N) for t in (tx, ty))
-        st = cr.STENCIL[k]
-        h = len(st) // 2
-        A = sum(np.diag([st[h + d]] * (300 - abs(d)), d) for d in range(-h, h + 1))
-        G = np.linalg.inv(A)
-        m = {3: 24, 4: 32, 5: 42}[k]
-        bc[0, :m] = 76 * G[0, :m] + G[1, :m] if k == 5 else G[0, :m]
-        bc[1, :m] = G[0, :m] if k == 5 else 0
     fin, fout = str(tmp_path / "in.bin"), str(tmp_path / "out.bin")
     with open(fin, "wb") as f:
         Xx.astype(np.complex64).tofile(f)
@@ -107,7 +104,7 @@ def test_adjoint_column_pass(tmp_path, N, k, to):
         for t in stored:
             t.tofile(f)
         np.exp(-1j * np.pi * np.arange(2 * N) / N).astype(np.complex64).tofile(f)
-        bc.tofile(f)
+        _padding(k, N).tofile(f)
     races = fs._run(exe, M, fin, fout)
     tj = int(np.fromfile(fout, dtype=np.int32, count=1)[0])
     Y = cr.untile_half(np.fromfile(fout, dtype=np.complex64, offset=4), M, N, tj)
