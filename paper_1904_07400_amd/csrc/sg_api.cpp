@@ -1205,8 +1205,9 @@ sg_status sg_bspline_coeffs(sg_plan p, const void* sigma, void* coeffs) {
     char* dst = (char*)coeffs + el * G.off;
     hipError_t e = hipSuccess;
     if (G.k >= 3) {
-      e = sg_launch_coeff_rows(prec, G.M, src, dst, G.N, G.k, p->st);
-      if (e == hipSuccess) e = sg_launch_coeff_cols(prec, G.N, dst, G.M, G.k, p->st);
+      // by way of the grid's spectra buffer (the column pass is not in place)
+      e = sg_launch_coeff_rows(prec, G.M, src, G.X, G.N, G.k, p->st);
+      if (e == hipSuccess) e = sg_launch_coeff_cols(prec, G.N, G.X, dst, G.M, G.k, p->st);
     } else if (src != dst) {
       e = hipMemcpyAsync(dst, src, el * (size_t)G.M * G.N, hipMemcpyDeviceToDevice, p->st);
     }

@@ -1421,7 +1421,7 @@ __global__ void k_check_finite(const In* __restrict__ x, int64_t n, int* __restr
 // ------------------------------------------------- coefficients (C out) --
 // sigma -> C for k = 3, 4, 5 written out (sg_bspline_coeffs): the x-solve along
 // rows (Eq. (C_system)) then the y-solve along columns (Eq. (z_system));
-// the two commute.  The per-step force path fuses them into passes A and B.
+// the two commute.  (The force path has both systems in its spectra: bnd.hpp.)
 template <int M>
 struct coeff_cfg {
   static constexpr int CH = elems_for(M, 16, 12);
@@ -1458,46 +1458,93 @@ __global__ void __launch_bounds__((coeff_cfg<M>::G * coeff_cfg<M>::T))
   }
 }
 
-template <int N>
-struct coeffc_cfg {
-  static constexpr int CH = elems_for(N, 16, 12);
-  static constexpr int T = N / CH;
-  static constexpr int P = T >= 64 ? 1 : 64 / T;
-  static constexpr int TRI = band_smem<double, T>::BYTES / 8 + 1;
-  static constexpr int SLOT = (N + 1) > TRI ? (N + 1) : TRI;
+// The column solve: the LDL^T factors of the band matrix (pivots and multipliers
+// reach their limits, to rounding, within kBndLen rows) applied as recursions down
+// and up the column, one thread per column so that a wave reads and writes pieces
+// of 64 columns.  A thread does kCoeffRows rows; its recursions start bnd_reach
+// rows before and after them, where what it leaves out has decayed below 1e-18.
+// (One column per workgroup, read at the row stride, was bound by partial lines:
+// 89 us at 2048^2, FP32, for 32 MB; this one 11.)  Fully unrolled, the rows in registers; the
+// 2.5 to 3.6 reads per value come from the caches.
+constexpr int kCoeffRows = 32;
+struct band_ldl {
+  double l1[kBndLen], l2[kBndLen], id[kBndLen];  // multipliers of rows i - 1, i - 2; scale / pivot
 };
+__host__ __device__ constexpr band_ldl make_ldl(int k) {
+  const double a0 = k == 5 ? 230.0 : (k == 4 ? 4.0 : 6.0), a1 = k == 5 ? 76.0 : 1.0, a2 = k == 5 ? 1.0 : 0.0;
+  band_ldl f{};
+  double d1 = 1.0, d2 = 1.0, m1 = 0.0;  // pivots of rows i - 1, i - 2; l1 of row i - 1
+  for (int i = 0; i < kBndLen; ++i) {
+    const double l2 = i >= 2 ? a2 / d2 : 0.0, l1 = i >= 1 ? (a1 - l2 * d2 * m1) / d1 : 0.0;
+    const double d = a0 - l1 * l1 * d1 - l2 * l2 * d2;
+    f.l1[i] = l1;
+    f.l2[i] = l2;
+    f.id[i] = band_scale(k) / d;
+    d2 = d1;
+    d1 = d;
+    m1 = l1;
+  }
+  return f;
+}
+static __constant__ const band_ldl kLdl[3] = {make_ldl(3), make_ldl(4), make_ldl(5)};
 
-template <typename R, int N>
-__global__ void __launch_bounds__((coeffc_cfg<N>::P * coeffc_cfg<N>::T))
-    k_coeff_cols(R* __restrict__ data, int M, int sys) {
-  using C = coeffc_cfg<N>;
-  constexpr int CH = C::CH, T = C::T, SLOT = C::SLOT;
-  __shared__ double smem[C::P * SLOT];
-  const int P = blockDim.x / T;
-  const int g = threadIdx.x / T, t = threadIdx.x % T;
-  const int c0 = blockIdx.x * P;
-  for (int s = 0; s < CH; ++s) {
-    const int l = threadIdx.x + s * P * T;
-    smem[(l % P) * SLOT + l / P] = (double)data[(int64_t)(l / P) * M + c0 + l % P];
-  }
-  __syncthreads();
-  double d[CH];
+// one chunk of a column from row i0; EDGE: it or its margins meet an end of the
+// column or rows whose factors are not yet at their limits
+template <int K, bool EDGE, typename R>
+__device__ __forceinline__ void coeff_chunk(const R* __restrict__ s, R* __restrict__ o, int n, int M, int i0) {
+  constexpr int H = bnd_reach(K), B = kCoeffRows;
+  const band_ldl& f = kLdl[K - 3];
+  const double c1 = f.l1[kBndLen - 1], c2 = f.l2[kBndLen - 1], cd = f.id[kBndLen - 1];
+  auto at = [&](int i) { return i < kBndLen ? (i < 0 ? 0 : i) : kBndLen - 1; };
+  double z[B + H], y1 = 0.0, y2 = 0.0;
 #pragma unroll
-  for (int e = 0; e < CH; ++e) d[e] = band_scale(sys) * smem[g * SLOT + t * CH + e];
-  __syncthreads();
-  if (sys == 3)
-    band_solve<3, CH, T>(d, t, smem + g * SLOT);
-  else if (sys == 4)
-    band_solve<4, CH, T>(d, t, smem + g * SLOT);
+  for (int q = 0; q < B + 2 * H; ++q) {
+    const int i = i0 - H + q;
+    double v, l1 = c1, l2 = c2, id = cd;
+    if constexpr (EDGE) {
+      const int r = i < 0 ? 0 : (i < n ? i : n - 1);
+      v = (double)s[(int64_t)r * M];
+      v = i < 0 ? 0.0 : v;
+      l1 = f.l1[at(i)];
+      l2 = f.l2[at(i)];
+      id = f.id[at(i)];
+    } else {
+      v = (double)s[(int64_t)i * M];
+    }
+    double y = v - l1 * y1;
+    if constexpr (K == 5) y -= l2 * y2;
+    if (q >= H) {
+      z[q - H] = y * id;
+      if constexpr (EDGE) z[q - H] = i < n ? z[q - H] : 0.0;
+    }
+    y2 = y1;
+    y1 = y;
+  }
+  double x1 = 0.0, x2 = 0.0;
+#pragma unroll
+  for (int q = B + H - 1; q >= 0; --q) {
+    const int i = i0 + q;
+    const double l1 = EDGE ? f.l1[at(i + 1)] : c1, l2 = EDGE ? f.l2[at(i + 2)] : c2;
+    double x = z[q] - l1 * x1;
+    if constexpr (K == 5) x -= l2 * x2;
+    if (q < B && (!EDGE || i < n)) o[(int64_t)i * M] = (R)x;
+    x2 = x1;
+    x1 = x;
+  }
+}
+
+// 64 columns by (blockDim / 64) chunks per workgroup; src and dst do not overlap
+template <typename R, int K>
+__global__ void __launch_bounds__(256) k_coeff_cols(const R* __restrict__ src, R* __restrict__ dst, int n, int M) {
+  const int nc = (M + 63) / 64, tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int c = tile % nc * 64 + threadIdx.x % 64;
+  const int i0 = __builtin_amdgcn_readfirstlane((int)(tile / nc * (blockDim.x / 64) + threadIdx.x / 64)) * kCoeffRows;
+  if (c >= M || i0 >= n) return;
+  constexpr int H = bnd_reach(K);
+  if (i0 - H < kBndLen || i0 + kCoeffRows + H + 2 > n)
+    coeff_chunk<K, true>(src + c, dst + c, n, M, i0);
   else
-    band_solve<5, CH, T>(d, t, smem + g * SLOT);
-#pragma unroll
-  for (int e = 0; e < CH; ++e) smem[g * SLOT + t * CH + e] = d[e];
-  __syncthreads();
-  for (int s = 0; s < CH; ++s) {
-    const int l = threadIdx.x + s * P * T;
-    data[(int64_t)(l / P) * M + c0 + l % P] = (R)smem[(l % P) * SLOT + l / P];
-  }
+    coeff_chunk<K, false>(src + c, dst + c, n, M, i0);
 }
 
 // ------------------------------------------------------------ launches --
@@ -1898,20 +1945,16 @@ static hipError_t coeff_rows_dispatch(int M, const R* src, R* dst, int nrows, in
 }
 
 template <typename R>
-static hipError_t coeff_cols_dispatch(int N, R* data, int M, int sys, hipStream_t st) {
-  switch (N) {
-#define CASE(SZ)                                                                                      \
-  case SZ: {                                                                                          \
-    using C = coeffc_cfg<SZ>;                                                                         \
-    const int P = pow2_div(M, C::P);                                                               \
-    hipLaunchKernelGGL((k_coeff_cols<R, SZ>), dim3(M / P), dim3(P * C::T), 0, st, data, M, sys);      \
-    return hipGetLastError();                                                                        \
-  }
-    SG_ROW_SIZES(CASE)
-#undef CASE
-    default:
-      return hipErrorInvalidValue;
-  }
+static hipError_t coeff_cols_dispatch(int N, const R* src, R* dst, int M, int k, hipStream_t st) {
+  const int chunks = (N + kCoeffRows - 1) / kCoeffRows, w = chunks < 4 ? chunks : 4;
+  const dim3 grid((M + 63) / 64 * ((chunks + w - 1) / w)), blk(64 * w);
+  if (k == 3)
+    hipLaunchKernelGGL((k_coeff_cols<R, 3>), grid, blk, 0, st, src, dst, N, M);
+  else if (k == 4)
+    hipLaunchKernelGGL((k_coeff_cols<R, 4>), grid, blk, 0, st, src, dst, N, M);
+  else
+    hipLaunchKernelGGL((k_coeff_cols<R, 5>), grid, blk, 0, st, src, dst, N, M);
+  return hipGetLastError();
 }
 
 hipError_t sg_launch_coeff_rows(int prec, int M, const void* src, void* dst, int nrows, int k, hipStream_t st) {
@@ -1920,10 +1963,10 @@ hipError_t sg_launch_coeff_rows(int prec, int M, const void* src, void* dst, int
   return coeff_rows_dispatch<float>(M, (const float*)src, (float*)dst, nrows, k, st);
 }
 
-hipError_t sg_launch_coeff_cols(int prec, int N, void* data, int M, int k, hipStream_t st) {
+hipError_t sg_launch_coeff_cols(int prec, int N, const void* src, void* dst, int M, int k, hipStream_t st) {
   if (k < 3 || k > 5) return hipErrorInvalidValue;
-  if (prec == 0) return coeff_cols_dispatch<double>(N, (double*)data, M, k, st);
-  return coeff_cols_dispatch<float>(N, (float*)data, M, k, st);
+  if (prec == 0) return coeff_cols_dispatch<double>(N, (const double*)src, (double*)dst, M, k, st);
+  return coeff_cols_dispatch<float>(N, (const float*)src, (float*)dst, M, k, st);
 }
 
 // ------------------------------------------------- stage twiddle tables --
