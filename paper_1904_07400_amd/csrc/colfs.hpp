@@ -140,7 +140,8 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
                                            const TO* __restrict__ tox, const TO* __restrict__ toy,
                                            const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
                                            const sg_bgrid* __restrict__ bg, cx<R>* smem,
-                                           const cx<R>* __restrict__ xb, int pg) {
+                                           const cx<R>* __restrict__ xb, int pg, int x_tiled) {
+  const int xt = N == 8192 ? x_tiled : 0;
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
   constexpr bool solve = MODE >= 2;
   constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);
@@ -172,9 +173,9 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
   // ---- loads of a column: the column (chunk of E per thread for the solve,
   // else D1); the spectrum-table entries of this thread's D3 bins
   auto load_col = [&](int t, int cc, cx<R> (&aa)[E]) {
-    const cx<R>* col = X + (int64_t)cc * N;
+    const cx<R>* col = X + x_base(cc, N, M, xt);
 #pragma unroll
-    for (int e = 0; e < E; ++e) aa[e] = col[(unsigned)(solve ? t * E + e : S::d1_index(t, e))];
+    for (int e = 0; e < E; ++e) aa[e] = col[(unsigned)x_at(solve ? t * E + e : S::d1_index(t, e), xt)];
   };
   auto load_tab = [&](int t, int cc, TO (&tt)[pre ? NT : 1][pre ? E : 1]) {
     if constexpr (pre) {
@@ -476,9 +477,9 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS, int COMP, 
 __global__ void __launch_bounds__(N / E) SG_WAVES_PER_EU(colfs_wpe<R, N>::value)
     k_colfs(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
             const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-            const sg_bgrid* __restrict__ bg, const cx<R>* __restrict__ xb = nullptr, int pg = 0) {
+            const sg_bgrid* __restrict__ bg, const cx<R>* __restrict__ xb = nullptr, int pg = 0, int xt = 0) {
   __shared__ cx<R> smem[colfs_cfg<R, N, E, SLOTS>::LDS];
-  colfs_body<R, TO, N, MODE, E, SLOTS, COMP, PF>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg);
+  colfs_body<R, TO, N, MODE, E, SLOTS, COMP, PF>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg, xt);
 }
 
 // Both force components of a column in one launch: the x pass (Yx into
@@ -489,11 +490,11 @@ template <typename R, typename TO, int N, int MODE, int E, int SLOTS>
 __global__ void __launch_bounds__(N / E) SG_WAVES_PER_EU(colfs_wpe<R, N>::value)
     k_colfs_xy(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
                const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
-               const sg_bgrid* __restrict__ bg, const cx<R>* __restrict__ xb = nullptr, int pg = 0) {
+               const sg_bgrid* __restrict__ bg, const cx<R>* __restrict__ xb = nullptr, int pg = 0, int xt = 0) {
   __shared__ cx<R> smem[colfs_cfg<R, N, E, SLOTS>::LDS];
-  colfs_body<R, TO, N, MODE, E, SLOTS, 1, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg);
+  colfs_body<R, TO, N, MODE, E, SLOTS, 1, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg, xt);
   __syncthreads();
-  colfs_body<R, TO, N, MODE, E, SLOTS, 2, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg);
+  colfs_body<R, TO, N, MODE, E, SLOTS, 2, false, true>(X, V, M, tj, tox, toy, r2n, twfs, bg, smem, xb, pg, xt);
 }
 
 // Plan-time spectrum columns of the long columns (FP64): column c of the
@@ -595,7 +596,8 @@ __global__ void __launch_bounds__(N / E)
     k_colfs_adj(const cx<R>* __restrict__ Xx, const cx<R>* __restrict__ Xy, cx<R>* __restrict__ Y, int M, int tj,
                 const TO* __restrict__ tox, const TO* __restrict__ toy, const cx<R>* __restrict__ r2n,
                 const cx<R>* __restrict__ twfs, const sg_bgrid* __restrict__ bg, int bord = 0,
-                const double* __restrict__ bc = nullptr) {
+                const double* __restrict__ bc = nullptr, int x_tiled = 0) {
+  const int xt = N == 8192 ? x_tiled : 0;
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
   constexpr bool solve = MODE >= 2;
   constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);
@@ -616,8 +618,8 @@ __global__ void __launch_bounds__(N / E)
   const bool packed = (c == 0);
   fs_tw<N, E, R, false> tw;
   tw.init(twfs, t);
-  const cx<R>* colx = Xx + (int64_t)c * N;
-  const cx<R>* coly = Xy + (int64_t)c * N;
+  const cx<R>* colx = Xx + x_base(c, N, M, xt);
+  const cx<R>* coly = Xy + x_base(c, N, M, xt);
   const TO* rowx = tox + (int64_t)c * (N + 1);
   const TO* rowy = toy + (int64_t)c * (N + 1);
   constexpr R ex = kind == 1 ? (R)-1 : (R)1;  // reflection sign of the x table (y: -ex)
@@ -634,8 +636,8 @@ __global__ void __launch_bounds__(N / E)
     for (int e = 0; e < E; ++e) {
       const int j = S::d1_index(tl, e);
       const cx<R> w = h ? r2n[(unsigned)opaque(j)] : cx<R>{(R)1, (R)0};
-      fx[e] = cmul(colx[(unsigned)j], w);
-      fy[e] = cmul(coly[(unsigned)j], w);
+      fx[e] = cmul(colx[(unsigned)x_at(j, xt)], w);
+      fy[e] = cmul(coly[(unsigned)x_at(j, xt)], w);
     }
     if constexpr (SLOTS == 2) {
       cx<R> f2[2][E];

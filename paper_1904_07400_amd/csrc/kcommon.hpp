@@ -60,4 +60,14 @@ __device__ __forceinline__ sg_bgrid grid_desc(const sg_bgrid* bg) {
   return d;
 }
 
+// The row spectra X: bin p of row j at x_base(p) + x_at(j), column-major, or (xt)
+// in tiles of two bins of one parity by four rows, so that four rows leave pass A
+// in whole 64-byte pieces (n rows of m bins).
+__device__ __forceinline__ int64_t x_base(int p, int n, int m, int xt) {
+  if (!xt) return (int64_t)p * n;
+  const int q = p >> 1;
+  return (int64_t)((p & 1) * (m / 2) + (q & ~1)) * n + (q & 1) * 4;
+}
+__device__ __forceinline__ int x_at(int j, int xt) { return xt ? (j >> 2) * 8 + (j & 3) : j; }
+
 }  // namespace sg

@@ -95,7 +95,7 @@ static hipError_t launch_colfs_m(const cx<R>* X, cx<R>* V, int M, int tj, const 
   if constexpr (Sel::SPLIT && SG_COLFS_XY && sizeof(R) == 4) {
     // both component passes of a column in one launch
     hipLaunchKernelGGL((k_colfs_xy<R, TO, N, MODE, Sel::E, Sel::SLOTS>), dim3(M, bg ? ngrids : 1), dim3(N / Sel::E),
-                       0, st, X, V, M, tj, tox, toy, r2n, tw, bg, (const cx<R>*)nullptr, pg);
+                       0, st, X, V, M, tj, tox, toy, r2n, tw, bg, (const cx<R>*)nullptr, pg, sg_x_tiled(1, M, N));
   } else if constexpr (Sel::SPLIT) {
     launch_colfs_k<R, TO, N, MODE, 1>(X, V, M, tj, tox, toy, r2n, pg, tw, bg, ngrids, st);
     launch_colfs_k<R, TO, N, MODE, 2>(X, V, M, tj, tox, toy, r2n, pg, tw, bg, ngrids, st);
@@ -301,7 +301,7 @@ static hipError_t launch_colfs_adj_m(const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y,
                                      int ngrids, int bord, const double* bc, hipStream_t st) {
   using Sel = colfs_adj_sel<R, N>;
   hipLaunchKernelGGL((k_colfs_adj<R, TO, N, MODE, Sel::E, Sel::SLOTS>), dim3(M, bg ? ngrids : 1), dim3(N / Sel::E), 0,
-                     st, Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, bord, bc);
+                     st, Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, bord, bc, sg_x_tiled(sizeof(R) == 4, M, N));
   return hipGetLastError();
 }
 

@@ -41,6 +41,8 @@ int sg_variants(int prec, int pass, int len);
 int sg_default_variant(int prec, int pass, int len);
 // largest tile (rows or columns per workgroup) of a pass in a variant
 int sg_max_tile(int prec, int pass, int len, int variant);
+// whether a grid's row spectra X are tiled (x_base in kcommon.hpp)
+int sg_x_tiled(int prec, int M, int N);
 // parts per padding value that pass A leaves for a grid of N rows of M
 int sg_pad_parts(int prec, int M, int N, int order);
 // rows (passes 0, 2) or columns (1) per workgroup that a launch over ngrids grids

@@ -117,6 +117,15 @@
 #ifndef SG_RF_E64
 #define SG_RF_E64 8
 #endif
+// FP32 forward rows from this length on: 16 elements per thread and one exchange
+// buffer per row, the even bins from load to store and then the odd ones, so that a
+// workgroup of 1024 threads holds four rows of 8192 in place of two (555 us at 8192^2,
+// 1.2 GB of writes for 0.54; now 335, with the tiles of x_base).  Shorter rows have
+// four or more either way, and lose as much to the one buffer (rows of 4096: 88 us,
+// 82 to 97 this way)
+#ifndef SG_RF_BIG32
+#define SG_RF_BIG32 8192
+#endif
 // elements per thread for transform lengths 3 * 2^a (a multiple of 3)
 #ifndef SG_E3
 #define SG_E3 12
@@ -375,12 +384,13 @@ constexpr int kLdsBudget = 144 * 1024;
 template <typename R, typename In, int M>
 struct rowfwd_cfg {
   static constexpr int L = M / 2;
-  static constexpr int E0 = sizeof(R) == 4 ? SG_RF_E32 : SG_RF_E64;
+  static constexpr bool BIG = sizeof(R) == 4 && M >= SG_RF_BIG32 && M % 3 != 0;
+  static constexpr int E0 = sizeof(R) == 4 ? (BIG ? 16 : SG_RF_E32) : SG_RF_E64;
   static constexpr int E = elems_for(L, E0, SG_E3);
   static constexpr int T = L / E;
   static constexpr int LL = lds_len<L>::value;
   static constexpr int SLOT = LL;  // per-row LDS slot (complex elements)
-  static constexpr int NB = (sizeof(R) == 4 && sizeof(In) == 4) ? SG_RF_NBUF32 : 1;  // exchange buffers per row
+  static constexpr int NB = (sizeof(R) == 4 && sizeof(In) == 4 && !BIG) ? SG_RF_NBUF32 : 1;  // exchange buffers per row
   // rows per workgroup: more rows make longer segments of the transposed store
   static constexpr int WG = sizeof(R) == 4 ? SG_RF_THREADS32 : SG_RF_THREADS64;
   static constexpr int G0 = WG / T < 1 ? 1 : (WG / T < 16 ? WG / T : 16);
@@ -390,6 +400,8 @@ struct rowfwd_cfg {
   // them per workgroup
   static constexpr int GP = G1 >= 4 ? 4 : (G1 >= 2 ? 2 : 1);
   static constexpr int G = G1 / GP * GP;
+  // two workgroups per CU where the LDS holds them
+  static constexpr int WPE = BIG ? 4 : 1;
   // e-values per transposed-store chunk (2T bins per e, G rows)
   static constexpr int EC = (SLOT / (2 * T)) < 1 ? 1 : ((SLOT / (2 * T)) > E ? E : SLOT / (2 * T));
 };
@@ -404,10 +416,10 @@ struct rowfwd_cfg {
 // pass.)
 template <typename R, typename In, int M>
 __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M>::T))
-    SG_WPE(R, RF)
+    __attribute__((amdgpu_waves_per_eu(rowfwd_cfg<R, In, M>::WPE)))
     k_row_fwd(const In* __restrict__ src, int64_t src_ld, cx<R>* __restrict__ X, int ldx, int nrows,
               const cx<R>* __restrict__ r2m, int solve, const double* __restrict__ bc,
-              const double* __restrict__ bcn, int full, const cx<R>* __restrict__ tw,
+              const double* __restrict__ bcn, int full, int xt, const cx<R>* __restrict__ tw,
               const sg_bgrid* __restrict__ bg) {
   cx<R>* xb = nullptr;
   if (bg) {  // batched: grid blockIdx.y of the class
@@ -444,6 +456,98 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   // behind a branch each
   const In* s = src + (int64_t)(active ? row : 0) * src_ld;
   const R m1 = active ? (R)1 : (R)0;
+  // the parts that the nb bins b0 + bs pl in the transposed store's LDS give:
+  // group q's of values v beyond the end and the start of the columns
+  auto parts = [&](int b0, int bs, int nb, bool skw) {
+    for (int i = threadIdx.x; i < nb * G / GP; i += blockDim.x) {
+      const int pl = i / (G / GP), q = i % (G / GP) * GP;
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        const int at = (side ? row0 + q : nrows - GP - row0 - q) / GP;
+        if (at >= pg || row0 + q >= nrows) continue;
+        double s0x = 0.0, s0y = 0.0, s1x = 0.0, s1y = 0.0;
+#pragma unroll
+        for (int gg = 0; gg < GP; ++gg) {
+          const cx<R> z = smem[skw ? pad(pl * G + q + gg) : pl * G + q + gg];
+          s0x += pw[0][side][q + gg] * (double)z.x;
+          s0y += pw[0][side][q + gg] * (double)z.y;
+          s1x += pw[1][side][q + gg] * (double)z.x;
+          s1y += pw[1][side][q + gg] * (double)z.y;
+        }
+        cx<R>* o = xb + ((int64_t)(b0 + bs * pl) * 4 + 2 * side) * pg + at;
+        o[0] = cx<R>{(R)s0x, (R)s0y};
+        o[pg] = cx<R>{(R)s1x, (R)s1y};
+      }
+    }
+  };
+  if constexpr (C::BIG) {
+    // the even bins from load to store, then the odd ones (of the same input in
+    // registers): one exchange buffer, half the registers
+    cx<R> z[E], pv{(R)0, (R)0};  // pv: the row's padding values at its first or last element
+#pragma unroll
+    for (int e = 0; e < E; ++e) z[e] = cx<R>{m1 * (R)s[2 * (t + e * T)], m1 * (R)s[2 * (t + e * T) + 1]};
+    if (solve) {
+      double v[2];
+      if (t == 0) {
+        bnd_sums<M>([&](int i) { return (double)s[M - 1 - i]; }, solve, bc, v);
+        pv = cx<R>{m1 * (R)v[0], m1 * (R)v[1]};
+      }
+      if (t == T - 1) {
+        bnd_sums<M>([&](int i) { return (double)s[i]; }, solve, bc, v);
+        pv = cx<R>{m1 * (R)v[1], m1 * (R)v[0]};
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      // opaque per step, so that its indices are not held across the others
+      int ts = opaque(t);
+      cx<R> a[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        a[e] = z[e];
+        if (e == 0 && t == 0) a[e] = h ? a[e] - pv : a[e] + pv;
+        if (e == E - 1 && t == T - 1) a[e] = h ? a[e] - pv : a[e] + pv;
+        if (h) a[e] = cmul(a[e], root_at(r2m, r2m[2 * ts], 2 * ts, 2 * e * T));  // w_M^n
+      }
+      fft<false, L, T>(a, lds, tw, opaque(t));
+      ts = opaque(t);
+#pragma unroll
+      for (int e = 0; e < E; ++e) lds[pad(ts + e * T)] = a[e];
+      __syncthreads();
+      ts = opaque(t);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int pp = ts + e * T;  // X bin p = 2 pp + h
+        const cx<R> zp = a[e], zm = conj(lds[pad(h ? L - 1 - pp : (pp == 0 ? 0 : L - pp))]);
+        const cx<R> sum = zp + zm, dif = cmul(root_at(r2m, r2m[2 * ts + h], 2 * ts + h, 2 * e * T), zp - zm);
+        a[e] = cx<R>{(R)0.5 * (sum.x + dif.y), (R)0.5 * (sum.y - dif.x)};
+        if (h == 0 && pp == 0) a[e] = cx<R>{zp.x + zp.y, zp.x - zp.y};
+      }
+      __syncthreads();
+      ts = opaque(t);
+      constexpr bool SKW = SG_RF_SKEW && (L + (L + 31) / 32 <= SLOT);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = (ts + e * T) * G + g;
+        smem[SKW ? pad(i) : i] = a[e];
+      }
+      __syncthreads();
+      if (xt && G % 4 == 0) {
+        // tiles of two bins by four rows
+        for (int idx = threadIdx.x; idx < L * G; idx += blockDim.x) {
+          const int jj = idx & 3, p2 = (idx >> 2) & 1, quad = (idx >> 3) % (G / 4), grp = (idx >> 3) / (G / 4);
+          const int pl = 2 * grp + p2, gg = 4 * quad + jj, i = pl * G + gg;
+          if (row0 + gg < nrows) X[x_base(2 * pl + h, ldx, M, 1) + x_at(row0 + gg, 1)] = smem[SKW ? pad(i) : i];
+        }
+      } else for (int idx = threadIdx.x; idx < L * G; idx += blockDim.x) {
+        const int pl = idx / G, gg = idx % G;
+        if (row0 + gg < nrows) X[x_base(2 * pl + h, ldx, M, xt) + x_at(row0 + gg, xt)] = smem[SKW ? pad(idx) : idx];
+      }
+      if (edge) parts(h, 2, L, SKW);
+      __syncthreads();
+    }
+    return;
+  }
   cx<R> ze[E], zo[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) {
@@ -545,29 +649,7 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
       const int pl = idx / G, gg = idx % G;
       if (row0 + gg < nrows) X[(int64_t)(2 * e0 * T + pl) * ldx + row0 + gg] = smem[SKW ? pad(idx) : idx];
     }
-    if (edge) {
-      // group q's part of values v beyond the end and the start of the columns
-      for (int i = threadIdx.x; i < nchunk / GP; i += blockDim.x) {
-        const int pl = i / (G / GP), q = i % (G / GP) * GP;
-#pragma unroll
-        for (int side = 0; side < 2; ++side) {
-          const int at = (side ? row0 + q : nrows - GP - row0 - q) / GP;
-          if (at >= pg || row0 + q >= nrows) continue;
-          double s0x = 0.0, s0y = 0.0, s1x = 0.0, s1y = 0.0;
-#pragma unroll
-          for (int gg = 0; gg < GP; ++gg) {
-            const cx<R> z = smem[SKW ? pad(pl * G + q + gg) : pl * G + q + gg];
-            s0x += pw[0][side][q + gg] * (double)z.x;
-            s0y += pw[0][side][q + gg] * (double)z.y;
-            s1x += pw[1][side][q + gg] * (double)z.x;
-            s1y += pw[1][side][q + gg] * (double)z.y;
-          }
-          cx<R>* o = xb + ((int64_t)(2 * e0 * T + pl) * 4 + 2 * side) * pg + at;
-          o[0] = cx<R>{(R)s0x, (R)s0y};
-          o[pg] = cx<R>{(R)s1x, (R)s1y};
-        }
-      }
-    }
+    if (edge) parts(2 * e0 * T, 1, nchunk / G, SKW);
     __syncthreads();
   }
 }
@@ -1230,7 +1312,7 @@ __global__ void __launch_bounds__((col_cfg<R, N>::P * col_cfg<R, N>::T))
 // with the padding values' share of k >= 3 added at the row's ends (bnd.hpp).
 template <typename R, typename Out, int M>
 __global__ void __launch_bounds__((rowfwd_cfg<R, R, M>::G * rowfwd_cfg<R, R, M>::T))
-    k_row_c2r(const cx<R>* __restrict__ Y, Out* __restrict__ out, int nrows, int tj, const cx<R>* __restrict__ r2m,
+    __attribute__((amdgpu_waves_per_eu(rowfwd_cfg<R, R, M>::WPE))) k_row_c2r(const cx<R>* __restrict__ Y, Out* __restrict__ out, int nrows, int tj, const cx<R>* __restrict__ r2m,
               int solve, const double* __restrict__ bc, const cx<R>* __restrict__ tw,
               const sg_bgrid* __restrict__ bg) {
   if (bg) {  // batched: packed spectra in the second half of V
@@ -1251,33 +1333,48 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, R, M>::G * rowfwd_cfg<R, R, M>:
   // bin p of this row: tile half p&1, index p>>1
   const cx<R>* b0 = Y + ((int64_t)jb * 2) * L * tj + jj;
   const cx<R>* b1 = Y + ((int64_t)jb * 2 + 1) * L * tj + jj;
+  // with many elements per thread each step takes the thread index through an
+  // opaque move, so that its indices are not held across the others
+  auto step = [&] { return C::BIG ? opaque(t) : t; };
   cx<R> ze[E], zo[E];
+  const int t0 = step();
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const int pp = t + e * T;
+    const int pp = t0 + e * T;
     // Z'[p] = (X[p] + conj X[M-p]) + i conj(w_2M^p) (X[p] - conj X[M-p]), X[M] packed in slot 0
     const cx<R> xe = b0[(int64_t)pp * tj];                       // X[2pp]
-    const cx<R> xo = b1[(int64_t)pp * tj];                       // X[2pp+1]
     cx<R> me = conj(b0[(int64_t)(pp == 0 ? 0 : L - pp) * tj]);   // conj X[M - 2pp]
-    const cx<R> mo = conj(b1[(int64_t)(L - 1 - pp) * tj]);       // conj X[M - 2pp - 1]
     if (pp == 0) {
       const cx<R> x0 = xe;  // (X_0, X_M)
       ze[e] = cx<R>{x0.x + x0.y, x0.x - x0.y};
     } else {
-      const cx<R> sum = xe + me, dif = cmulc(xe - me, root_at(r2m, r2m[2 * t], 2 * t, 2 * e * T));
+      const cx<R> sum = xe + me, dif = cmulc(xe - me, root_at(r2m, r2m[2 * t0], 2 * t0, 2 * e * T));
       ze[e] = cx<R>{sum.x - dif.y, sum.y + dif.x};
     }
-    const cx<R> sum = xo + mo, dif = cmulc(xo - mo, root_at(r2m, r2m[2 * t + 1], 2 * t + 1, 2 * e * T));
-    zo[e] = cx<R>{sum.x - dif.y, sum.y + dif.x};
   }
-  fft<true, L, T>(ze, lds, tw, t);
-  fft<true, L, T>(zo, lds, tw, t);
+  // the odd bins: loaded with the even ones, where the registers hold both
+  auto odd = [&] {
+    const int t1 = step();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int pp = t1 + e * T;
+      const cx<R> xo = b1[(int64_t)pp * tj];                  // X[2pp+1]
+      const cx<R> mo = conj(b1[(int64_t)(L - 1 - pp) * tj]);  // conj X[M - 2pp - 1]
+      const cx<R> sum = xo + mo, dif = cmulc(xo - mo, root_at(r2m, r2m[2 * t1 + 1], 2 * t1 + 1, 2 * e * T));
+      zo[e] = cx<R>{sum.x - dif.y, sum.y + dif.x};
+    }
+  };
+  if constexpr (!C::BIG) odd();
+  fft<true, L, T>(ze, lds, tw, step());
+  if constexpr (C::BIG) odd();
+  fft<true, L, T>(zo, lds, tw, step());
+  const int t2 = step();
   // z[n'] = ze + exp(2 pi i n'/M) zo, n' < M/2: x[2n'] = Re z, x[2n'+1] = Im
   // z; z[n' + M/2] is the difference
   cx<R> past{(R)0, (R)0}, before{(R)0, (R)0};  // x[M], x[M + 1] (thread 0); x[2M - 2], x[2M - 1] (thread T - 1)
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const cx<R> o = cmulc(zo[e], root_at(r2m, r2m[2 * t], 2 * t, 2 * e * T));
+    const cx<R> o = cmulc(zo[e], root_at(r2m, r2m[2 * t2], 2 * t2, 2 * e * T));
     if (e == 0) past = ze[e] - o;
     if (e == E - 1) before = ze[e] - o;
     ze[e] = ze[e] + o;
@@ -1304,7 +1401,7 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, R, M>::G * rowfwd_cfg<R, R, M>:
   if (active) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const int n = t + e * T;
+      const int n = t2 + e * T;
       out[(int64_t)row * M + 2 * n] = (Out)ze[e].x;
       out[(int64_t)row * M + 2 * n + 1] = (Out)ze[e].y;
     }
@@ -1631,12 +1728,14 @@ static hipError_t launch_row_fwd_t(const In* src, int64_t src_ld, cx<R>* X, int 
                                    int solve, const double* bc, const double* bcn, int full, const cx<R>* tw,
                                    const sg_bgrid* bg, int ngrids, int tile, hipStream_t st) {
   using C = rowfwd_cfg<R, In, M>;
+  if (C::BIG && full) return hipErrorInvalidValue;  // plan time is FP64
   const int G = rows_fwd_tile<R, M>(tile, nrows, bg ? ngrids : 1, bcn != nullptr);
   const int blocks = (nrows + G - 1) / G;
   constexpr int row_bytes = C::SLOT * C::NB * (int)sizeof(cx<R>);
   dyn_lds_optin<&k_row_fwd<R, In, M>>(C::G * row_bytes);
   hipLaunchKernelGGL((k_row_fwd<R, In, M>), dim3(blocks, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st, src,
-                     src_ld, X, nrows, nrows, r2m, solve, bc, bcn, full, tw, bg);
+                     src_ld, X, nrows, nrows, r2m, solve, bc, bcn, full,
+                     bg ? sg_x_tiled(sizeof(R) == 4, M, nrows) : 0, tw, bg);
   return hipGetLastError();
 }
 
@@ -1861,6 +1960,11 @@ static int pad_rows_t(int M) {
       return 1;
   }
 }
+// Rows of the long form leave pass A four at a time; the columns of 8192 read the
+// tiles at no cost forward, 5 % adjoint (columns of 4096: pass A 88 -> 80 us, pass B
+// as much slower, so they stay column-major)
+int sg_x_tiled(int prec, int M, int N) { return prec == 1 && N == 8192 && M >= SG_RF_BIG32 && M % 3 != 0; }
+
 int sg_pad_parts(int prec, int M, int N, int order) {
   return bnd_parts(order, N, prec == 0 ? pad_rows_t<double>(M) : pad_rows_t<float>(M));
 }
@@ -2048,7 +2152,10 @@ static hipError_t launch_row_c2r_t(const cx<R>* Y, R* out, int nrows, int tj, co
                                    const double* bc,
                                    const cx<R>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   using C = rowfwd_cfg<R, R, M>;
-  const int G = rows_fwd_tile<R, M>(0, nrows, bg ? ngrids : 1, false);
+  // the long rows at most 512 threads: two workgroups per CU (8192 rows of 8192:
+  // 402 us, one of 1024 threads 437)
+  const int G0 = rows_fwd_tile<R, M>(0, nrows, bg ? ngrids : 1, false);
+  const int G = C::BIG && G0 * C::T > 512 ? 512 / C::T : G0;
   constexpr int row_bytes = C::SLOT * (int)sizeof(cx<R>);
   dyn_lds_optin<&k_row_c2r<R, R, M>>(C::G * row_bytes);
   hipLaunchKernelGGL((k_row_c2r<R, R, M>), dim3((nrows + G - 1) / G, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st,
