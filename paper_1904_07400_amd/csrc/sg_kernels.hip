@@ -390,6 +390,7 @@ struct rowfwd_cfg {
   static constexpr int T = L / E;
   static constexpr int LL = lds_len<L>::value;
   static constexpr int SLOT = LL;  // per-row LDS slot (complex elements)
+  static constexpr int RS = SLOT + 8;  // that of k_row_c2r: the rows' slots start in different banks
   static constexpr int NB = (sizeof(R) == 4 && sizeof(In) == 4 && !BIG) ? SG_RF_NBUF32 : 1;  // exchange buffers per row
   // rows per workgroup: more rows make longer segments of the transposed store
   static constexpr int WG = sizeof(R) == 4 ? SG_RF_THREADS32 : SG_RF_THREADS64;
@@ -1321,14 +1322,17 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, R, M>::G * rowfwd_cfg<R, R, M>:
     out += d.off;
   }
   using C = rowfwd_cfg<R, R, M>;
-  constexpr int L = C::L, E = C::E, T = C::T, SLOT = C::SLOT;
-  extern __shared__ __align__(16) unsigned char sg_dyn_lds[];  // G * SLOT elements, sized at launch
+  constexpr int L = C::L, E = C::E, T = C::T;
+  extern __shared__ __align__(16) unsigned char sg_dyn_lds[];  // G * RS elements, sized at launch
   cx<R>* const smem = reinterpret_cast<cx<R>*>(sg_dyn_lds);
   const int G = blockDim.x / T;
-  const int g = threadIdx.x / T, t = threadIdx.x % T;
+  // FP32 rows interleaved lane by lane, as in k_row_inv (8192^2: 402 -> 377 us;
+  // FP64, tiles of two rows, 10.8 -> 12.7 at 1024^2, so not there)
+  constexpr bool ILV = sizeof(R) == 4;
+  const int g = ILV ? threadIdx.x % G : threadIdx.x / T, t = ILV ? threadIdx.x / G : threadIdx.x % T;
   const int row = xcd_tile(blockIdx.x, gridDim.x) * G + g;
   const bool active = row < nrows;
-  cx<R>* lds = smem + g * SLOT;
+  cx<R>* lds = smem + g * C::RS;
   const int jb = (active ? row : 0) / tj, jj = (active ? row : 0) % tj;
   // bin p of this row: tile half p&1, index p>>1
   const cx<R>* b0 = Y + ((int64_t)jb * 2) * L * tj + jj;
@@ -2153,10 +2157,10 @@ static hipError_t launch_row_c2r_t(const cx<R>* Y, R* out, int nrows, int tj, co
                                    const cx<R>* tw, const sg_bgrid* bg, int ngrids, hipStream_t st) {
   using C = rowfwd_cfg<R, R, M>;
   // the long rows at most 512 threads: two workgroups per CU (8192 rows of 8192:
-  // 402 us, one of 1024 threads 437)
+  // 402 us against 437 with one of 1024 threads)
   const int G0 = rows_fwd_tile<R, M>(0, nrows, bg ? ngrids : 1, false);
   const int G = C::BIG && G0 * C::T > 512 ? 512 / C::T : G0;
-  constexpr int row_bytes = C::SLOT * (int)sizeof(cx<R>);
+  constexpr int row_bytes = C::RS * (int)sizeof(cx<R>);
   dyn_lds_optin<&k_row_c2r<R, R, M>>(C::G * row_bytes);
   hipLaunchKernelGGL((k_row_c2r<R, R, M>), dim3((nrows + G - 1) / G, bg ? ngrids : 1), dim3(G * C::T), G * row_bytes, st,
                      Y, out, nrows, tj, r2m, solve, bc, tw, bg);
