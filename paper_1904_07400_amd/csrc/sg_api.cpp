@@ -1205,9 +1205,10 @@ sg_status sg_bspline_coeffs(sg_plan p, const void* sigma, void* coeffs) {
     char* dst = (char*)coeffs + el * G.off;
     hipError_t e = hipSuccess;
     if (G.k >= 3) {
-      // by way of the grid's spectra buffer (the column pass is not in place)
-      e = sg_launch_coeff_rows(prec, G.M, src, G.X, G.N, G.k, p->st);
-      if (e == hipSuccess) e = sg_launch_coeff_cols(prec, G.N, G.X, dst, G.M, G.k, p->st);
+      // long columns, whose pass is not in place, by way of the grid's spectra buffer
+      void* mid = G.N < kCoeffLong ? (void*)dst : G.X;
+      e = sg_launch_coeff_rows(prec, G.M, src, mid, G.N, G.k, p->st);
+      if (e == hipSuccess) e = sg_launch_coeff_cols(prec, G.N, mid, dst, G.M, G.k, p->st);
     } else if (src != dst) {
       e = hipMemcpyAsync(dst, src, el * (size_t)G.M * G.N, hipMemcpyDeviceToDevice, p->st);
     }

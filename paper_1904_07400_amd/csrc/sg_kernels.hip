@@ -1559,13 +1559,58 @@ __global__ void __launch_bounds__((coeff_cfg<M>::G * coeff_cfg<M>::T))
   }
 }
 
-// The column solve: the LDL^T factors of the band matrix (pivots and multipliers
+// The column solve of columns below kCoeffLong, in place: P columns per workgroup.
+template <int N>
+struct coeffc_cfg {
+  static constexpr int CH = elems_for(N, 16, 12);
+  static constexpr int T = N / CH;
+  static constexpr int P = T >= 64 ? 1 : 64 / T;
+  static constexpr int TRI = band_smem<double, T>::BYTES / 8 + 1;
+  static constexpr int SLOT = (N + 1) > TRI ? (N + 1) : TRI;
+};
+
+template <typename R, int N>
+__global__ void __launch_bounds__((coeffc_cfg<N>::P * coeffc_cfg<N>::T))
+    k_coeff_cols(R* __restrict__ data, int M, int sys) {
+  using C = coeffc_cfg<N>;
+  constexpr int CH = C::CH, T = C::T, SLOT = C::SLOT;
+  __shared__ double smem[C::P * SLOT];
+  const int P = blockDim.x / T;
+  const int g = threadIdx.x / T, t = threadIdx.x % T;
+  const int c0 = blockIdx.x * P;
+  for (int s = 0; s < CH; ++s) {
+    const int l = threadIdx.x + s * P * T;
+    smem[(l % P) * SLOT + l / P] = (double)data[(int64_t)(l / P) * M + c0 + l % P];
+  }
+  __syncthreads();
+  double d[CH];
+#pragma unroll
+  for (int e = 0; e < CH; ++e) d[e] = band_scale(sys) * smem[g * SLOT + t * CH + e];
+  __syncthreads();
+  if (sys == 3)
+    band_solve<3, CH, T>(d, t, smem + g * SLOT);
+  else if (sys == 4)
+    band_solve<4, CH, T>(d, t, smem + g * SLOT);
+  else
+    band_solve<5, CH, T>(d, t, smem + g * SLOT);
+#pragma unroll
+  for (int e = 0; e < CH; ++e) smem[g * SLOT + t * CH + e] = d[e];
+  __syncthreads();
+  for (int s = 0; s < CH; ++s) {
+    const int l = threadIdx.x + s * P * T;
+    data[(int64_t)(l / P) * M + c0 + l % P] = (R)smem[(l % P) * SLOT + l / P];
+  }
+}
+
+// The column solve of long columns: the LDL^T factors of the band matrix (pivots and multipliers
 // reach their limits, to rounding, within kBndLen rows) applied as recursions down
 // and up the column, one thread per column so that a wave reads and writes pieces
 // of 64 columns.  A thread does kCoeffRows rows; its recursions start bnd_reach
 // rows before and after them, where what it leaves out has decayed below 1e-18.
 // (One column per workgroup, read at the row stride, was bound by partial lines:
-// 89 us at 2048^2, FP32, for 32 MB; this one 11.)  Fully unrolled, the rows in registers; the
+// 89 us at 2048^2, FP32, for 32 MB; this one 11.  The line lies where the chunks'
+// serial rows stop being the longer ones: both systems k = 3, 5 at 1024^2 FP32 13.6,
+// 20.3 us against 27.0, 28.8, at 512^2 11.5, 18.2 against 11.4, 13.3.)  Fully unrolled, the rows in registers; the
 // 2.5 to 3.6 reads per value come from the caches.
 constexpr int kCoeffRows = 32;
 struct band_ldl {
@@ -1636,7 +1681,7 @@ __device__ __forceinline__ void coeff_chunk(const R* __restrict__ s, R* __restri
 
 // 64 columns by (blockDim / 64) chunks per workgroup; src and dst do not overlap
 template <typename R, int K>
-__global__ void __launch_bounds__(256) k_coeff_cols(const R* __restrict__ src, R* __restrict__ dst, int n, int M) {
+__global__ void __launch_bounds__(256) k_coeff_cols_long(const R* __restrict__ src, R* __restrict__ dst, int n, int M) {
   const int nc = (M + 63) / 64, tile = xcd_tile(blockIdx.x, gridDim.x);
   const int c = tile % nc * 64 + threadIdx.x % 64;
   const int i0 = __builtin_amdgcn_readfirstlane((int)(tile / nc * (blockDim.x / 64) + threadIdx.x / 64)) * kCoeffRows;
@@ -2053,15 +2098,35 @@ static hipError_t coeff_rows_dispatch(int M, const R* src, R* dst, int nrows, in
 }
 
 template <typename R>
+static hipError_t coeff_cols_short(int N, R* data, int M, int sys, hipStream_t st) {
+  switch (N) {
+#define CASE(SZ)                                                                                       \
+  case SZ:                                                                                             \
+    if constexpr (SZ < kCoeffLong) {                                                                   \
+      using C = coeffc_cfg<SZ>;                                                                        \
+      const int P = pow2_div(M, C::P);                                                                 \
+      hipLaunchKernelGGL((k_coeff_cols<R, SZ>), dim3(M / P), dim3(P * C::T), 0, st, data, M, sys);     \
+      return hipGetLastError();                                                                        \
+    }                                                                                                  \
+    return hipErrorInvalidValue;
+    SG_SIZES(CASE)
+#undef CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+
+template <typename R>
 static hipError_t coeff_cols_dispatch(int N, const R* src, R* dst, int M, int k, hipStream_t st) {
+  if (N < kCoeffLong) return src == dst ? coeff_cols_short<R>(N, dst, M, k, st) : hipErrorInvalidValue;
   const int chunks = (N + kCoeffRows - 1) / kCoeffRows, w = chunks < 4 ? chunks : 4;
   const dim3 grid((M + 63) / 64 * ((chunks + w - 1) / w)), blk(64 * w);
   if (k == 3)
-    hipLaunchKernelGGL((k_coeff_cols<R, 3>), grid, blk, 0, st, src, dst, N, M);
+    hipLaunchKernelGGL((k_coeff_cols_long<R, 3>), grid, blk, 0, st, src, dst, N, M);
   else if (k == 4)
-    hipLaunchKernelGGL((k_coeff_cols<R, 4>), grid, blk, 0, st, src, dst, N, M);
+    hipLaunchKernelGGL((k_coeff_cols_long<R, 4>), grid, blk, 0, st, src, dst, N, M);
   else
-    hipLaunchKernelGGL((k_coeff_cols<R, 5>), grid, blk, 0, st, src, dst, N, M);
+    hipLaunchKernelGGL((k_coeff_cols_long<R, 5>), grid, blk, 0, st, src, dst, N, M);
   return hipGetLastError();
 }
 

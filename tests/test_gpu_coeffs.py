@@ -1,6 +1,6 @@
-"""GPU tests of the written-out spline coefficients at the edges of the column
-solve's chunks of 32 rows and their margins (24, 32, 42 rows), of its tiles of 64
-columns, and in place, on noise against the oracle.  Bars: 1e-13 of the largest
+"""GPU tests of the written-out spline coefficients on both sides of the column
+solve's line (1024 rows; from there on chunks of 32 rows with margins, tiles of 64
+columns) and in place, on noise against the oracle.  Bars: 1e-13 of the largest
 value (FP64; the systems amplify by at most 23), 1e-6 for single floats (two
 roundings of 6e-8, the first amplified by at most 4.8)."""
 import numpy as np
@@ -11,7 +11,7 @@ from gpu_util import to_dev
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(4, 4), (12, 32), (24, 48), (64, 64), (96, 96), (128, 128), (48, 192), (192, 256), (16, 2048)]
+SIZES = [(4, 4), (64, 64), (48, 768), (4, 1024), (96, 1024), (64, 1536), (24, 2048), (192, 2048)]
 
 
 @pytest.mark.parametrize("k", [3, 4, 5])
