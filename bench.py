@@ -84,7 +84,7 @@ KERNEL_SOURCES = ["paper_1904_07400_amd/csrc/sg_kernels.hip", "paper_1904_07400_
 # per-step kernels of the three passes (pass B: the four-step column kernel
 # for columns of 2048, 4096 and 8192, its radix-3 form for 1536, the
 # Stockham kernel otherwise)
-PASS_KERNELS = r"k_(row_fwd|colfs3|colfs|col|row_inv)<"
+PASS_KERNELS = r"k_(row_fwd|colfs3|colfs|colw|col|row_inv)<"
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "forces_4096_k3_fp32_traffic.md")
 
 
@@ -196,7 +196,7 @@ def batch_trace_summary(trace_csv, per_step):
     launches per step (three per class)."""
     import csv
     import re
-    step_kernel = re.compile(r"sg::k_(row_fwd|row_inv|col|colfs|colfs3)<float")
+    step_kernel = re.compile(r"sg::k_(row_fwd|row_inv|col|colfs|colfs3|colw)<float")
     rows = sorted((r for r in csv.DictReader(open(trace_csv)) if step_kernel.search(r["Kernel_Name"])),
                   key=lambda r: int(r["Start_Timestamp"]))
     home = rows[0]["Stream_Id"]
@@ -625,7 +625,7 @@ def main():
     dom = max(range(3), key=lambda i: pass32[i])
     name = "ABC"[dom]
     achieved = bpc[name] * cells / (pass32[dom] * 1e-3) / 1e9
-    kname = {"A": "k_row_fwd", "B": "k_colfs" if n in (4096, 8192) else "k_col", "C": "k_row_inv"}[name]
+    kname = {"A": "k_row_fwd", "B": {4096: "k_colw", 8192: "k_colfs_xy", 2048: "k_colfs"}.get(n, "k_col"), "C": "k_row_inv"}[name]
     step_gbs = sum(bpc.values()) * cells / (ms32 * 1e-3) / 1e9
     roofline = {"bound": "hbm", "kernel": kname,
                 "byte_model": "algorithmic (read X 8, weight spectra 4 + 4, write V 16 B/cell for pass B; "
