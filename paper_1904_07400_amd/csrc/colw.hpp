@@ -38,8 +38,10 @@ struct cw_shape {
   static constexpr int P = T >= 64 ? 1 : 64 / T;  // columns per workgroup
   static_assert(N >= 256 && N <= 4096 && (N & (N - 1)) == 0, "16 x 16 x R3, R3 <= 16");
   static_assert(ROW >= 16 * STR && N + N / 16 <= SLOT, "LDS slot");
-  // twiddle table: w_N^(t k1) at k1 T + t, then w_T^(t0 k2) at N + k2 R3 + t0
-  static constexpr int TW_SIZE = N + T;
+  // twiddle table: w_N^(t k1) at k1 T + t, then w_T^(t0 k2) at N + k2 R3 + t0, then
+  // (even k) w_2N^q' of the bins q' = d3_base(u) at N + T + u and d3_base(u) +
+  // 15 D3_SPAN at N + 2 T + u
+  static constexpr int TW_SIZE = N + 3 * T;
   // output order of the forward transform: thread u, register r holds bin
   // d3_base(u) + d3_off(r)
   static constexpr int D3_SPAN = 16 * R3;
@@ -269,6 +271,13 @@ __device__ __forceinline__ void cw_inv(cx<R> (&v)[NA][16], cx<R>* lds, const TW&
   }
 }
 
+// Single-float entries of both halves and both twiddle sets fit the registers;
+// hi + lo pairs are read where they are used, the first set as well.
+template <typename TO>
+struct cw_keep {
+  static constexpr bool on = sizeof(TO) == 4;
+};
+
 // exp(-2 pi i e / 32), e < 16
 template <typename R>
 __host__ __device__ constexpr cx<R> cw_w32(int e) {
@@ -278,48 +287,48 @@ __host__ __device__ constexpr cx<R> cw_w32(int e) {
   return e <= 8 ? cx<R>{(R)c[e], (R)-c[8 - e]} : cx<R>{(R)-c[16 - e], (R)-c[e - 8]};
 }
 
-// Single-float entries of both halves and both twiddle sets fit the registers;
-// hi + lo pairs are read where they are used, the first set as well.
-template <typename TO>
-struct cw_keep {
-  static constexpr bool on = sizeof(TO) == 4;
-};
-
 // Even k: the bin phases exp(-i pi (c/2M + q/2N)) (CJ: their conjugates) onto
-// one half's bins db + D3_SPAN H, w the phase of bin db: D3_SPAN / 2N = 1 / 32, so
-// each is w times a constant.
+// one half's bins d3_base(u) + D3_SPAN H.  D3_SPAN / 2N = 1 / 32, so each is a constant
+// times the phase w0 of H = 0 (H < 8) or w15 of H = 15, whichever is nearer in
+// frequency: the bins next to zero on either side, which hold most of a smooth
+// density, get the product of the column's and the bin's phase and no more (all
+// from w0: 9 % more error at 4096^2, k = 2).
 template <int N, bool CJ, typename R>
-__device__ __forceinline__ void cw_phase(cx<R> (&a)[16], cx<R> w) {
+__device__ __forceinline__ void cw_phase(cx<R> (&a)[16], cx<R> w0, cx<R> w15) {
   using S = cw_shape<N>;
 #pragma unroll
   for (int H = 0; H < 16; ++H) {
-    const cx<R> p = cmul(w, cw_w32<R>(H));
+    const cx<R> p = H < 8 ? cmul(w0, cw_w32<R>(H)) : cmulc(w15, cw_w32<R>(15 - H));
     cx<R>& z = a[S::d3_reg(H)];
     z = CJ ? cmulc(z, p) : cmul(z, p);
   }
 }
-// the phase of bin db of half h in column c
-template <int N, typename R>
-__device__ __forceinline__ cx<R> cw_phase0(const cx<R>* __restrict__ r2n, int c, int M, int db, int h) {
-  const cx<R> w = cmul(r2n[(unsigned)db], fs_half_phase<R>((double)c / (2.0 * M)));
-  return h ? cmul(w, fs_half_phase<R>(1.0 / (2.0 * N))) : w;
+// exp(-i pi c / 2M), c < M, of the column: the Taylor sums of sine and cosine on
+// [0, pi/2) in FP64 to 1e-10, rounded once (the library's sincospi, once per column,
+// takes 28 us of the forward and 41 of the adjoint pass at 4096^2).
+template <typename R>
+__device__ __forceinline__ cx<R> cw_phase_col(int c, int M) {
+  const double a = (double)c * (1.57079632679489661923 / M), z = -a * a;
+  double cs = 1.0, sn = 1.0;
+#pragma unroll
+  for (int n = 16; n >= 2; n -= 2) {  // sum of z^(n/2) / n!, of z^(n/2) / (n + 1)!
+    cs = 1.0 + z * (1.0 / (n * (n - 1))) * cs;
+    sn = 1.0 + z * (1.0 / (n * (n + 1))) * sn;
+  }
+  return {(R)cs, (R)(-a * sn)};
 }
 
 // One column (or, T < 64, the P columns of one wave).  exch: this workgroup
-// holds the packed column 0.  t: this thread within its column c, w2t:
-// w_2N^t, lds: the column's two slots.
+// holds the packed column 0.  t: this thread within its column c, lds: the
+// column's two slots.
 template <typename R, typename TO, int N, int kind, typename TW>
 __device__ __forceinline__ void cw_column(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj,
                                           const TO* __restrict__ tox, const TO* __restrict__ toy,
-                                          const cx<R>* __restrict__ r2n, const TW& tw, cx<R> w2t, cx<R>* lds, int c,
+                                          const cx<R>* __restrict__ r2n, const TW& tw, cx<R>* lds, int c,
                                           int t, bool exch, const cx<R>* __restrict__ xb, int pg) {
   using S = cw_shape<N>;
   constexpr int T = S::T, SL = S::SLOT;
   constexpr bool PRE = cw_keep<TO>::on;
-  // opaque(): this column's products of the constant w_2N^t stay here instead
-  // of being held in registers from one column to the next
-  SG_OPAQUE(w2t.x);
-  SG_OPAQUE(w2t.y);
   const bool packed = c == 0;
   const cx<R>* col = X + (int64_t)c * N;
   cx<R> f[2][16];
@@ -333,30 +342,40 @@ __device__ __forceinline__ void cw_column(const cx<R>* __restrict__ X, cx<R>* __
     cw_load_tab<N>(tox + p * S::TAB, t, h, e[0]);
     cw_load_tab<N>(toy + p * S::TAB, t, h, e[1]);
   };
-  // w_2N^(t + T e): T / 2N = 1 / 32, so w_2N^t times a constant
-  auto w2n_at = [&](int e) -> cx<R> { return cmul(w2t, cw_w32<R>(e)); };
   TO tv[2][16];
   if constexpr (PRE) load_tab(c, 0, tv);
 
   SG_CW_FENCE();
   // ---- forward: even and odd bins of the zero-padded column
+  {
+    // w_2N^(t + T e), loaded per column (opaque(): not held from one to the next)
+    const int tw2 = opaque(t);
+    auto w2n_at = [&](int e) -> cx<R> { return r2n[(unsigned)(tw2 + T * e)]; };
 #pragma unroll
-  for (int e = 0; e < 16; ++e) f[1][e] = cmul(f[0][e], w2n_at(e));
-  if (xb) {
-    // onto elements 0, 1 (threads 0, 1) and N - 1, N - 2 (the last two)
-    if (t < 2) {
-      f[0][0] = f[0][0] + xv;
-      f[1][0] = f[1][0] - cmul(xv, w2n_at(0));
-    } else {  // zero but in the last two
-      f[0][15] = f[0][15] + xv;
-      f[1][15] = f[1][15] - cmul(xv, w2n_at(15));
+    for (int e = 0; e < 16; ++e) f[1][e] = cmul(f[0][e], w2n_at(e));
+    if (xb) {
+      // onto elements 0, 1 (threads 0, 1) and N - 1, N - 2 (the last two)
+      if (t < 2) {
+        f[0][0] = f[0][0] + xv;
+        f[1][0] = f[1][0] - cmul(xv, w2n_at(0));
+      } else {  // zero but in the last two
+        f[0][15] = f[0][15] + xv;
+        f[1][15] = f[1][15] - cmul(xv, w2n_at(15));
+      }
     }
   }
   cw_fwd<N, 2>(f, lds, tw, false, t);
   SG_CW_FENCE();
   if constexpr (kind == 1) {
-    cw_phase<N, false>(f[0], cw_phase0<N>(r2n, c, M, db, 0));
-    cw_phase<N, false>(f[1], cw_phase0<N>(r2n, c, M, db, 1));
+    // this thread's roots of the bin phases
+    const int tp = opaque(N + T + t);
+    const cx<R> wc = cw_phase_col<R>(c, M);
+    const cx<R> ph0 = tw.tab[(unsigned)tp], ph15 = tw.tab[(unsigned)(tp + T)];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const cx<R> w = h ? cmul(wc, fs_half_phase<R>(1.0 / (2.0 * N))) : wc;
+      cw_phase<N, false>(f[h], cmul(ph0, w), cmul(ph15, w));
+    }
   }
 
   // ---- one half at a time: the products of both components and their
@@ -418,11 +437,13 @@ __device__ __forceinline__ void cw_column(const cx<R>* __restrict__ X, cx<R>* __
         acc[1][e] = gg[1][e];
       }
     } else {
-      SG_OPAQUE(w2t.x);
-      SG_OPAQUE(w2t.y);
+      // w_2N^(t + T e): loaded for even k; for odd k (T / 2N = 1 / 32) w_2N^t times a
+      // constant
+      const int tw2 = opaque(t);
+      const cx<R> wb = r2n[(unsigned)tw2];
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const cx<R> w = w2n_at(e);
+        const cx<R> w = kind == 1 ? r2n[(unsigned)(tw2 + T * e)] : cmul(wb, cw_w32<R>(e));
 #pragma unroll
         for (int comp = 0; comp < 2; ++comp) {  // as multiply-adds onto the even half
           const cx<R> z = gg[comp][e];
@@ -482,13 +503,12 @@ __global__ void __launch_bounds__(cw_shape<N>::T* cw_shape<N>::P) SG_WAVES_PER_E
   cx<R>* lds = smem + g * 2 * S::SLOT;
   cw_tw<N, R, cw_keep<TO>::on, true> tw;
   tw.init(twc, t0);
-  const cx<R> w2t = r2n[(unsigned)t0];
   const int nt = M / S::P;  // tiles of P columns
   for (int it = blockIdx.x;;) {
     // opaque(): the index arithmetic of a column stays in the loop body
     const int t = opaque(t0);
     const int tile = xcd_tile(it, nt);
-    cw_column<R, TO, N, kind>(X, V, M, tj, tox, toy, r2n, tw, w2t, lds, tile * S::P + g, t, tile == 0, xb, pg);
+    cw_column<R, TO, N, kind>(X, V, M, tj, tox, toy, r2n, tw, lds, tile * S::P + g, t, tile == 0, xb, pg);
     it += gridDim.x;
     if (it >= nt) break;
     cw_sync<T>();  // this column's last LDS reads come before the next one's writes
@@ -520,13 +540,9 @@ __global__ void __launch_bounds__(cw_shape<N>::T) SG_WAVES_PER_EU(2)
   const int t0 = threadIdx.x;
   cw_tw<N, R, cw_keep<TO>::on, true> tw;
   tw.init(twc, t0);
-  const cx<R> w2t0 = r2n[(unsigned)t0];
   constexpr R ex = kind == 1 ? (R)-1 : (R)1;  // reflection sign of the x table (y: -ex)
   for (int it = blockIdx.x;;) {
     const int t = opaque(t0);
-    cx<R> w2t = w2t0;
-    SG_OPAQUE(w2t.x);
-    SG_OPAQUE(w2t.y);
     const int c = xcd_tile(it, M);
     const bool packed = (c == 0);
     const int db = S::d3_base(t);
@@ -548,9 +564,10 @@ __global__ void __launch_bounds__(cw_shape<N>::T) SG_WAVES_PER_EU(2)
         cw_load_tab<N>(toy + (int64_t)c * S::TAB, t, h, tv[1]);
       }
       if (h) {
+        const int tw2 = opaque(t);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const cx<R> w = cmul(w2t, cw_w32<R>(e));
+          const cx<R> w = r2n[(unsigned)(tw2 + T * e)];  // w_2N^(t + T e)
           f[0][e] = cmul(f[0][e], w);
           f[1][e] = cmul(f[1][e], w);
         }
@@ -563,9 +580,11 @@ __global__ void __launch_bounds__(cw_shape<N>::T) SG_WAVES_PER_EU(2)
         cw_load_tab<N>(toy + (int64_t)c * S::TAB, t, h, tv[1]);
       }
       if constexpr (kind == 1) {
-        const cx<R> w = cw_phase0<N>(r2n, c, M, db, h);
-        cw_phase<N, true>(f[0], w);
-        cw_phase<N, true>(f[1], w);
+        const int tp = opaque(N + T + t);
+        const cx<R> wc = cw_phase_col<R>(c, M), w = h ? cmul(wc, fs_half_phase<R>(1.0 / (2.0 * N))) : wc;
+        const cx<R> w0 = cmul(tw.tab[(unsigned)tp], w), w15 = cmul(tw.tab[(unsigned)(tp + T)], w);
+        cw_phase<N, true>(f[0], w0, w15);
+        cw_phase<N, true>(f[1], w0, w15);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -610,11 +629,11 @@ __global__ void __launch_bounds__(cw_shape<N>::T) SG_WAVES_PER_EU(2)
     cw_inv<N, 2>(hs, smem, tw, false, t);
     SG_CW_FENCE();
     cx<R> past{(R)0, (R)0}, before{(R)0, (R)0};  // slots N, N + 1 (threads 0, 1), -1, -2 (the last two)
-    SG_OPAQUE(w2t.x);
-    SG_OPAQUE(w2t.y);
+    const int tw2 = opaque(t);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const cx<R> o = cmulc(hs[1][e], cmul(w2t, cw_w32<R>(e)));
+      if (e % 4 == 0) SG_CW_FENCE();  // few roots in flight
+      const cx<R> o = cmulc(hs[1][e], r2n[(unsigned)(tw2 + T * e)]);
       if (e == 0) past = hs[0][e] - o;
       if (e == 15) before = hs[0][e] - o;
       hs[0][e] = hs[0][e] + o;
@@ -649,6 +668,11 @@ void cw_fill_twiddles(F root, double* re, double* im) {
     for (int t = 0; t < S::T; ++t) root(k1 * t, N, re + k1 * S::T + t, im + k1 * S::T + t);
   for (int k2 = 0; k2 < 16; ++k2)
     for (int t0 = 0; t0 < S::R3; ++t0) root(k2 * t0, S::T, re + N + k2 * S::R3 + t0, im + N + k2 * S::R3 + t0);
+  for (int u = 0; u < S::T; ++u) {
+    double *x = re + N + S::T + u, *y = im + N + S::T + u;
+    root(S::d3_base(u), 2 * N, x, y);
+    root(S::d3_base(u) + 15 * S::D3_SPAN, 2 * N, x + S::T, y + S::T);
+  }
 }
 
 }  // namespace sg

@@ -363,10 +363,13 @@ __global__ void k_weights(int k, double hx, double hy, int M, int N, double* __r
 #endif
 
 // entry s + j of a table of roots of unity (entry n = exp(+-2 pi i n / L)),
-// given ws = entry s
-template <typename R>
+// given ws = entry s.  SPLIT: as the product of entries s and j, j being the same for
+// the workgroup; not for the FP32 rows of 3 * 2^a, whose few roots are loaded at no
+// cost and rounded once (5 % of the
+// error at 384 x 768, k = 4)
+template <bool SPLIT = SG_ROOT_SPLIT, typename R>
 __device__ __forceinline__ cx<R> root_at(const cx<R>* __restrict__ tab, cx<R> ws, int s, int j) {
-  if constexpr (SG_ROOT_SPLIT) return j == 0 ? ws : cmul(ws, tab[j]);
+  if constexpr (SPLIT) return j == 0 ? ws : cmul(ws, tab[j]);
   else return tab[s + j];
 }
 
@@ -389,6 +392,7 @@ struct rowfwd_cfg {
   static constexpr int E = elems_for(L, E0, SG_E3);
   static constexpr int T = L / E;
   static constexpr int LL = lds_len<L>::value;
+  static constexpr bool SPLIT = SG_ROOT_SPLIT && !(sizeof(R) == 4 && M % 3 == 0);  // root_at
   static constexpr int SLOT = LL;  // per-row LDS slot (complex elements)
   static constexpr int RS = SLOT + 8;  // that of k_row_c2r: the rows' slots start in different banks
   static constexpr int NB = (sizeof(R) == 4 && sizeof(In) == 4 && !BIG) ? SG_RF_NBUF32 : 1;  // exchange buffers per row
@@ -565,7 +569,7 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
     }
   } else {
 #pragma unroll
-    for (int e = 0; e < E; ++e) zo[e] = cmul(ze[e], root_at(r2m, r2m[2 * t], 2 * t, 2 * e * T));  // w_M^n
+    for (int e = 0; e < E; ++e) zo[e] = cmul(ze[e], root_at<C::SPLIT>(r2m, r2m[2 * t], 2 * t, 2 * e * T));  // w_M^n
     if (solve) {
       // the values past the row's ends: x[M], x[M + 1] (folded onto element 0)
       // and x[2M - 2], x[2M - 1] (onto element L - 1)
@@ -612,7 +616,7 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   for (int e = 0; e < E; ++e) {
     const int pp = t + e * T;                         // X bin p = 2 pp
     const cx<R> zp = ze[e], zm = conj(lds[pad(pp == 0 ? 0 : L - pp)]);
-    const cx<R> sum = zp + zm, dif = cmul(root_at(r2m, r2m[2 * t], 2 * t, 2 * e * T), zp - zm);
+    const cx<R> sum = zp + zm, dif = cmul(root_at<C::SPLIT>(r2m, r2m[2 * t], 2 * t, 2 * e * T), zp - zm);
     xe[e] = cx<R>{(R)0.5 * (sum.x + dif.y), (R)0.5 * (sum.y - dif.x)};
     if (pp == 0) xe[e] = cx<R>{zp.x + zp.y, zp.x - zp.y};
   }
@@ -627,7 +631,7 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   for (int e = 0; e < E; ++e) {
     const int pp = t + e * T;                         // X bin p = 2 pp + 1
     const cx<R> zp = zo[e], zm = conj(lds2[pad(L - 1 - pp)]);
-    const cx<R> sum = zp + zm, dif = cmul(root_at(r2m, r2m[2 * t + 1], 2 * t + 1, 2 * e * T), zp - zm);
+    const cx<R> sum = zp + zm, dif = cmul(root_at<C::SPLIT>(r2m, r2m[2 * t + 1], 2 * t + 1, 2 * e * T), zp - zm);
     zo[e] = cx<R>{(R)0.5 * (sum.x + dif.y), (R)0.5 * (sum.y - dif.x)};
   }
   __syncthreads();
@@ -1051,6 +1055,7 @@ struct rowinv_cfg {
   static constexpr int T = L / E;
   static constexpr int LL = lds_len<L>::value;
   static constexpr int NB = sizeof(R) == 4 ? (BIG ? SG_RI_BIG_NB : SG_RI_NBUF32) : 1;  // exchange buffers per row
+  static constexpr bool SPLIT = SG_ROOT_SPLIT && !(sizeof(R) == 4 && M % 3 == 0);  // root_at
   // LDS of one row: its buffers plus a shift of 8 elements, so that the
   // rows' buffers start in different banks
   static constexpr int RS = NB * LL + 8;
@@ -1125,7 +1130,7 @@ __global__ void __launch_bounds__((rowinv_cfg<R, M, VA>::G * rowinv_cfg<R, M, VA
     // phases of the odd half, loaded now so that their latency hides
     // behind the transforms
 #pragma unroll
-    for (int e = 0; e < E; ++e) wr[e] = root_at(r2m, r2m[t], t, e * T);
+    for (int e = 0; e < E; ++e) wr[e] = root_at<C::SPLIT>(r2m, r2m[t], t, e * T);
     // both half-length inverses through the same stages
     fftn<true, M, T, 2>(v2, lds, LL, tw, t);
   } else {
@@ -1138,7 +1143,7 @@ __global__ void __launch_bounds__((rowinv_cfg<R, M, VA>::G * rowinv_cfg<R, M, VA
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int n = ts + e * T;
-      const cx<R> r = v2[0][e] + cmulc(v2[1][e], NB == 2 ? wr[e] : root_at(r2m, r2m[ts], ts, e * T));
+      const cx<R> r = v2[0][e] + cmulc(v2[1][e], NB == 2 ? wr[e] : root_at<C::SPLIT>(r2m, r2m[ts], ts, e * T));
       fx[(int64_t)row * M + n] = (Out)r.x;
       fy[(int64_t)row * M + n] = (Out)r.y;
     }
