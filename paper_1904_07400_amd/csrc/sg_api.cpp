@@ -1205,8 +1205,8 @@ sg_status sg_bspline_coeffs(sg_plan p, const void* sigma, void* coeffs) {
     char* dst = (char*)coeffs + el * G.off;
     hipError_t e = hipSuccess;
     if (G.k >= 3) {
-      // long columns, whose pass is not in place, by way of the grid's spectra buffer
-      void* mid = G.N < kCoeffLong ? (void*)dst : G.X;
+      // the chunked column pass is not in place: by way of the grid's spectra buffer
+      void* mid = sg_coeff_long(G.M, G.N, G.k) ? G.X : (void*)dst;
       e = sg_launch_coeff_rows(prec, G.M, src, mid, G.N, G.k, p->st);
       if (e == hipSuccess) e = sg_launch_coeff_cols(prec, G.N, mid, dst, G.M, G.k, p->st);
     } else if (src != dst) {

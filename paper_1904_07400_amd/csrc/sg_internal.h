@@ -72,8 +72,8 @@ hipError_t sg_launch_spec_col(int N, const void* S, int M, void* tab, int kind, 
 int sg_twiddles(int prec, int pass, int len, const void* roots, void* out, hipStream_t st);
 hipError_t sg_launch_check_finite(int prec, const void* x, int64_t n, int* flag, hipStream_t st);
 hipError_t sg_launch_coeff_rows(int prec, int M, const void* src, void* dst, int nrows, int k, hipStream_t st);
-// from kCoeffLong rows on src and dst must not overlap, below they are one array
-constexpr int kCoeffLong = 1024;
+// src and dst must not overlap if sg_coeff_long, else they are one array
+bool sg_coeff_long(int M, int N, int k);
 hipError_t sg_launch_coeff_cols(int prec, int N, const void* src, void* dst, int M, int k, hipStream_t st);
 // Adjoint after the two forward row transforms of gx, gy (Xx, Xy
 // column-major like X): conjugate-spectrum column pass into Y (tiles of tj

@@ -1564,7 +1564,8 @@ __global__ void __launch_bounds__((coeff_cfg<M>::G * coeff_cfg<M>::T))
   }
 }
 
-// The column solve of columns below kCoeffLong, in place: P columns per workgroup.
+// The column solve of short columns and small grids (sg_coeff_long), in place: P
+// columns per workgroup.
 template <int N>
 struct coeffc_cfg {
   static constexpr int CH = elems_for(N, 16, 12);
@@ -1613,10 +1614,9 @@ __global__ void __launch_bounds__((coeffc_cfg<N>::P * coeffc_cfg<N>::T))
 // of 64 columns.  A thread does kCoeffRows rows; its recursions start bnd_reach
 // rows before and after them, where what it leaves out has decayed below 1e-18.
 // (One column per workgroup, read at the row stride, was bound by partial lines:
-// 89 us at 2048^2, FP32, for 32 MB; this one 11.  The line lies where the chunks'
-// serial rows stop being the longer ones: both systems k = 3, 5 at 1024^2 FP32 13.6,
-// 20.3 us against 27.0, 28.8, at 512^2 11.5, 18.2 against 11.4, 13.3.)  Fully unrolled, the rows in registers; the
-// 2.5 to 3.6 reads per value come from the caches.
+// 89 us at 2048^2, FP32, for 32 MB; this one 11.  For where the line lies see
+// sg_coeff_long.)  Fully unrolled, the rows in registers; the 2.5 to 3.6 reads per
+// value come from the caches.
 constexpr int kCoeffRows = 32;
 struct band_ldl {
   double l1[kBndLen], l2[kBndLen], id[kBndLen];  // multipliers of rows i - 1, i - 2; scale / pivot
@@ -2102,19 +2102,31 @@ static hipError_t coeff_rows_dispatch(int M, const R* src, R* dst, int nrows, in
   }
 }
 
+// Whether the columns take the chunked solve.  Its time is that of one chunk's
+// serial rows (k = 5: 12 us) until the chip is full, that of a workgroup per column
+// grows with the columns' partial lines.  Whole call, chunked against whole columns, FP32:
+// k = 3: 64 x 1024 11.3 against 9.9 us, 96 x 1536 11.5 / 10.7, 256 x 1024 11.9 /
+// 12.7, 64 x 2048 11.2 / 12.7, 4 x 4096 11.7 / 10.8, 4 x 8192 11.8 / 16.2, 1024^2
+// 14.1 / 27.6; k = 5: 256 x 1024 18.2 / 14.1, 4 x 8192 19.7 / 17.5, 256 x 2048 18.8 /
+// 20.0, 1024^2 20.8 / 29.0.  FP64 changes over at the same sizes.
+bool sg_coeff_long(int M, int N, int k) {
+  const int64_t cells = (int64_t)M * N;
+  if (N < 1024) return false;
+  if (k == 5) return cells >= (1 << 19);
+  return cells >= (1 << 18) || N >= 8192 || (N >= 2048 && cells >= (1 << 17));
+}
+
 template <typename R>
 static hipError_t coeff_cols_short(int N, R* data, int M, int sys, hipStream_t st) {
   switch (N) {
 #define CASE(SZ)                                                                                       \
-  case SZ:                                                                                             \
-    if constexpr (SZ < kCoeffLong) {                                                                   \
-      using C = coeffc_cfg<SZ>;                                                                        \
-      const int P = pow2_div(M, C::P);                                                                 \
-      hipLaunchKernelGGL((k_coeff_cols<R, SZ>), dim3(M / P), dim3(P * C::T), 0, st, data, M, sys);     \
-      return hipGetLastError();                                                                        \
-    }                                                                                                  \
-    return hipErrorInvalidValue;
-    SG_SIZES(CASE)
+  case SZ: {                                                                                           \
+    using C = coeffc_cfg<SZ>;                                                                          \
+    const int P = pow2_div(M, C::P);                                                                   \
+    hipLaunchKernelGGL((k_coeff_cols<R, SZ>), dim3(M / P), dim3(P * C::T), 0, st, data, M, sys);       \
+    return hipGetLastError();                                                                          \
+  }
+    SG_ROW_SIZES(CASE)
 #undef CASE
     default:
       return hipErrorInvalidValue;
@@ -2123,7 +2135,7 @@ static hipError_t coeff_cols_short(int N, R* data, int M, int sys, hipStream_t s
 
 template <typename R>
 static hipError_t coeff_cols_dispatch(int N, const R* src, R* dst, int M, int k, hipStream_t st) {
-  if (N < kCoeffLong) return src == dst ? coeff_cols_short<R>(N, dst, M, k, st) : hipErrorInvalidValue;
+  if (!sg_coeff_long(M, N, k)) return src == dst ? coeff_cols_short<R>(N, dst, M, k, st) : hipErrorInvalidValue;
   const int chunks = (N + kCoeffRows - 1) / kCoeffRows, w = chunks < 4 ? chunks : 4;
   const dim3 grid((M + 63) / 64 * ((chunks + w - 1) / w)), blk(64 * w);
   if (k == 3)
