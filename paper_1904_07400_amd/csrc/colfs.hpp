@@ -141,7 +141,7 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
                                            const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ twfs,
                                            const sg_bgrid* __restrict__ bg, cx<R>* smem,
                                            const cx<R>* __restrict__ xb, int pg, int x_tiled) {
-  const int xt = N == 8192 ? x_tiled : 0;
+  const int xt = (sizeof(R) == 4 && N == 8192) ? x_tiled : 0;  // as sg_x_tiled
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
   constexpr bool solve = MODE >= 2;
   constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);
@@ -597,7 +597,7 @@ __global__ void __launch_bounds__(N / E)
                 const TO* __restrict__ tox, const TO* __restrict__ toy, const cx<R>* __restrict__ r2n,
                 const cx<R>* __restrict__ twfs, const sg_bgrid* __restrict__ bg, int bord = 0,
                 const double* __restrict__ bc = nullptr, int x_tiled = 0) {
-  const int xt = N == 8192 ? x_tiled : 0;
+  const int xt = (sizeof(R) == 4 && N == 8192) ? x_tiled : 0;  // as sg_x_tiled
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
   constexpr bool solve = MODE >= 2;
   constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);
@@ -782,32 +782,15 @@ __global__ void __launch_bounds__(N / E)
       for (int e = 0; e < E; ++e) hs[h][e] = g1[0][e];
     }
   }
-  cx<R> acc[E];
   const int to = fresh_t();
-  cx<R> past{(R)0, (R)0}, before{(R)0, (R)0};  // slots N, N + 1 (threads 0, 1), -1, -2 (the last two)
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const cx<R> o = cmulc(hs[1][e], r2n[(unsigned)opaque(S::d1_index(to, e))]);
-    if (e == 0) past = hs[0][e] - o;
-    if (e == E - 1) before = hs[0][e] - o;
-    acc[e] = hs[0][e] + o;
-  }
-  if (!solve && bord) {
-    // the gradients found in the padding slots, to the threads of the ends
-    __syncthreads();
-    if (t < 2) smem[t] = past;
-    if (t >= T - 2) smem[2 + T - 1 - t] = before;
-    __syncthreads();
-    const cx<R> p0 = smem[0], p1 = smem[1], b0 = smem[2], b1 = smem[3];
-    const int len = bnd_reach(bord);
-    static_assert(S::B1 * S::LB2 >= kBndLen, "the ends lie in the first and the last element of a thread");
-    const int j0 = S::d1_index(to, 0), j1 = N - 1 - S::d1_index(to, E - 1);
-    if (j0 < len) acc[0] = bnd_add(acc[0], b0, b1, bc, j0);
-    if (j1 < len) acc[E - 1] = bnd_add(acc[E - 1], p0, p1, bc, j1);
-  }
+  // w_2N^-j times the odd half's element e
+  auto odd = [&](int e) { return cmulc(hs[1][e], r2n[(unsigned)opaque(S::d1_index(to, e))]); };
   cx<R>* out = Y + (int64_t)(c & 1) * (M / 2) * tj + (int64_t)(c >> 1) * tj;
   const int64_t jstride = (int64_t)M * tj;
   if constexpr (solve) {
+    cx<R> acc[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = hs[0][e] + odd(e);
     // D1 -> chunks of E (thread t: rows [t E, (t+1) E)) through slot 0, then
     // the y-solve (its LDS in the same slot, after the barrier)
     __syncthreads();
@@ -828,11 +811,34 @@ __global__ void __launch_bounds__(N / E)
       out[(int64_t)(j / tj) * jstride + (j % tj)] = cx<R>{(R)d[e].x, (R)d[e].y};
     }
   } else {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    auto put = [&](int e, cx<R> v) {
       const int j = S::d1_index(to, e);
-      out[(int64_t)(j / tj) * jstride + (j % tj)] = acc[e];
+      out[(int64_t)(j / tj) * jstride + (j % tj)] = v;
+    };
+    // the ends first, and each of the others on its own (FP64 columns of 8192: with
+    // all elements held across the exchange the call took 1.05 to 1.18 times as long)
+    {
+      const cx<R> o0 = odd(0), o1 = odd(E - 1);
+      cx<R> a0 = hs[0][0] + o0, a1 = hs[0][E - 1] + o1;
+      if (bord) {
+        // the gradients found in slots N, N + 1 (threads 0, 1) and -1, -2 (the last
+        // two), to the threads of the ends
+        __syncthreads();
+        if (t < 2) smem[t] = hs[0][0] - o0;
+        if (t >= T - 2) smem[2 + T - 1 - t] = hs[0][E - 1] - o1;
+        __syncthreads();
+        const cx<R> p0 = smem[0], p1 = smem[1], b0 = smem[2], b1 = smem[3];
+        const int len = bnd_reach(bord);
+        static_assert(S::B1 * S::LB2 >= kBndLen, "the ends lie in the first and the last element of a thread");
+        const int j0 = S::d1_index(to, 0), j1 = N - 1 - S::d1_index(to, E - 1);
+        if (j0 < len) a0 = bnd_add(a0, b0, b1, bc, j0);
+        if (j1 < len) a1 = bnd_add(a1, p0, p1, bc, j1);
+      }
+      put(0, a0);
+      put(E - 1, a1);
     }
+#pragma unroll
+    for (int e = 1; e < E - 1; ++e) put(e, hs[0][e] + odd(e));
   }
 }
 
