@@ -47,44 +47,25 @@ __device__ __forceinline__ cx<R> bnd_add(cx<R> v, cx<R> u0, cx<R> u1, const doub
   return {bnd_add(v.x, u0.x, u1.x, bc, i), bnd_add(v.y, u0.y, u1.y, bc, i)};
 }
 
-// The two sums of the line x(0), x(1), ... of N real values by one thread, its
-// loads 24 together.
-template <int N, typename F>
-__device__ __forceinline__ void bnd_sums(F x, int order, const double* __restrict__ bc, double (&s)[2]) {
-  constexpr int LEN = N < kBndLen ? N : kBndLen, B = LEN < 24 ? LEN : 24;
-  s[0] = s[1] = 0.0;
-#pragma unroll 1
-  for (int i0 = 0; i0 < LEN && i0 < bnd_reach(order); i0 += B) {
-    double v[B];
-#pragma unroll
-    for (int k = 0; k < B; ++k) v[k] = x(i0 + k < LEN ? i0 + k : LEN - 1);
-#pragma unroll
-    for (int k = 0; k < B; ++k)  // zero past the line's end and the reach
-      s[0] += (i0 + k < kBndLen ? bc[i0 + k] : 0.0) * v[k];
-    if (order == 5) {
-#pragma unroll
-      for (int k = 0; k < B; ++k) s[1] += (i0 + k < kBndLen ? bc[kBndLen + i0 + k] : 0.0) * v[k];
-    }
-  }
-}
-
-// The columns' padding values come from pass A in parts, one per group of rows of
+// The padding values of columns of more than one wave come from pass A in parts (the
+// shorter columns' threads sum their own), one per group of rows of
 // a size that depends on the row length and the precision only, so that the result
 // does not depend on the rows per workgroup (bnd_parts of them, in groups of gp
-// rows): part w of the value of slot N, N + 1, -1, -2 (i = 0 .. 3) of column c at
-// xb[(4 c + i) pg + w].
+// rows): part w of the value of slot N, N + 1, -1, -2 (i = 0 .. 3) of column c < M at
+// xb[4 (w M + c) + i], so that the rows of one group leave their parts of
+// neighbouring columns next to each other.
 __host__ __device__ constexpr int bnd_parts(int order, int n, int gp) {
   const int len = bnd_reach(order) < n ? bnd_reach(order) : n;
   return (len + gp - 1) / gp;
 }
 template <typename R>
-__device__ __forceinline__ cx<R> bnd_total(const cx<R>* __restrict__ p, int pg) {
+__device__ __forceinline__ cx<R> bnd_total(const cx<R>* __restrict__ p, int pg, int M) {
   double x = 0.0, y = 0.0;
   for (int w0 = 0; w0 < pg; w0 += 8) {
     // eight loads together, those past pg masked
     cx<R> z[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) z[i] = p[w0 + i < pg ? w0 + i : pg - 1];
+    for (int i = 0; i < 8; ++i) z[i] = p[(int64_t)4 * M * (w0 + i < pg ? w0 + i : pg - 1)];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       x += w0 + i < pg ? (double)z[i].x : 0.0;
@@ -96,9 +77,9 @@ __device__ __forceinline__ cx<R> bnd_total(const cx<R>* __restrict__ p, int pg) 
 // The value that thread t of the column's T >= 4 threads folds in: that of slot
 // N + t for t < 2, of slot t - T for the last two; zero elsewhere.
 template <int T, typename R>
-__device__ __forceinline__ cx<R> bnd_value(const cx<R>* __restrict__ xb, int pg, int c, int t) {
+__device__ __forceinline__ cx<R> bnd_value(const cx<R>* __restrict__ xb, int pg, int M, int c, int t) {
   if (!xb || (t >= 2 && t < T - 2)) return cx<R>{(R)0, (R)0};
-  return bnd_total(xb + (int64_t)(4 * c + (t < 2 ? t : 2 + T - 1 - t)) * pg, pg);
+  return bnd_total(xb + 4 * c + (t < 2 ? t : 2 + T - 1 - t), pg, M);
 }
 
 }  // namespace sg

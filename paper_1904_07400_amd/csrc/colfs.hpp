@@ -217,7 +217,7 @@ __device__ __forceinline__ void colfs_body(const cx<R>* __restrict__ X, cx<R>* _
   const TO* rowy = toy + (int64_t)c * (N + 1);
   const int itn = it + (int)gridDim.x;
   // the column's padding values (bnd.hpp), in the threads that fold them in
-  const cx<R> xv = solve ? cx<R>{(R)0, (R)0} : bnd_value<T>(xb, pg, c, t);
+  const cx<R> xv = solve ? cx<R>{(R)0, (R)0} : bnd_value<T>(xb, pg, M, c, t);
   // this column's table entries first, then (PF) the next column: loads
   // complete in order, so waiting for the entries leaves the prefetch in
   // flight

@@ -245,7 +245,7 @@ __global__ void __launch_bounds__(kC3T) SG_WAVES_PER_EU(SG_COLFS3_WPE)
   for (int e = 0; e < E; ++e) a[e] = col[(unsigned)at(e)];
   // the column's padding values (bnd.hpp), folded onto elements 0, 1 (lanes 0, 1)
   // and N - 1, N - 2 (lanes 63, 62); each wave of the radix-3 step meets all four
-  const cx<R> xv = solve ? cx<R>{(R)0, (R)0} : bnd_value<64>(xb, pg, c, lane);
+  const cx<R> xv = solve ? cx<R>{(R)0, (R)0} : bnd_value<64>(xb, pg, M, c, lane);
   const cx<R> end = lane < 2 ? xv : cx<R>{(R)0, (R)0}, start = lane >= 62 ? xv : cx<R>{(R)0, (R)0};
   TO tv[pre ? 4 : 1][pre ? E : 1];
   if constexpr (pre) {

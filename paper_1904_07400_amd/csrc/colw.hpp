@@ -335,7 +335,7 @@ __device__ __forceinline__ void cw_column(const cx<R>* __restrict__ X, cx<R>* __
 #pragma unroll
   for (int e = 0; e < 16; ++e) f[0][e] = col[(unsigned)(t + T * e)];
   // the column's padding values (bnd.hpp), in the threads that fold them in
-  const cx<R> xv = bnd_value<T>(xb, pg, c, t);
+  const cx<R> xv = bnd_value<T>(xb, pg, M, c, t);
   // the spectrum entries (x, y) of one half at this thread's output bins
   const int db = S::d3_base(t);
   auto load_tab = [&](int64_t p, int h, TO (&e)[2][16]) {

@@ -511,8 +511,8 @@ hipError_t launch_cols(sg_plan p, const GridClass& c, int tile, hipStream_t q, c
   if (G.fs)
     return sg_launch_colfs(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.tab_bytes, G.r2n,
                            pg, G.twfs, d, ng, q);
-  return sg_launch_col(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.r2n, pg, G.twB, d, ng, tile,
-                       c.var[1], q);
+  return sg_launch_col(prec, c.N, nullptr, nullptr, c.M, tj, nullptr, nullptr, G.kind, G.r2n, pg, c.k >= 3 ? c.k : 0,
+                       G.bcn, G.twB, d, ng, tile, c.var[1], q);
 }
 
 // The inverse row pass of one class (its launch variant and that variant's
@@ -1015,8 +1015,9 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
         }
         if (s == SG_OK) (ax ? G.bcn : G.bcm) = (double*)bnd[bk];
       }
-      // the columns' padding values, which pass A leaves for pass B
-      if (s == SG_OK && G.k >= 3) s = dev_alloc(p, &G.xb, cb * 4 * (size_t)G.M * sg_pad_parts(pc, G.M, G.N, G.k));
+      // the parts of the columns' padding values that pass A leaves for pass B
+      const int parts = G.k >= 3 ? sg_pad_parts(pc, G.M, G.N, G.k) : 0;
+      if (s == SG_OK && parts) s = dev_alloc(p, &G.xb, cb * 4 * (size_t)G.M * parts);
       if (s == SG_OK && fresh) s = build_spectra(p, G, roots64[2 * G.M], roots64[2 * G.N]);
     }
     p->grids.push_back(G);
@@ -1331,7 +1332,7 @@ sg_status sg_plan_classes(sg_plan p, int32_t* nclasses, int32_t* info, int32_t c
       o[3] = (int32_t)c.members.size();
       for (int pass = 0; pass < 3; ++pass) {
         const int t = sg_tile(prec, pass, pass == 1 ? c.N : c.M, c.var[pass], pass == 1 ? c.M : c.N,
-                              (int)c.members.size(), c.tile[pass], pass == 0 && c.k >= 3);
+                              (int)c.members.size(), c.tile[pass], pass == 0 && p->grids[c.members[0]].xb);
         o[4 + pass] = t;
       }
       o[7] = c.src;

@@ -43,7 +43,8 @@ int sg_default_variant(int prec, int pass, int len);
 int sg_max_tile(int prec, int pass, int len, int variant);
 // whether a grid's row spectra X are tiled (x_base in kcommon.hpp)
 int sg_x_tiled(int prec, int M, int N);
-// parts per padding value that pass A leaves for a grid of N rows of M
+// parts per padding value that pass A leaves for a grid of N rows of M; 0: the column
+// pass sums the values itself
 int sg_pad_parts(int prec, int M, int N, int order);
 // rows (passes 0, 2) or columns (1) per workgroup that a launch over ngrids grids
 // with `lines` of them uses when asked for tile (0: its default); parts: pass 0 of a
@@ -53,10 +54,11 @@ int sg_tile(int prec, int pass, int len, int variant, int lines, int ngrids, int
 // tj rows (sg_row_tile), the layout the inverse row pass reads.  kind: 0 for
 // odd k (tables of A, W = i A), 1 for even k (W = ph i A, ph the bin's
 // half-cell phase); tx, ty are the quarter tables of A in either case; pg: the
-// parts per padding value in the descriptors' xb, or 0.
+// parts per padding value in the descriptors' xb, or 0; order (0 for k < 3), bc: the
+// interpolation system and the columns' coefficient table.
 hipError_t sg_launch_col(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                         int kind, const void* r2n, int pg, const void* tw, const sg_bgrid* bg,
-                         int ngrids, int tile, int variant, hipStream_t st);
+                         int kind, const void* r2n, int pg, int order, const double* bc, const void* tw,
+                         const sg_bgrid* bg, int ngrids, int tile, int variant, hipStream_t st);
 int sg_row_tile(int prec, int M, int N);
 hipError_t sg_launch_row_inv(int prec, int M, const void* V, void* fx, void* fy, int nrows, int tj, const void* r2m,
                              const void* tw, const sg_bgrid* bg, int ngrids, int tile, int variant, hipStream_t st);

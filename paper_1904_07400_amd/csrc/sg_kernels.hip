@@ -411,6 +411,67 @@ struct rowfwd_cfg {
   static constexpr int EC = (SLOT / (2 * T)) < 1 ? 1 : ((SLOT / (2 * T)) > E ? E : SLOT / (2 * T));
 };
 
+// The two sums of bnd.hpp at both ends of a row of M reals, which the threads hold
+// as pairs z[e] = x[2 (t + e T)], x[2 (t + e T) + 1]: each of up to 32 lanes takes
+// its pairs' share, a tree over the lanes adds them (an order that does not depend
+// on the launch).  T <= 32: the thread's own pairs, both ends over the row's lanes.
+// T >= 64: the first 32 lanes take the row's last pairs and the last 32 its first, one
+// each, loaded once more where they are needed.  The loads leave with the row's own.
+// (By one thread at each end, 24 to 48 loads and multiply-adds in series, a step of
+// 1024 x 64, k = 5, FP32 took 26.4 us against 24.2.)
+template <typename R, typename In, int M, int E, int T>
+struct row_ends {
+  static constexpr bool OWN = T <= 32;
+  static constexpr int W = OWN ? T : 32;
+  static constexpr int NE = OWN ? ((kBndLen / 2 + T - 1) / T < E ? (kBndLen / 2 + T - 1) / T : E) : 1;
+  static constexpr int NS = OWN ? 2 : 1;  // ends per lane
+  static_assert(M / 2 == E * T && 64 >= kBndLen, "pairs");
+  double c[NS][NE][4];  // c0 of the pair's two elements, c1
+  R x[2];               // T >= 64: the elements
+  __device__ __forceinline__ void load(const In* __restrict__ s, int order, const double* __restrict__ bc, int t) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        // the pair's distance from its end; the table is zero from the reach on
+        int l = OWN ? (i ? T - 1 - t : t) + e * T : (t < W ? t : T - 1 - t);
+        l = l < kBndLen / 2 ? l : kBndLen / 2 - 1;
+        c[i][e][0] = bc[2 * l];
+        c[i][e][1] = bc[2 * l + 1];
+        if (order == 5) {
+          c[i][e][2] = bc[kBndLen + 2 * l];
+          c[i][e][3] = bc[kBndLen + 2 * l + 1];
+        }
+        if constexpr (!OWN) {
+          x[0] = (R)s[t < W ? M - 1 - 2 * l : 2 * l];
+          x[1] = (R)s[t < W ? M - 2 - 2 * l : 2 * l + 1];
+        }
+      }
+  }
+  // past: the values of the slots M, M + 1, in thread 0; before: of 2 M - 1, 2 M - 2,
+  // in thread T - 1
+  __device__ __forceinline__ void sum(const cx<R>* z, int order, cx<R>& past, cx<R>& before) const {
+    double v[2][2];  // [start, end of the row][value]
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      v[i][0] = v[i][1] = 0.0;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const cx<R> p = !OWN ? cx<R>{x[0], x[1]} : (i ? cx<R>{z[E - 1 - e].y, z[E - 1 - e].x} : z[e]);
+        v[i][0] += c[i][e][0] * (double)p.x + c[i][e][1] * (double)p.y;
+        if (order == 5) v[i][1] += c[i][e][2] * (double)p.x + c[i][e][3] * (double)p.y;
+      }
+#pragma unroll
+      for (int m = W / 2; m > 0; m /= 2) {
+        v[i][0] += __shfl_xor(v[i][0], m, W);
+        if (order == 5) v[i][1] += __shfl_xor(v[i][1], m, W);
+      }
+    }
+    past = cx<R>{(R)v[NS - 1][0], (R)v[NS - 1][1]};
+    before = cx<R>{(R)v[0][0], (R)v[0][1]};
+  }
+};
+
 // solve: the order (3, 4, 5) whose interpolation system the spectra hold, with
 // the row's coefficient table bc (bnd.hpp), or 0.  bcn (the columns' table): the
 // workgroups of a grid's first and last rows also leave, per bin and group of GP
@@ -444,18 +505,11 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   const bool active = row < nrows;
   cx<R>* lds = smem + g * SLOT * NB;
   cx<R>* lds2 = lds + (NB - 1) * SLOT;
-  // the weights of this workgroup's rows in the padding values beyond the end
-  // (side 0) and the start (side 1) of the columns
+  // whether this workgroup's rows count in the padding values beyond the end (side
+  // 0) or the start (side 1) of the columns
   constexpr int GP = C::GP;
   const int pg = bcn ? bnd_parts(solve, nrows, GP) : 0;
   const bool edge = bcn && (row0 < pg * GP || nrows - row0 - G < pg * GP);
-  __shared__ double pw[2][2][C::G];
-  if (edge)
-    for (int i = threadIdx.x; i < 4 * G; i += blockDim.x) {
-      const int v = i / (2 * G), side = i / G % 2, r = row0 + i % G;
-      const int far = side ? r : nrows - 1 - r;  // distance from that end
-      pw[v][side][i % G] = (r < nrows && far < kBndLen) ? bcn[v * kBndLen + far] : 0.0;
-    }
   // loads are unconditional (a row past nrows reads row 0 and is masked
   // afterwards), so that they issue together rather than one at a time
   // behind a branch each
@@ -464,27 +518,38 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
   // the parts that the nb bins b0 + bs pl in the transposed store's LDS give:
   // group q's of values v beyond the end and the start of the columns
   auto parts = [&](int b0, int bs, int nb, bool skw) {
-    for (int i = threadIdx.x; i < nb * G / GP; i += blockDim.x) {
-      const int pl = i / (G / GP), q = i % (G / GP) * GP;
+    for (int q = 0; q < G && row0 + q < nrows; q += GP)
 #pragma unroll
       for (int side = 0; side < 2; ++side) {
         const int at = (side ? row0 + q : nrows - GP - row0 - q) / GP;
-        if (at >= pg || row0 + q >= nrows) continue;
-        double s0x = 0.0, s0y = 0.0, s1x = 0.0, s1y = 0.0;
+        if (at >= pg) continue;
+        // the group's weights, by the rows' distance from that end (< kBndLen)
+        double w[2][GP];
 #pragma unroll
         for (int gg = 0; gg < GP; ++gg) {
-          const cx<R> z = smem[skw ? pad(pl * G + q + gg) : pl * G + q + gg];
-          s0x += pw[0][side][q + gg] * (double)z.x;
-          s0y += pw[0][side][q + gg] * (double)z.y;
-          s1x += pw[1][side][q + gg] * (double)z.x;
-          s1y += pw[1][side][q + gg] * (double)z.y;
+          const int far = GP * at + (side ? gg : GP - 1 - gg);
+          w[0][gg] = bcn[far];
+          w[1][gg] = bcn[kBndLen + far];
         }
-        cx<R>* o = xb + ((int64_t)(b0 + bs * pl) * 4 + 2 * side) * pg + at;
-        o[0] = cx<R>{(R)s0x, (R)s0y};
-        o[pg] = cx<R>{(R)s1x, (R)s1y};
+        for (int pl = threadIdx.x; pl < nb; pl += blockDim.x) {
+          double s0x = 0.0, s0y = 0.0, s1x = 0.0, s1y = 0.0;
+#pragma unroll
+          for (int gg = 0; gg < GP; ++gg) {
+            const cx<R> z = smem[skw ? pad(pl * G + q + gg) : pl * G + q + gg];
+            s0x += w[0][gg] * (double)z.x;
+            s0y += w[0][gg] * (double)z.y;
+            if (solve == 5) {  // zero otherwise
+              s1x += w[1][gg] * (double)z.x;
+              s1y += w[1][gg] * (double)z.y;
+            }
+          }
+          cx<R>* o = xb + 4 * ((int64_t)at * M + b0 + bs * pl) + 2 * side;
+          o[0] = cx<R>{(R)s0x, (R)s0y};
+          o[1] = cx<R>{(R)s1x, (R)s1y};
+        }
       }
-    }
   };
+  row_ends<R, In, M, E, T> ends;
   if constexpr (C::BIG) {
     // the even bins from load to store, then the odd ones (of the same input in
     // registers): one exchange buffer, half the registers
@@ -492,15 +557,11 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
 #pragma unroll
     for (int e = 0; e < E; ++e) z[e] = cx<R>{m1 * (R)s[2 * (t + e * T)], m1 * (R)s[2 * (t + e * T) + 1]};
     if (solve) {
-      double v[2];
-      if (t == 0) {
-        bnd_sums<M>([&](int i) { return (double)s[M - 1 - i]; }, solve, bc, v);
-        pv = cx<R>{m1 * (R)v[0], m1 * (R)v[1]};
-      }
-      if (t == T - 1) {
-        bnd_sums<M>([&](int i) { return (double)s[i]; }, solve, bc, v);
-        pv = cx<R>{m1 * (R)v[1], m1 * (R)v[0]};
-      }
+      ends.load(s, solve, bc, t);
+      cx<R> v, w;
+      ends.sum(z, solve, v, w);
+      if (t == 0) pv = cx<R>{m1 * v.x, m1 * v.y};
+      if (t == T - 1) pv = cx<R>{m1 * w.y, m1 * w.x};
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -559,6 +620,7 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
     const int n = t + e * T;
     ze[e] = cx<R>{m1 * (R)s[2 * n], m1 * (R)s[2 * n + 1]};
   }
+  if (solve) ends.load(s, solve, bc, t);
   if (full) {  // rows of 2M values (plan time): fold the upper half in
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -573,16 +635,15 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, In, M>::G * rowfwd_cfg<R, In, M
     if (solve) {
       // the values past the row's ends: x[M], x[M + 1] (folded onto element 0)
       // and x[2M - 2], x[2M - 1] (onto element L - 1)
-      double v[2];
+      cx<R> v, w;
+      ends.sum(ze, solve, v, w);  // of the row before the values are added
       if (t == 0) {
-        bnd_sums<M>([&](int i) { return (double)s[M - 1 - i]; }, solve, bc, v);
-        const cx<R> hi{m1 * (R)v[0], m1 * (R)v[1]};
+        const cx<R> hi{m1 * v.x, m1 * v.y};
         ze[0] = ze[0] + hi;
         zo[0] = zo[0] - hi;  // w_M^0 = 1
       }
       if (t == T - 1) {
-        bnd_sums<M>([&](int i) { return (double)s[i]; }, solve, bc, v);
-        const cx<R> hi{m1 * (R)v[1], m1 * (R)v[0]};
+        const cx<R> hi{m1 * w.y, m1 * w.x};
         ze[E - 1] = ze[E - 1] + hi;
         zo[E - 1] = zo[E - 1] - cmul(hi, r2m[2 * (L - 1)]);
       }
@@ -691,6 +752,58 @@ struct col_cfg {
   static constexpr int P0 = T >= WG ? 1 : WG / T;
   static constexpr int PL = (LB / BYTES) < 1 ? 1 : (LB / BYTES);
   static constexpr int P = P0 < PL ? P0 : PL;
+};
+
+// Whether the columns' padding values (bnd.hpp) are summed in the column pass itself,
+// from the threads' own elements: where the threads of a column lie in one wave, 32
+// or fewer.  A grid of few rows is all ends, and the parts that pass A leaves
+// otherwise come after its own store: forward rows of 32 x 32, k = 3, FP32 10.2 us
+// with them against 6.6, of 8192 x 8 35.9 against 18.8.  Longer columns: k_row_fwd.
+__host__ __device__ constexpr bool col_own_ends(int prec, int N) {
+  return N / elems_for(N, prec == 0 ? SG_COL_E64 : SG_COL_E32, SG_E3) <= 32;
+}
+// The values beyond the end (slots N, N + 1) and the start (-1, -2) of a column whose
+// elements t + e T the T threads hold in a: each thread's share, then a tree over
+// them.
+template <typename R, int E, int T>
+struct col_ends {
+  static constexpr int NE = (kBndLen + T - 1) / T < E ? (kBndLen + T - 1) / T : E;
+  double c[2][NE][2];
+  __device__ __forceinline__ void load(int order, const double* __restrict__ bc, int t) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        // distance from the start (i = 0), the end (1); the table's last entry is zero
+        int l = (i ? T - 1 - t : t) + e * T;
+        l = l < kBndLen ? l : kBndLen - 1;
+        c[i][e][0] = bc[l];
+        if (order == 5) c[i][e][1] = bc[kBndLen + l];
+      }
+  }
+  __device__ __forceinline__ void sum(const cx<R>* a, int order, cx<R> (&end)[2], cx<R> (&start)[2]) const {
+    cx<double> v[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      v[i][0] = v[i][1] = cx<double>{0.0, 0.0};
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const cx<R> z = a[i ? E - 1 - e : e];
+        v[i][0] = v[i][0] + cx<double>{c[i][e][0] * (double)z.x, c[i][e][0] * (double)z.y};
+        if (order == 5) v[i][1] = v[i][1] + cx<double>{c[i][e][1] * (double)z.x, c[i][e][1] * (double)z.y};
+      }
+#pragma unroll
+      for (int m = T / 2; m > 0; m /= 2) {
+        v[i][0] = v[i][0] + cx<double>{__shfl_xor(v[i][0].x, m, T), __shfl_xor(v[i][0].y, m, T)};
+        if (order == 5) v[i][1] = v[i][1] + cx<double>{__shfl_xor(v[i][1].x, m, T), __shfl_xor(v[i][1].y, m, T)};
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      start[q] = cx<R>{(R)v[0][q].x, (R)v[0][q].y};
+      end[q] = cx<R>{(R)v[1][q].x, (R)v[1][q].y};
+    }
+  }
 };
 
 // spectrum lookup helpers: real tables A with W = i A (odd k) or W = ph i A
@@ -807,12 +920,13 @@ __device__ __forceinline__ void col_product(const cx<R>* f, cx<R>* g, int half, 
 }
 
 // kind: 0 odd k, 1 even k (phased tables).  xb, pg: the parts of the
-// columns' padding values (bnd.hpp), or NULL.
+// columns' padding values (bnd.hpp), or NULL; col_own_ends: order (0 for k < 3) and bc,
+// the columns' coefficient table, in their place.
 template <typename R, typename TO, int N, int kind, int VA = 0>
 __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
     SG_WPE(R, COL) k_col(const cx<R>* __restrict__ X, cx<R>* __restrict__ V, int M, int tj, const TO* __restrict__ tox,
-          const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ xb, int pg,
-          const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
+          const TO* __restrict__ toy, const cx<R>* __restrict__ r2n, const cx<R>* __restrict__ xb, int pg, int order,
+          const double* __restrict__ bc, const cx<R>* __restrict__ tw, const sg_bgrid* __restrict__ bg) {
   if (bg) {  // batched: grid blockIdx.y of the class
     const sg_bgrid d = grid_desc(bg);
     X = reinterpret_cast<const cx<R>*>(d.X);
@@ -837,6 +951,10 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
   cx<R> a[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) a[e] = col[(unsigned)(t + e * T)];
+  constexpr bool own = col_own_ends(sizeof(R) == 4, N);
+  static_assert(own == (T <= 32), "the threads of one wave");
+  col_ends<R, E, own ? T : 32> ends;
+  if (own && order) ends.load(order, bc, t);
   // With four exchange buffers: every table entry of the four products is
   // loaded here, after the column (loads complete in order), so that their
   // latency overlaps the forward transforms (in order x even, y even, x odd, y
@@ -875,19 +993,14 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
     fo[e] = cmul(a[e], w2n[e]);
     fe[e] = a[e];
   }
-  if (xb) {
+  if (own ? order != 0 : xb != nullptr) {
     // the values past the column's ends, folded onto elements 0, 1 (slots N, N
     // + 1) and N - 1, N - 2 (slots -1, -2)
     cx<R> end[2], start[2];
-    if constexpr (T >= 4) {
-      end[0] = end[1] = start[0] = start[1] = bnd_value<T>(xb, pg, c, t);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        end[i] = bnd_total(xb + (int64_t)(4 * c + i) * pg, pg);
-        start[i] = bnd_total(xb + (int64_t)(4 * c + 2 + i) * pg, pg);
-      }
-    }
+    if constexpr (own)
+      ends.sum(a, order, end, start);
+    else
+      end[0] = end[1] = start[0] = start[1] = bnd_value<T>(xb, pg, M, c, t);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       // element i of thread i (or of thread 0 when it holds both)
@@ -1795,8 +1908,8 @@ static hipError_t launch_row_fwd_t(const In* src, int64_t src_ld, cx<R>* X, int 
 
 template <typename R, int N, int VA = 0>
 static hipError_t launch_col_t(const cx<R>* X, cx<R>* V, int M, int tj, const void* tx, const void* ty, int kind,
-                               const cx<R>* r2n, int pg, const cx<R>* tw, const sg_bgrid* bg, int ngrids,
-                               int tile, hipStream_t st) {
+                               const cx<R>* r2n, int pg, int order, const double* bc, const cx<R>* tw,
+                               const sg_bgrid* bg, int ngrids, int tile, hipStream_t st) {
   using C = col_cfg<R, N, VA>;
   using TO = typename tabs<R>::odd;
   const int P = pow2_div(M, pick_tile(tile, C::P, M, default_cols(C::P, C::T, M, bg ? ngrids : 1)));
@@ -1809,7 +1922,7 @@ static hipError_t launch_col_t(const cx<R>* X, cx<R>* V, int M, int tj, const vo
     constexpr int KD = decltype(kd)::value;
     dyn_lds_optin<&k_col<R, TO, N, KD, VA>>(C::P * col_bytes);
     hipLaunchKernelGGL((k_col<R, TO, N, KD, VA>), grid, dim3(P * C::T), lds, st, X, V, M, tj, tox, toy, r2n,
-                       (const cx<R>*)nullptr, pg, tw, bg);
+                       (const cx<R>*)nullptr, pg, order, bc, tw, bg);
   };
   if (kind == 1)
     go(std::integral_constant<int, 1>{});
@@ -1884,15 +1997,15 @@ static hipError_t row_fwd_dispatch(int M, const In* src, int64_t ld, cx<R>* X, i
 #if SG_IN_PART(2)
 template <typename R>
 static hipError_t col_dispatch(int N, const cx<R>* X, cx<R>* V, int M, int tj, const void* tx, const void* ty,
-                               int kind, const cx<R>* r2n, int pg, const cx<R>* tw, const sg_bgrid* bg,
-                               int ngrids, int tile, int variant, hipStream_t st) {
+                               int kind, const cx<R>* r2n, int pg, int order, const double* bc, const cx<R>* tw,
+                               const sg_bgrid* bg, int ngrids, int tile, int variant, hipStream_t st) {
   switch (N) {
 #define CASE(SZ)                                                                                        \
   case SZ:                                                                                              \
     if (sizeof(R) == 4 && variant == 1 && col_variants<SZ>())                                           \
-      return launch_col_t<R, SZ, col_variants<SZ>() ? 1 : 0>(X, V, M, tj, tx, ty, kind, r2n, pg, tw, bg, \
-                                                              ngrids, tile, st);                        \
-    return launch_col_t<R, SZ>(X, V, M, tj, tx, ty, kind, r2n, pg, tw, bg, ngrids, tile, st);
+      return launch_col_t<R, SZ, col_variants<SZ>() ? 1 : 0>(X, V, M, tj, tx, ty, kind, r2n, pg, order, \
+                                                              bc, tw, bg, ngrids, tile, st);            \
+    return launch_col_t<R, SZ>(X, V, M, tj, tx, ty, kind, r2n, pg, order, bc, tw, bg, ngrids, tile, st);
     SG_SIZES(CASE)
 #undef CASE
     default:
@@ -1939,13 +2052,13 @@ hipError_t sg_launch_row_fwd(int prec, int M, const void* src, int64_t ld, void*
 
 #if SG_IN_PART(2)
 hipError_t sg_launch_col(int prec, int N, const void* X, void* V, int M, int tj, const void* tx, const void* ty,
-                         int kind, const void* r2n, int pg, const void* tw, const sg_bgrid* bg,
-                         int ngrids, int tile, int variant, hipStream_t st) {
+                         int kind, const void* r2n, int pg, int order, const double* bc, const void* tw,
+                         const sg_bgrid* bg, int ngrids, int tile, int variant, hipStream_t st) {
   if (prec == 0)
     return col_dispatch<double>(N, (const cx<double>*)X, (cx<double>*)V, M, tj, tx, ty, kind,
-                                (const cx<double>*)r2n, pg, (const cx<double>*)tw, bg, ngrids, tile, 0, st);
+                                (const cx<double>*)r2n, pg, order, bc, (const cx<double>*)tw, bg, ngrids, tile, 0, st);
   return col_dispatch<float>(N, (const cx<float>*)X, (cx<float>*)V, M, tj, tx, ty, kind, (const cx<float>*)r2n,
-                             pg, (const cx<float>*)tw, bg, ngrids, tile, variant, st);
+                             pg, order, bc, (const cx<float>*)tw, bg, ngrids, tile, variant, st);
 }
 
 int sg_row_tile(int prec, int M, int N) {
@@ -2020,6 +2133,7 @@ static int pad_rows_t(int M) {
 int sg_x_tiled(int prec, int M, int N) { return prec == 1 && N == 8192 && M >= SG_RF_BIG32 && M % 3 != 0; }
 
 int sg_pad_parts(int prec, int M, int N, int order) {
+  if (col_own_ends(prec, N)) return 0;
   return bnd_parts(order, N, prec == 0 ? pad_rows_t<double>(M) : pad_rows_t<float>(M));
 }
 
