@@ -394,7 +394,6 @@ struct rowfwd_cfg {
   static constexpr int LL = lds_len<L>::value;
   static constexpr bool SPLIT = SG_ROOT_SPLIT && !(sizeof(R) == 4 && M % 3 == 0);  // root_at
   static constexpr int SLOT = LL;  // per-row LDS slot (complex elements)
-  static constexpr int RS = SLOT + 8;  // that of k_row_c2r: the rows' slots start in different banks
   static constexpr int NB = (sizeof(R) == 4 && sizeof(In) == 4 && !BIG) ? SG_RF_NBUF32 : 1;  // exchange buffers per row
   // rows per workgroup: more rows make longer segments of the transposed store
   static constexpr int WG = sizeof(R) == 4 ? SG_RF_THREADS32 : SG_RF_THREADS64;
@@ -405,6 +404,13 @@ struct rowfwd_cfg {
   // them per workgroup
   static constexpr int GP = G1 >= 4 ? 4 : (G1 >= 2 ? 2 : 1);
   static constexpr int G = G1 / GP * GP;
+  // k_row_c2r's slot.  FP32, whose rows are interleaved lane by lane there: 32 lanes
+  // hold 32 / G neighbouring elements of each of G rows, so the rows' slots start
+  // 32 / G words of 8 bytes apart (mod 32; 8 words past
+  // the padded row, all 16 rows of 512 or 1536 met in a few banks: adjoint of 512 x
+  // 8192 158 us, 146 so; 1536 x 8192 552, 514)
+  static constexpr int GB = 32 / pow2_div(1 << 20, G < 16 ? G : 16);
+  static constexpr int RS = sizeof(R) == 4 ? SLOT + (GB - SLOT % 32 + 32) % 32 : SLOT + 8;
   // two workgroups per CU where the LDS holds them
   static constexpr int WPE = BIG ? 4 : 1;
   // e-values per transposed-store chunk (2T bins per e, G rows)
@@ -1444,9 +1450,11 @@ __global__ void __launch_bounds__((rowfwd_cfg<R, R, M>::G * rowfwd_cfg<R, R, M>:
   extern __shared__ __align__(16) unsigned char sg_dyn_lds[];  // G * RS elements, sized at launch
   cx<R>* const smem = reinterpret_cast<cx<R>*>(sg_dyn_lds);
   const int G = blockDim.x / T;
-  // FP32 rows interleaved lane by lane, as in k_row_inv (8192^2: 402 -> 377 us;
-  // FP64, tiles of two rows, 10.8 -> 12.7 at 1024^2, so not there)
-  constexpr bool ILV = sizeof(R) == 4;
+  // FP32 rows interleaved lane by lane, as in k_row_inv (whole adjoint of 4096 x
+  // 2048 273 -> 260 us, 768 x 512 44.9 -> 41.6, level elsewhere; FP64, tiles of two rows,
+  // 10.8 -> 12.7 at 1024^2, so not there, and not for rows of one or two threads:
+  // 48 x 64 30.5 -> 34)
+  constexpr bool ILV = sizeof(R) == 4 && T >= 4;
   const int g = ILV ? threadIdx.x % G : threadIdx.x / T, t = ILV ? threadIdx.x / G : threadIdx.x % T;
   const int row = xcd_tile(blockIdx.x, gridDim.x) * G + g;
   const bool active = row < nrows;
