@@ -591,13 +591,13 @@ __global__ void __launch_bounds__(N / E)
 #ifndef SG_ADJ_OPQ
 #define SG_ADJ_OPQ 1
 #endif
-template <typename R, typename TO, int N, int MODE, int E, int SLOTS>
+template <typename R, typename TO, int N, int MODE, int E, int SLOTS, bool XT = false>
 __global__ void __launch_bounds__(N / E)
     k_colfs_adj(const cx<R>* __restrict__ Xx, const cx<R>* __restrict__ Xy, cx<R>* __restrict__ Y, int M, int tj,
                 const TO* __restrict__ tox, const TO* __restrict__ toy, const cx<R>* __restrict__ r2n,
                 const cx<R>* __restrict__ twfs, const sg_bgrid* __restrict__ bg, int bord = 0,
                 const double* __restrict__ bc = nullptr, int x_tiled = 0) {
-  const int xt = (sizeof(R) == 4 && N == 8192) ? x_tiled : 0;  // as sg_x_tiled
+  const int xt = XT ? x_tiled : 0;
   constexpr int kind = (MODE == 1 || MODE == 3) ? 1 : 0;
   constexpr bool solve = MODE >= 2;
   constexpr int SYS = MODE == 2 ? 3 : (MODE == 3 ? 4 : 5);

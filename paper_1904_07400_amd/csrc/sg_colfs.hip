@@ -300,8 +300,20 @@ static hipError_t launch_colfs_adj_m(const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y,
                                      const TO* toy, const cx<R>* r2n, const cx<R>* tw, const sg_bgrid* bg,
                                      int ngrids, int bord, const double* bc, hipStream_t st) {
   using Sel = colfs_adj_sel<R, N>;
-  hipLaunchKernelGGL((k_colfs_adj<R, TO, N, MODE, Sel::E, Sel::SLOTS>), dim3(M, bg ? ngrids : 1), dim3(N / Sel::E), 0,
-                     st, Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, bord, bc, sg_x_tiled(sizeof(R) == 4, M, N));
+  auto go = [&](auto xt) {
+    hipLaunchKernelGGL((k_colfs_adj<R, TO, N, MODE, Sel::E, Sel::SLOTS, decltype(xt)::value>), dim3(M, bg ? ngrids : 1),
+                       dim3(N / Sel::E), 0, st, Xx, Xy, Y, M, tj, tox, toy, r2n, tw, bg, bord, bc, (int)decltype(xt)::value);
+  };
+  // tiled row spectra: a kernel of its own (the choice made per element cost 3 % of
+  // the pass on grids without them, 764 -> 790 us at 4096 x 8192)
+  if constexpr (sizeof(R) == 4 && N == 8192) {
+    if (sg_x_tiled(1, M, N))
+      go(std::true_type{});
+    else
+      go(std::false_type{});
+  } else {
+    go(std::false_type{});
+  }
   return hipGetLastError();
 }
 

@@ -2135,9 +2135,12 @@ static int pad_rows_t(int M) {
       return 1;
   }
 }
-// Rows of the long form leave pass A four at a time; the columns of 8192 read the
-// tiles at no cost forward, 5 % adjoint (columns of 4096: pass A 88 -> 80 us, pass B
-// as much slower, so they stay column-major)
+// The long rows' form stores the bins of one parity at a time, four rows of each: 32-byte
+// pieces, two bins apart.  In tiles pass A takes 318 us against 434 at 8192^2, and the
+// columns of 8192 read them at 1 to 3 %.  Rows of 4096 hold neighbouring bins, and lose:
+// 4096 x 8192 in tiles, step 1387 -> 1411 us, adjoint 1284 -> 1308, 2048 x 8192 687
+// -> 704 and 618 -> 651; and the columns of 4096 lose what pass A gains (88 -> 80
+// us at 4096^2)
 int sg_x_tiled(int prec, int M, int N) { return prec == 1 && N == 8192 && M >= SG_RF_BIG32 && M % 3 != 0; }
 
 int sg_pad_parts(int prec, int M, int N, int order) {
