@@ -504,7 +504,7 @@ constexpr int kSideStreams = 4;
 hipError_t launch_cols(sg_plan p, const GridClass& c, int tile, hipStream_t q, const sg_bgrid* desc = nullptr) {
   const int prec = p->prec == SG_FP64 ? 0 : 1;
   const GridPlan& G = p->grids[c.members[0]];
-  const int pg = c.k >= 3 ? sg_pad_parts(prec, c.M, c.N, c.k) : 0;
+  const int pg = c.k >= 3 ? sg_pad_parts(prec, c.M, c.N, c.k, G.fs) : 0;
   const int ng = (int)c.members.size();
   const int tj = sg_row_tile(prec, c.M, c.N);
   const sg_bgrid* d = desc ? desc : c.desc;
@@ -1016,7 +1016,7 @@ sg_status sg_plan_create(sg_plan* out, const sg_grid* grids, int32_t ngrids, sg_
         if (s == SG_OK) (ax ? G.bcn : G.bcm) = (double*)bnd[bk];
       }
       // the parts of the columns' padding values that pass A leaves for pass B
-      const int parts = G.k >= 3 ? sg_pad_parts(pc, G.M, G.N, G.k) : 0;
+      const int parts = G.k >= 3 ? sg_pad_parts(pc, G.M, G.N, G.k, G.fs) : 0;
       if (s == SG_OK && parts) s = dev_alloc(p, &G.xb, cb * 4 * (size_t)G.M * parts);
       if (s == SG_OK && fresh) s = build_spectra(p, G, roots64[2 * G.M], roots64[2 * G.N]);
     }

@@ -43,9 +43,9 @@ int sg_default_variant(int prec, int pass, int len);
 int sg_max_tile(int prec, int pass, int len, int variant);
 // whether a grid's row spectra X are tiled (x_base in kcommon.hpp)
 int sg_x_tiled(int prec, int M, int N);
-// parts per padding value that pass A leaves for a grid of N rows of M; 0: the column
-// pass sums the values itself
-int sg_pad_parts(int prec, int M, int N, int order);
+// parts per padding value that pass A leaves for a grid of N rows of M whose columns
+// take the Stockham or a four-step pass; 0: the column pass sums the values itself
+int sg_pad_parts(int prec, int M, int N, int order, int four_step);
 // rows (passes 0, 2) or columns (1) per workgroup that a launch over ngrids grids
 // with `lines` of them uses when asked for tile (0: its default); parts: pass 0 of a
 // plan with k >= 3

@@ -761,12 +761,13 @@ struct col_cfg {
 };
 
 // Whether the columns' padding values (bnd.hpp) are summed in the column pass itself,
-// from the threads' own elements: where the threads of a column lie in one wave, 32
-// or fewer.  A grid of few rows is all ends, and the parts that pass A leaves
-// otherwise come after its own store: forward rows of 32 x 32, k = 3, FP32 10.2 us
-// with them against 6.6, of 8192 x 8 35.9 against 18.8.  Longer columns: k_row_fwd.
+// from the threads' own elements: where the threads of a column lie in one wave.  A
+// grid of few rows is all ends, and the parts that pass A leaves otherwise come
+// after its own store: forward rows of 32 x 32, k = 3, FP32 10.2 us with them against
+// 6.6, of 8192 x 8 35.9 against 18.8; step of 8192 x 512 119.5 us against 109.3, of
+// 512 x 512 24.1 against 22.9.  Longer columns: k_row_fwd.
 __host__ __device__ constexpr bool col_own_ends(int prec, int N) {
-  return N / elems_for(N, prec == 0 ? SG_COL_E64 : SG_COL_E32, SG_E3) <= 32;
+  return N / elems_for(N, prec == 0 ? SG_COL_E64 : SG_COL_E32, SG_E3) <= 64;
 }
 // The values beyond the end (slots N, N + 1) and the start (-1, -2) of a column whose
 // elements t + e T the T threads hold in a: each thread's share, then a tree over
@@ -958,8 +959,8 @@ __global__ void __launch_bounds__((col_cfg<R, N, VA>::P * col_cfg<R, N, VA>::T))
 #pragma unroll
   for (int e = 0; e < E; ++e) a[e] = col[(unsigned)(t + e * T)];
   constexpr bool own = col_own_ends(sizeof(R) == 4, N);
-  static_assert(own == (T <= 32), "the threads of one wave");
-  col_ends<R, E, own ? T : 32> ends;
+  static_assert(own == (T <= 64), "the threads of one wave");
+  col_ends<R, E, own ? T : 64> ends;
   if (own && order) ends.load(order, bc, t);
   // With four exchange buffers: every table entry of the four products is
   // loaded here, after the column (loads complete in order), so that their
@@ -2143,8 +2144,8 @@ static int pad_rows_t(int M) {
 // us at 4096^2)
 int sg_x_tiled(int prec, int M, int N) { return prec == 1 && N == 8192 && M >= SG_RF_BIG32 && M % 3 != 0; }
 
-int sg_pad_parts(int prec, int M, int N, int order) {
-  if (col_own_ends(prec, N)) return 0;
+int sg_pad_parts(int prec, int M, int N, int order, int four_step) {
+  if (!four_step && col_own_ends(prec, N)) return 0;
   return bnd_parts(order, N, prec == 0 ? pad_rows_t<double>(M) : pad_rows_t<float>(M));
 }
 

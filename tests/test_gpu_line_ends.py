@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 SIZES = [(8, 8), (16, 12), (32, 8), (96, 4), (192, 8), (256, 12), (512, 8), (768, 16), (1024, 8), (1536, 4), (4096, 4),
          (8192, 8),
-         (8, 16), (12, 24), (4, 64), (8, 128), (8, 192), (16, 256), (12, 384), (8, 512), (4, 768)]
+         (8, 16), (12, 24), (4, 64), (8, 128), (8, 192), (16, 256), (12, 384), (8, 512), (4, 768), (8, 1024),
+         (12, 1536)]
 
 
 @pytest.mark.parametrize("k", [3, 4, 5])
