@@ -1889,8 +1889,12 @@ static inline int pick_tile(int tile, int cap, int n, int dflt) {
 template <typename R, int M>
 static int rows_fwd_tile(int tile, int nrows, int ngrids, bool parts) {
   using C = rowfwd_cfg<R, R, M>;
-  // two rows: 16- or 32-byte pieces of X; whole groups where it leaves parts
-  const int g = pick_tile(tile, C::G, nrows, default_rows(C::G, C::T, nrows, ngrids, 256, 2));
+  // two rows: 16- or 32-byte pieces of X; whole groups where it leaves parts.  The long
+  // form, whose threads take a row's halves in turn, spreads few rows over one
+  // workgroup each (8192 x 64: step 49.1 -> 46.5 us, adjoint 69.2 -> 60.2; 256 rows:
+  // 68.4 -> 70.3, so not there)
+  const int least = C::BIG && (int64_t)nrows * ngrids <= 128 ? 1 : 2;
+  const int g = pick_tile(tile, C::G, nrows, default_rows(C::G, C::T, nrows, ngrids, 256, least));
   return parts ? (g + C::GP - 1) / C::GP * C::GP : g;
 }
 template <typename R, int M, int VA>
