@@ -2355,12 +2355,16 @@ static hipError_t launch_col_adj_t(const cx<R>* Xx, const cx<R>* Xy, cx<R>* Y, i
   const int lds = P * C::SLOT * (int)sizeof(cx<R>);
   const TO* tox = (const TO*)tx;
   const TO* toy = (const TO*)ty;
+  auto go = [&](auto kd) {
+    constexpr int KD = decltype(kd)::value;
+    dyn_lds_optin<&k_col_adj<R, TO, N, KD>>(C::P * C::SLOT * (int)sizeof(cx<R>));
+    hipLaunchKernelGGL((k_col_adj<R, TO, N, KD>), grid, dim3(P * C::T), lds, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
+                       bc, tw, bg);
+  };
   if (kind == 1)
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 1>), grid, dim3(P * C::T), lds, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
-                       bc, tw, bg);
+    go(std::integral_constant<int, 1>{});
   else
-    hipLaunchKernelGGL((k_col_adj<R, TO, N, 0>), grid, dim3(P * C::T), lds, st, Xx, Xy, Y, M, tj, tox, toy, r2n, solve,
-                       bc, tw, bg);
+    go(std::integral_constant<int, 0>{});
   return hipGetLastError();
 }
 
