@@ -22,14 +22,19 @@ namespace sg {
 // prefetching loop (odd k; even k 0.226 against 0.314), the adjoint 0.192
 // against 0.314.  At 2048 the forward passes are level for odd k (0.055 against
 // 0.054 ms) and it spills for even k (0.069 against 0.057), and both directions
-// read one order of the tables.
+// read one order of the tables.  On grids of fewer than 128 columns, where a column's
+// own time counts, the forward pass is up to 4 us behind the four-step kernel's
+// 512 threads (4 x 4096, k = 1, step 21.3 us against 25.0) and the adjoint 3 us ahead;
+// the four-step kernel on these tables, read entry by entry, takes 39.6.
 template <typename R, int N>
 constexpr bool colw_len() {
   return sizeof(R) == 4 && N == 4096;
 }
 
-// elements per thread, LDS slots and component split per precision and
-// length (chosen so that no kernel spills registers)
+// elements per thread, LDS slots and component split per precision and length, chosen
+// for the fewest spilled registers.  Forward scratch per lane: FP64 0 to 36 bytes up to
+// 4096, 88 to 488 at 8192; FP32 none, but 120 for even k with hi + lo tables at 2048;
+// k_colw 76 (hi + lo tables 100, 112)
 template <typename R, int N>
 struct colfs_sel {
   static constexpr bool ok = false;
