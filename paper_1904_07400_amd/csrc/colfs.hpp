@@ -815,8 +815,14 @@ __global__ void __launch_bounds__(N / E)
       const int j = S::d1_index(to, e);
       out[(int64_t)(j / tj) * jstride + (j % tj)] = v;
     };
-    // the ends first, and each of the others on its own (FP64 columns of 8192: with
-    // all elements held across the exchange the call took 1.05 to 1.18 times as long)
+    // the ends first.  Of 16 elements each of the others is formed on its own (FP64
+    // columns of 8192: with all of them held across the exchange the call took 1.05 to
+    // 1.18 times as long); of 8 all are formed before it
+    constexpr bool HOLD = E == 8;
+    cx<R> mid[HOLD ? E : 1];
+    if constexpr (HOLD)
+#pragma unroll
+      for (int e = 1; e < E - 1; ++e) mid[e] = hs[0][e] + odd(e);
     {
       const cx<R> o0 = odd(0), o1 = odd(E - 1);
       cx<R> a0 = hs[0][0] + o0, a1 = hs[0][E - 1] + o1;
@@ -838,7 +844,7 @@ __global__ void __launch_bounds__(N / E)
       put(E - 1, a1);
     }
 #pragma unroll
-    for (int e = 1; e < E - 1; ++e) put(e, hs[0][e] + odd(e));
+    for (int e = 1; e < E - 1; ++e) put(e, HOLD ? mid[HOLD ? e : 0] : hs[0][e] + odd(e));
   }
 }
 
