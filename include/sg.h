@@ -62,9 +62,11 @@ typedef enum {
 
 typedef enum {
   SG_FP64 = 0,       /* every per-step array double; FFT and products in FP64 */
-  SG_FP32_SPLIT = 1  /* float arrays; coefficient solve in FP64, FFT in FP32 with
-                        FP64-derived twiddles; kernel spectra as hi+lo float pairs (as single floats
-                        for ny = 2048, 4096, 8192 unless SG_FLAG_SPECTRA_SPLIT) */
+  SG_FP32_SPLIT = 1  /* float arrays; FFT and products in FP32 with FP64-derived twiddles; kernel
+                        spectra, for k >= 3 with the inverse symbols of the interpolation systems,
+                        formed in FP64 and kept as hi+lo float pairs (as single floats for ny = 2048,
+                        4096, 8192 unless SG_FLAG_SPECTRA_SPLIT); the systems' values at the ends of
+                        the lines summed in FP64.  sg_bspline_coeffs solves the systems in FP64 */
 } sg_precision;
 
 /* One grid.  Cell sizes are dx = (x1-x0)/nx, dy = (y1-y0)/ny (Sec. 2, grid
@@ -126,12 +128,14 @@ sg_status sg_weights(sg_plan p, int32_t g, double* wx, double* wy);
  * (z_system) and (C_system), C = 0 outside the grid; for k = 4, 5 the
  * systems of the same construction with the cubic spline's values
  * (1, 4, 1) / 6 and the quartic's (1, 76, 230, 76, 1) / 384 per axis.  Packed buffers;
- * sigma and coeffs may alias. */
+ * sigma and coeffs may alias.  A cell depends on values further than 24, 32, 42
+ * cells away (k = 3, 4, 5) below rounding, and a non-finite value reaches the cells of
+ * its neighbourhood (at least these, at most 96 cells away), not all of its line. */
 sg_status sg_bspline_coeffs(sg_plan p, const void* sigma, void* coeffs);
 
-/* sigma -> (Fx, Fy) at the cell centres for every grid of the plan:
- * coefficient solve, then one forward and two inverse zero-padded FFT
- * convolutions (Sec. 4.2).  Packed buffers; fx and fy must not alias sigma
+/* sigma -> (Fx, Fy) at the cell centres for every grid of the plan: one
+ * forward and two inverse zero-padded FFT convolutions (Sec. 4.2), for k >= 3
+ * with the interpolation systems of sg_bspline_coeffs inside them.  Packed buffers; fx and fy must not alias sigma
  * or each other.
  *
  * Batching: the plan groups its grids into classes of equal (nx, ny, order);
@@ -190,9 +194,9 @@ sg_status sg_plan_classes(sg_plan p, int32_t* nclasses, int32_t* info, int32_t c
 sg_status sg_plan_tuning(sg_plan p, int32_t cls, int32_t* out);
 
 /* Adjoint of sg_forces: gsigma = d<gfx,Fx> + <gfy,Fy> / d sigma, i.e. the
- * transposed convolutions (correlation with the weights) followed by the
- * transposed coefficient solve (the matrices of Eqs. (z_system) and
- * (C_system) are symmetric).  Packed buffers; gsigma must not alias the
+ * transposed convolutions (correlation with the weights), with the
+ * transposed interpolation systems inside them (the matrices of Eqs.
+ * (z_system) and (C_system) are symmetric).  Packed buffers; gsigma must not alias the
  * inputs. */
 sg_status sg_forces_adjoint(sg_plan p, const void* gfx, const void* gfy, void* gsigma);
 
