@@ -648,7 +648,7 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32",
-        "precision_form": "FP32-split: f32 FFTs and products, f64 coefficient solve, f32 spectra "
+        "precision_form": "FP32-split: f32 FFTs and products, f64 symbols and end sums of the interpolation systems, f32 spectra "
                           "(the hi+lo spectra form is timed beside it: spectra_split)",
         "data": "synthetic",
         "config": {"workload": f"{n}x{n} cells on [-1,1]^2, k={k}, sigma = 32 seeded Gaussian clumps x taper "

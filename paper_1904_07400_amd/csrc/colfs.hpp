@@ -1,5 +1,6 @@
-// Column pass for long columns (N = 2048, 4096, 8192) on the four-step transform
-// of fft4.hpp: one column of the row spectra per workgroup of N / E threads.
+// Column pass for long columns (N = 2048, 8192, in FP64 also 1024 and 4096) on the
+// four-step transform of fft4.hpp: one column of the row spectra per workgroup of N / E
+// threads.
 //
 // Per column p (a bin of the row transforms; column 0 carries the real bins
 // p = 0 and p = M packed as U = C_0 + i C_M):
@@ -21,6 +22,10 @@
 // so that no exchange needs a barrier before its writes; AREAS = 1 gives one
 // area of two slots (FP64, or N = 8192 in FP32), whose exchanges take a
 // barrier before their writes as well.
+//
+// The library launches MODE 0 and 1 without PF; the others (the system solved on the
+// column, the prefetching loop, N = 4096 and 1024 in FP32) are compiled by the CPU
+// emulation's cases of them only.
 #pragma once
 #include "bnd.hpp"
 #include "fft4.hpp"
@@ -119,9 +124,6 @@ struct colfs_cfg {
 #ifndef SG_COLFS_WPE_D2048
 #define SG_COLFS_WPE_D2048 2
 #endif
-#ifndef SG_COLFS_WPE_F4096
-#define SG_COLFS_WPE_F4096 1
-#endif
 #ifndef SG_COLFS_WPE_F2048
 #define SG_COLFS_WPE_F2048 3
 #endif
@@ -129,7 +131,7 @@ template <typename R, int N>
 struct colfs_wpe {
   static constexpr int value =
       sizeof(R) == 8 ? (N == 2048 ? SG_COLFS_WPE_D2048 : 1)
-                     : (N == 4096 ? SG_COLFS_WPE_F4096 : (N == 2048 ? SG_COLFS_WPE_F2048 : 1));
+                     : (N == 2048 ? SG_COLFS_WPE_F2048 : 1);
 };
 
 // OPQ: the thread index through opaque() (as in the prefetching loop), so

@@ -14,8 +14,8 @@
 // sub-transform at n = lane + 64 e (e < E = L / 64) and, after the forward,
 // register r at k = lane + 64 r, i.e. bin 3 (lane + 64 r) + q.
 //
-// The column is otherwise processed as in colfs.hpp (y-solve, forward of the
-// zero-padded 2N column as even and odd bins, products with the spectra,
+// The column is otherwise processed as in colfs.hpp (padding values of k >= 3, or,
+// MODE >= 2, the y-solve; forward of the zero-padded 2N column as even and odd bins, products with the spectra,
 // four inverses cropped to N, V(p) and V(2M - p) in the tiled layout):
 //  - the odd-bin input x_j w_2N^j shares the radix-3 reads of x: its radix-3
 //    weights are (w_6 w_3^q)^r, its twiddle w_2N^(n (2q + 1));
@@ -23,10 +23,11 @@
 //    inverse's twiddle by the writer, and w_2N^(-L r) = w_6^-r, applied by
 //    the reader.
 // LDS: four slots of one padded column.  Slot 0 holds x for the forward
-// radix-3 step, slots 2 and 3 the y-solve's scratch and then the waves'
+// radix-3 step, slots 2 and 3 (the y-solve's scratch and then) the waves'
 // sub-transform areas ([L q, L q + L) of each slot, touched by wave q only),
 // all four the inverse radix-3 exchange.  Workgroup barriers: after x is
-// written, before and after the inverse exchange, and those of the y-solve.
+// written, before and after the inverse exchange (and those of the y-solve).
+// The library launches MODE 0 and 1.
 #pragma once
 #include <type_traits>
 

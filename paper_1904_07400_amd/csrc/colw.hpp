@@ -16,7 +16,10 @@
 // barrier.  The inverse runs the steps backwards and takes the forward's
 // output order.  Against the four-step form of fft4.hpp (8 elements per
 // thread, three exchanges per transform): two exchanges, half the threads,
-// and so two independent workgroups per compute unit at N = 4096.
+// and so two independent workgroups per compute unit at N = 4096, the length that
+// the library launches (N = 256 .. 2048, P columns per wave, in the CPU emulation).
+// Its registers do not hold all of it: 76 bytes of scratch per lane forward (hi + lo
+// tables 100, even k 112), none in the adjoint with single-float tables.
 //
 // LDS slot: element (k1, t1 or k2, t0) at k1 ROW + STR (t1 or k2) + t0, STR =
 // R3 + 1; ROW is chosen so that the 32 lanes of one access of 8-byte words
